@@ -556,10 +556,291 @@ __device__ __forceinline__ void ls_substitute(const double2 *F, int ld, const do
     if (lane == 0) *info = 0;
 }
 
-// Cholesky solve of (A + delta I) h = b in FP64 by one wave, delta = ridge *
-// mean(Re diag A).  Lane l owns rows l, l + 64, ... (R slots).  The factor is
-// stored by columns, F[k ld + r] = L[r][k] (ld = 64 in LDS, where K <= 64,
-// else K), zero above the diagonal, so the lanes read one column at
+// 1 / sqrt(x) for x > 0 in FP64: the hardware estimate (relative error about
+// 2^-24) and one third-order step, whose remaining error is below FP64
+// rounding; of the largest finite number where x is infinite (the step would
+// give NaN).
+__device__ __forceinline__ double ls_rsqrt(double x)
+{
+    x = fmin(x, 1.7976931348623157e308);
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-(x * y), y, 1.0);
+    return fma(y * e, fma(0.375, e, 0.5), y);
+}
+
+// Cholesky solve of (A + delta I) h = b in FP64 for K <= kLsPanelMaxK, delta =
+// ridge * mean(Re diag A): one workgroup of eight waves, the lower triangle
+// and the extra row conj(b) packed by columns in LDS (R (R + 1) / 2 complex128,
+// R = K + 1; K = 139 fits 160 KiB).  Factoring the extra
+// row along with the others is the forward substitution: row K of the factor
+// is y^H with L y = b.
+//
+// The columns form a serial chain -- pivot, 1 / sqrt, scale, update of the next
+// column -- which is what bounds the solve (the arithmetic of K = 81 is 2 us of
+// one CU).  So panels of kLsPanel columns are factored by wave 0 alone in
+// registers, lane = row, values of other rows by readlane: no LDS round trip
+// and no barrier inside a panel.  The other seven waves meanwhile subtract
+// the panel before from the columns past this one (2 x 2 entries per thread
+// over the triangle); then all waves bring the next panel's columns up to
+// date.  Two barriers per panel instead of one per column.
+// Measured on MI355X: K = 33 in 18 us (load 2, panels 13.5, substitution 2.5)
+// and K = 81 in 51 us; a left-looking column at a time took 30 us (four waves,
+// factor in LDS) and 348 us (one wave, factor in memory).  A panel column takes
+// about 600 cycles of one wave's issue (some 55 FP64 and readlane instructions).
+// info = 0, or j + 1 when the pivot of column j is not positive (h is NaN).
+constexpr int kLsPanel = 8;
+constexpr int kLsPanelWaves = 8;
+constexpr int kLsPanelMaxK = 139;
+constexpr size_t ls_panel_lds(int K) { return (size_t)(K + 1) * (K + 2) / 2 * sizeof(double2); }
+static_assert(ls_panel_lds(kLsPanelMaxK) + 2048 <= 160 * 1024, "the triangle does not fit LDS");
+
+// Columns j0 .. j0 + 7 by one wave (rows j0 + lane + 64 s); returns 0 or the
+// 1-based column of a pivot that is not positive.
+template <int S>
+__device__ __forceinline__ int ls_panel_factor(double2 *F, double *invd, int K, int j0, int lane)
+{
+    const int R = K + 1;
+    double id = 0.0;
+    double2 a[S][kLsPanel];
+#pragma unroll
+    for (int q = 0; q < kLsPanel; ++q) {
+        const int j = j0 + q, base = j * R - j * (j + 1) / 2;
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const int r = j0 + lane + 64 * s;
+            a[s][q] = j < K && r >= j && r < R ? F[base + r] : make_double2(0.0, 0.0);
+        }
+    }
+    // Straight-line code: columns past K are zeros and come to NaN, which goes
+    // nowhere, and a failed pivot only notes its column.
+    int fail = 0;
+#pragma unroll
+    for (int q = 0; q < kLsPanel; ++q) {
+        const double piv = ls_bcast(a[0][q].x, q);
+        fail = fail == 0 && j0 + q < K && !(piv > 0.0) ? j0 + q + 1 : fail;
+        const double inv = ls_rsqrt(piv);
+        if (lane == q) id = inv;
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            a[s][q].x *= inv;
+            a[s][q].y *= inv;
+        }
+#pragma unroll
+        for (int c = q + 1; c < kLsPanel; ++c) {
+            const double cx = ls_bcast(a[0][q].x, c), cy = ls_bcast(a[0][q].y, c);   // L[j0 + c][j0 + q]
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                a[s][c].x = fma(-a[s][q].x, cx, a[s][c].x);
+                a[s][c].x = fma(-a[s][q].y, cy, a[s][c].x);
+                a[s][c].y = fma(-a[s][q].y, cx, a[s][c].y);
+                a[s][c].y = fma(a[s][q].x, cy, a[s][c].y);
+            }
+        }
+    }
+    if (lane < kLsPanel && j0 + lane < K) invd[j0 + lane] = id;
+#pragma unroll
+    for (int q = 0; q < kLsPanel; ++q) {
+        const int j = j0 + q, base = j * R - j * (j + 1) / 2;
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const int r = j0 + lane + 64 * s;
+            if (j < K && r >= j && r < R) F[base + r] = a[s][q];
+        }
+    }
+    return fail;
+}
+
+// acc -= a conj(c)
+__device__ __forceinline__ void ls_sub(double2 &acc, double2 a, double2 c)
+{
+    acc.x = fma(-a.x, c.x, acc.x);
+    acc.x = fma(-a.y, c.y, acc.x);
+    acc.y = fma(-a.y, c.x, acc.y);
+    acc.y = fma(a.x, c.y, acc.y);
+}
+
+template <int S>
+__global__ void __launch_bounds__(64 * kLsPanelWaves) ls_solve_panel_kernel(const double2 *__restrict__ A,
+                                                                            const double2 *__restrict__ b, int K,
+                                                                            double ridge, float2 *__restrict__ h,
+                                                                            int32_t *__restrict__ info)
+{
+    extern __shared__ double2 ls_smem[];
+    __shared__ double invd[kLsPanelMaxK];   // 1 / L[j][j]
+    __shared__ int bad;
+    double2 *F = ls_smem;
+    constexpr int T = 64 * kLsPanelWaves;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int R = K + 1;
+    const auto base = [R](int k) { return k * R - k * (k + 1) / 2; };   // F[base(k) + r] = entry (r, k)
+    double tr = 0.0;
+#pragma unroll
+    for (int t = 0; t < S; ++t) {
+        const int i = lane + 64 * t;
+        tr += i < K ? A[(int64_t)i * K + i].x : 0.0;
+    }
+    const double delta = ridge * ls_wave_sum(tr) / K;
+    if (tid == 0) bad = 0;
+    // the lower triangle: wave w the rows w, w + 8, ..., lane = column, U rows in flight
+    constexpr int U = 8 / S + 1;
+    for (int r0 = w; r0 < R; r0 += U * kLsPanelWaves) {
+        double2 v[U][S];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int t = 0; t < S; ++t) {
+                const int r = r0 + u * kLsPanelWaves, k = lane + 64 * t;
+                v[u][t] = make_double2(0.0, 0.0);
+                if (r < R && k <= r && k < K) v[u][t] = r < K ? A[(int64_t)r * K + k] : b[k];
+            }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int t = 0; t < S; ++t) {
+                const int r = r0 + u * kLsPanelWaves, k = lane + 64 * t;
+                double2 x = v[u][t];
+                if (r == K) x.y = -x.y;
+                if (r == k) x = make_double2(x.x + delta, 0.0);
+                if (r < R && k <= r && k < K) F[base(k) + r] = x;
+            }
+    }
+    __syncthreads();
+
+    for (int j0 = 0; j0 < K; j0 += kLsPanel) {
+        if (w == 0) {
+            __builtin_amdgcn_s_setprio(3);   // the chain before the other wave of its SIMD
+            int fail;
+            if (S == 3 && R - j0 > 128)
+                fail = ls_panel_factor<S>(F, invd, K, j0, lane);
+            else if (S >= 2 && R - j0 > 64)
+                fail = ls_panel_factor<S >= 2 ? 2 : 1>(F, invd, K, j0, lane);
+            else
+                fail = ls_panel_factor<1>(F, invd, K, j0, lane);
+            if (lane == 0 && fail != 0) bad = fail;
+            __builtin_amdgcn_s_setprio(0);
+        } else if (j0 > 0) {
+            // the panel before this one out of the columns past this one
+            const int cs = j0 + kLsPanel, jp = j0 - kLsPanel;
+            const int m = (R - cs + 1) / 2;   // pairs of rows / columns from cs on
+            for (int e = tid - 64; e < m * (m + 1) / 2 && cs < K; e += T - 64) {
+                int ti = (int)((sqrtf(8.f * (float)e + 1.f) - 1.f) * 0.5f);
+                ti += (ti + 1) * (ti + 2) / 2 <= e ? 1 : 0;
+                ti -= ti * (ti + 1) / 2 > e ? 1 : 0;
+                const int tj = e - ti * (ti + 1) / 2;
+                const int r0 = cs + 2 * ti, r1 = r0 + 1 < R ? r0 + 1 : R - 1;
+                const int c0 = cs + 2 * tj, c1 = c0 + 1 < R ? c0 + 1 : R - 1;
+                double2 s00 = make_double2(0.0, 0.0), s01 = s00, s10 = s00, s11 = s00;
+#pragma unroll
+                for (int q = 0; q < kLsPanel; ++q) {
+                    const double2 *P = F + base(jp + q);
+                    const double2 a0 = P[r0], a1 = P[r1], x0 = P[c0], x1 = P[c1];
+                    ls_sub(s00, a0, x0);
+                    ls_sub(s01, a0, x1);
+                    ls_sub(s10, a1, x0);
+                    ls_sub(s11, a1, x1);
+                }
+                const auto add = [&](int r, int c, double2 s) {
+                    double2 &f = F[base(c) + r];
+                    f = make_double2(f.x + s.x, f.y + s.y);
+                };
+                if (c0 < K) {
+                    add(r0, c0, s00);
+                    if (r0 + 1 < R) add(r0 + 1, c0, s10);
+                }
+                if (c0 + 1 < K) {
+                    if (r0 >= c0 + 1) add(r0, c0 + 1, s01);
+                    if (r0 + 1 < R) add(r0 + 1, c0 + 1, s11);
+                }
+            }
+        }
+        __syncthreads();
+        if (bad != 0) {   // the same in every thread
+            for (int i = tid; i < K; i += T) h[i] = make_float2(NAN, NAN);
+            if (tid == 0) *info = bad;
+            return;
+        }
+        // this panel out of the next one's columns: wave w the column j0 + 8 + w
+        const int c = j0 + kLsPanel + w;
+        if (c < K) {
+            for (int r = c + lane; r < R; r += 64) {
+                double2 s = F[base(c) + r];
+#pragma unroll
+                for (int q = 0; q < kLsPanel; ++q) {
+                    const double2 *P = F + base(j0 + q);
+                    ls_sub(s, P[r], P[c]);
+                }
+                F[base(c) + r] = s;
+            }
+        }
+        __syncthreads();
+    }
+    // L^H h = y in the unknowns y_r / L[r][r], so that the entry of row j is h_j
+    // when its turn comes: all waves scale the columns, then wave 0, lane l
+    // holding rows l, l + 64, ..., sweeps the rows of the factor from the last
+    // (read four steps ahead, a zero from the diagonal on), h_j broadcast from
+    // its owner
+    const int zero = R * (R + 1) / 2 - 1;   // entry (K, K), unused so far
+    for (int k = w; k < K; k += kLsPanelWaves) {
+        const double v = invd[k];
+        for (int r = k + lane; r < R; r += 64) {
+            double2 &f = F[base(k) + r];
+            f = make_double2(f.x * v, f.y * v);
+        }
+    }
+    if (tid == 0) F[zero] = make_double2(0.0, 0.0);
+    __syncthreads();
+    if (w != 0) return;
+    double yx[S], yy[S];
+    int rb[S];
+#pragma unroll
+    for (int t = 0; t < S; ++t) {
+        const int r = lane + 64 * t;
+        rb[t] = base(r < K ? r : K - 1);
+        const double2 v = F[rb[t] + K];
+        yx[t] = v.x;
+        yy[t] = -v.y;
+    }
+    constexpr int D = 4;
+    double2 f[D][S];   // L[j][r] / L[r][r]
+    const auto row = [&](int j, double2(&g)[S]) {
+#pragma unroll
+        for (int t = 0; t < S; ++t) g[t] = F[lane + 64 * t < j ? rb[t] + j : zero];
+    };
+#pragma unroll
+    for (int d = 0; d < D; ++d) row(K - 1 - d, f[d]);
+    for (int j0 = K - 1; j0 >= 0; j0 -= D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            // past the first row (j < 0) the factors are zero
+            const int j = j0 - d;
+            double mx = yx[0], my = yy[0];
+#pragma unroll
+            for (int t = 1; t < S; ++t) {
+                mx = j >= 64 * t ? yx[t] : mx;
+                my = j >= 64 * t ? yy[t] : my;
+            }
+            const double hx = ls_bcast(mx, j & 63), hy = ls_bcast(my, j & 63);
+#pragma unroll
+            for (int t = 0; t < S; ++t) {
+                // y_r -= conj(L[j][r]) h_j
+                yx[t] = fma(-f[d][t].y, hy, fma(-f[d][t].x, hx, yx[t]));
+                yy[t] = fma(f[d][t].y, hx, fma(-f[d][t].x, hy, yy[t]));
+            }
+            row(j - D, f[d]);
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < S; ++t) {
+        const int r = lane + 64 * t;
+        if (r < K) h[r] = make_float2((float)yx[t], (float)yy[t]);
+    }
+    if (lane == 0) *info = 0;
+}
+
+// The same solve for K > kLsPanelMaxK, by one wave with the factor in the
+// caller's workspace.  Lane l owns rows l, l + 64, ... (R slots).  The factor is
+// stored by columns, F[k K + r] = L[r][k], zero above the diagonal, so the lanes read one column at
 // consecutive addresses and the entries of row j are broadcasts.
 // Left-looking: for column j every owned row r >= j forms
 //   s_r = A[r][j] - sum_{k<j} L[r][k] conj(L[j][k]),
@@ -574,14 +855,12 @@ __device__ __forceinline__ void ls_substitute(const double2 *F, int ld, const do
 // value read is finite), so the inner loops have no per-lane branches; only
 // rows a lane owns are stored.  info = 0, or j + 1 when the pivot of column
 // j is not positive (h is then NaN).
-template <bool LDS, int R>
+template <int R>
 __global__ void __launch_bounds__(64) ls_solve_kernel(const double2 *__restrict__ A, const double2 *__restrict__ b,
-                                                      int K, double ridge, double2 *__restrict__ Fg,
+                                                      int K, double ridge, double2 *__restrict__ F,
                                                       float2 *__restrict__ h, int32_t *__restrict__ info)
 {
-    extern __shared__ double2 ls_smem[];
-    double2 *F = LDS ? ls_smem : Fg;
-    const int ld = LDS ? 64 : K;
+    const int ld = K;
     const int lane = threadIdx.x;
     int rc[R];   // owned rows clamped into the matrix (loads only)
 #pragma unroll
@@ -686,95 +965,6 @@ __global__ void __launch_bounds__(64) ls_solve_kernel(const double2 *__restrict_
     }
 
     ls_substitute<R>(F, ld, b, K, h, info, lane);
-}
-
-// The same solve for K <= kLsSolve4MaxK on four waves: F in LDS (column
-// stride 64); the sums of column j are split over the waves (lane = row r,
-// wave w the columns k = w, w + 4, ... < j, two partial sums each) and added
-// up in wave order by every wave after one barrier, so all waves hold the
-// same column; wave j mod 4 stores it, and only that wave reads it later (it
-// owns k = j), so the column needs no second barrier.  The partial sums
-// alternate between two LDS buffers; each lane reads its A entry of column j
-// before the barrier.  Wave 0 runs the substitutions at the end.
-constexpr int kLsSolve4MaxK = 56;   // F and the partial sums within 64 KiB of LDS
-__global__ void __launch_bounds__(256) ls_solve4_kernel(const double2 *__restrict__ A,
-                                                        const double2 *__restrict__ b, int K, double ridge,
-                                                        float2 *__restrict__ h, int32_t *__restrict__ info)
-{
-    extern __shared__ double2 ls_smem[];
-    double2 *F = ls_smem;             // K columns of 64
-    double2 *part = ls_smem + 64 * K; // 2 x 4 x 64 partial sums
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int rc = min(lane, K - 1);
-    // F = strict lower triangle of A, zero elsewhere (the diagonal included)
-    for (int e = tid; e < 64 * K; e += 256) {
-        const int k = e >> 6, r = e & 63;
-        F[e] = (r < K && r > k) ? A[(int64_t)r * K + k] : make_double2(0.0, 0.0);
-    }
-    double tr = 0.0;
-    for (int i = lane; i < K; i += 64) tr += A[(int64_t)i * K + i].x;
-    const double delta = ridge * ls_wave_sum(tr) / K;
-    const double dg = A[(int64_t)rc * K + rc].x + delta;   // Re A[r][r] + delta of the lane's row
-    __syncthreads();
-    for (int j = 0; j < K; ++j) {
-        const double2 aj = F[j * 64 + rc];   // A[r][j] (column j is not written before the barrier)
-        // -sum_{k = w mod 4, k < j} L[r][k] conj(L[j][k])
-        double2 s0 = make_double2(0.0, 0.0), s1 = s0;
-        int k = w;
-        for (; k + 4 < j; k += 8) {
-            const double2 c0 = F[k * 64 + j], a0 = F[k * 64 + rc];
-            const double2 c1 = F[(k + 4) * 64 + j], a1 = F[(k + 4) * 64 + rc];
-            s0.x = fma(-a0.x, c0.x, s0.x);
-            s0.x = fma(-a0.y, c0.y, s0.x);
-            s0.y = fma(-a0.y, c0.x, s0.y);
-            s0.y = fma(a0.x, c0.y, s0.y);
-            s1.x = fma(-a1.x, c1.x, s1.x);
-            s1.x = fma(-a1.y, c1.y, s1.x);
-            s1.y = fma(-a1.y, c1.x, s1.y);
-            s1.y = fma(a1.x, c1.y, s1.y);
-        }
-        if (k < j) {
-            const double2 c0 = F[k * 64 + j], a0 = F[k * 64 + rc];
-            s0.x = fma(-a0.x, c0.x, s0.x);
-            s0.x = fma(-a0.y, c0.y, s0.x);
-            s0.y = fma(-a0.y, c0.x, s0.y);
-            s0.y = fma(a0.x, c0.y, s0.y);
-        }
-        double2 *pj = part + (j & 1) * 256;
-        pj[w * 64 + lane] = make_double2(s0.x + s1.x, s0.y + s1.y);
-        __syncthreads();
-        double2 s = aj;
-        if (lane == j) s.x += dg;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            s.x += pj[q * 64 + lane].x;
-            s.y += pj[q * 64 + lane].y;
-        }
-        const double piv = ls_bcast(s.x, j);
-        if (!(piv > 0.0)) {   // the same in every wave
-            if (w == 0) {
-                for (int i = lane; i < K; i += 64) h[i] = make_float2(NAN, NAN);
-                if (lane == 0) *info = j + 1;
-            }
-            return;
-        }
-        if (w == (j & 3)) {
-            const double d = sqrt(piv), inv = 1.0 / d;
-            if (lane == j)
-                F[j * 64 + lane] = make_double2(d, 0.0);
-            else if (lane > j && lane < K)
-                F[j * 64 + lane] = make_double2(s.x * inv, s.y * inv);
-        }
-        // Column j is read again (by other lanes of the wave that stored it)
-        // before the next barrier: the LDS accesses of one wave execute in
-        // program order, and this keeps the compiler from moving those reads
-        // above the stores.
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    }
-    __syncthreads();   // every column stored
-    if (w == 0) ls_substitute<1>(F, 64, b, K, h, info, lane);
 }
 
 __global__ void __launch_bounds__(kBlock) ls_zero_kernel(double2 *__restrict__ p, int64_t count)
@@ -1035,28 +1225,28 @@ DPD_EXPORT dpd_status dpd_ls_solve(void *stream, int32_t K, const void *A, const
     for (const void *q : {A, b, (const void *)ws})
         if ((uintptr_t)q % 16 != 0) return DPD_EINVAL;
     if ((uintptr_t)h % 8 != 0 || (uintptr_t)info % 4 != 0) return DPD_EINVAL;
-    const bool in_lds = K <= 64;   // F at column stride 64: at most 64 KiB of LDS
-    const size_t lds = (size_t)K * 64 * sizeof(double2);
-    const int slots = (K + 63) / 64;
-    const int R = slots <= 1 ? 1 : slots <= 2 ? 2 : slots <= 4 ? 4 : slots <= 8 ? 8 : 16;
+    const int slots = (K + 63) / 64;   // rows per lane of the one-wave form
     const hipStream_t st = (hipStream_t)stream;
     const double2 *Ad = (const double2 *)A, *bd = (const double2 *)b;
     double2 *F = (double2 *)ws;
     float2 *hd = (float2 *)h;
     int32_t *id = (int32_t *)info;
-    if (K <= kLsSolve4MaxK)
-        hipLaunchKernelGGL(ls_solve4_kernel, dim3(1), dim3(256), (size_t)(64 * K + 2 * 4 * 64) * sizeof(double2), st,
-                           Ad, bd, K, ridge, hd, id);
-    else if (in_lds)
-        hipLaunchKernelGGL((ls_solve_kernel<true, 1>), dim3(1), dim3(64), lds, st, Ad, bd, K, ridge, F, hd, id);
-    else if (R == 2)
-        hipLaunchKernelGGL((ls_solve_kernel<false, 2>), dim3(1), dim3(64), 0, st, Ad, bd, K, ridge, F, hd, id);
-    else if (R == 4)
-        hipLaunchKernelGGL((ls_solve_kernel<false, 4>), dim3(1), dim3(64), 0, st, Ad, bd, K, ridge, F, hd, id);
-    else if (R == 8)
-        hipLaunchKernelGGL((ls_solve_kernel<false, 8>), dim3(1), dim3(64), 0, st, Ad, bd, K, ridge, F, hd, id);
+    if (K <= kLsPanelMaxK) {
+        // the triangle fits one CU's LDS; 64-row slots of a panel: K + 1 rows
+        const dim3 blk(64 * kLsPanelWaves);
+        const size_t lds = ls_panel_lds(K);
+        if (K < 64)
+            hipLaunchKernelGGL((ls_solve_panel_kernel<1>), dim3(1), blk, lds, st, Ad, bd, K, ridge, hd, id);
+        else if (K < 128)
+            hipLaunchKernelGGL((ls_solve_panel_kernel<2>), dim3(1), blk, lds, st, Ad, bd, K, ridge, hd, id);
+        else
+            hipLaunchKernelGGL((ls_solve_panel_kernel<3>), dim3(1), blk, lds, st, Ad, bd, K, ridge, hd, id);
+    } else if (slots <= 4)
+        hipLaunchKernelGGL((ls_solve_kernel<4>), dim3(1), dim3(64), 0, st, Ad, bd, K, ridge, F, hd, id);
+    else if (slots <= 8)
+        hipLaunchKernelGGL((ls_solve_kernel<8>), dim3(1), dim3(64), 0, st, Ad, bd, K, ridge, F, hd, id);
     else
-        hipLaunchKernelGGL((ls_solve_kernel<false, 16>), dim3(1), dim3(64), 0, st, Ad, bd, K, ridge, F, hd, id);
+        hipLaunchKernelGGL((ls_solve_kernel<16>), dim3(1), dim3(64), 0, st, Ad, bd, K, ridge, F, hd, id);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? DPD_OK : hip_fail(e);
 }

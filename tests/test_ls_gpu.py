@@ -222,6 +222,33 @@ def test_solve_reports_indefinite(torch, dpd):
     assert torch.isnan(h3.real).all()
 
 
+@pytest.mark.parametrize("K", [7, 8, 9, 62, 95, 96, 127, 128, 139, 140])
+def test_solve_panel_edges(torch, dpd, K):
+    """The panel solve at whole and partial panels of eight columns, at its 64-row
+    slots' limits (K + 1 rows) and on both sides of its largest K, and the
+    column of a pivot that is not positive or not a number (a NaN on the
+    diagonal reaches the first pivot through the mean diagonal)."""
+    rng = np.random.default_rng(1000 + K)
+    X = rng.standard_normal((2 * K + 8, K)) + 1j * rng.standard_normal((2 * K + 8, K))
+    A = X.conj().T @ X
+    A = (A + A.conj().T) / 2
+    b = rng.standard_normal(K) + 1j * rng.standard_normal(K)
+    At, bt = torch.from_numpy(A).cuda(), torch.from_numpy(b).cuda()
+    low = At.masked_fill(torch.ones_like(At.real).triu(1).bool(), float("nan"))   # only the lower triangle is read
+    h, info = dpd.ls_solve(low, bt, 1e-3)
+    assert int(info.item()) == 0
+    ref = np.linalg.solve(A + 1e-3 * np.mean(np.real(np.diag(A))) * np.eye(K), b)
+    rel = np.linalg.norm(h.cpu().numpy() - ref) / np.linalg.norm(ref)
+    assert rel <= 1e-6, rel
+    for j in {0, K // 2, K - 1}:
+        for v in (-1.0, float("nan")):
+            B = At.clone()
+            B[j, j] = v
+            h, info = dpd.ls_solve(B, bt)
+            assert int(info.item()) == (j + 1 if v == v else 1)
+            assert bool(torch.isnan(h.real).all())
+
+
 def test_recovers_generating_coefficients(torch, dpd, orc):
     """t = D_h(y) exactly (FP64 oracle): GPU normal equations + GPU solve give
     coefficients whose model reproduces t to far below the FP32 noise floor of
