@@ -17,7 +17,9 @@
  * Conventions shared by every entry point
  *   - Samples are interleaved complex64 (float re, float im; 8 bytes), in
  *     device memory owned by the caller.  Pointers must be 8-byte aligned;
- *     16-byte alignment (and an even row stride) selects the vector fast path.
+ *     the forward calls take any such address and row stride at full speed,
+ *     elsewhere 16-byte alignment (and an even row stride) selects the vector
+ *     fast path.
  *   - Coefficients use the stacking of section 2.2: for each main-branch order
  *     (in the order passed to dpd_create) its L taps, then for each
  *     conjugate-branch order its L taps, then c.  K = (n_main + n_conj)*L + 1
@@ -56,11 +58,12 @@ typedef enum dpd_status {
 typedef struct dpd_plan dpd_plan;
 typedef struct dpd_batch dpd_batch;
 
-/* Launch shape of the forward kernels; chosen by the autotuner or defaulted.
+/* Launch shape of the forward kernels; chosen by the autotuner or by size.
  *   samples_per_thread: consecutive outputs per thread (2, 4 or 8)
- *   stage_lds: 1 = the tile and its (L-1)-sample halo are staged through LDS
- *              with coalesced 16-byte loads, 0 = each thread loads its own
- *              window (halo re-reads hit the cache)
+ *   stage_lds: 1 = streaming: persistent waves, the chunk and its (L-1)-sample
+ *              halo staged through LDS with coalesced 16-byte loads, 0 =
+ *              one-shot: each thread loads its own window (halo re-reads hit
+ *              the cache)
  *   block: threads per block (must be 256; other values are rejected)
  *   grid_mult: persistent batched kernel only -- resident blocks per CU */
 typedef struct dpd_tune {
@@ -124,8 +127,12 @@ dpd_status dpd_set_coeffs_device(dpd_plan *plan, const void *coeffs_dev, void *s
 dpd_status dpd_set_coeffs_device_if(dpd_plan *plan, const void *coeffs_dev, const int32_t *flag_dev,
                                     void *stream);
 
-/* dpd_set_tune / dpd_get_tune -- launch shape of this plan's forward kernels.
- * Fields outside the supported set are DPD_EINVAL. */
+/* dpd_set_tune / dpd_get_tune -- launch shape of this plan's forward kernels,
+ * used from then on at every size (until then each call takes the shape
+ * measured best for its size; dpd_get_tune then reports the shape of long
+ * streams).  Filters of more than eight taps have one-shot kernels of 2 and 4
+ * samples per thread and a streaming kernel of 8: other values take the
+ * nearest.  Fields outside the supported set are DPD_EINVAL. */
 dpd_status dpd_set_tune(dpd_plan *plan, const dpd_tune *tune);
 dpd_status dpd_get_tune(const dpd_plan *plan, dpd_tune *tune);
 

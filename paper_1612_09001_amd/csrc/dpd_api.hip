@@ -127,60 +127,6 @@ hipError_t launch_prep(const CoefMap &map, const void *raw, float *M, hipStream_
     return hipGetLastError();
 }
 
-// ------------------------------------------------------ generic forward ---
-// Any L <= 16, any NI <= 8, 8-byte alignment: one output per thread, runtime
-// loops over taps and power levels (the specialised kernels cover the common
-// shapes; this one keeps every valid plan usable).
-__global__ void __launch_bounds__(kBlock) fwd_generic_kernel(FwdParams p, int NI, int L)
-{
-    const cfloat *M = as_const(p.M);
-    const int64_t total = p.total_tiles;   // rows * n for this kernel
-    for (int64_t idx = (int64_t)blockIdx.x * kBlock + threadIdx.x; idx < total;
-         idx += (int64_t)gridDim.x * kBlock) {
-        const int64_t row = idx / p.n;
-        const int64_t m = idx - row * p.n;
-        const float2 *x = p.in + row * p.ld;
-        const float2 *hist = row == 0 ? p.hist : nullptr;
-        float zr = M[4 * L * NI], zi = M[4 * L * NI + 1];
-        for (int k = 0; k < L; ++k) {
-            const int64_t t = m - k;
-            float2 v = make_float2(0.f, 0.f);
-            if (t >= 0)
-                v = x[t];
-            else if (hist != nullptr && t >= -(int64_t)(L - 1))
-                v = hist[(L - 1) + t];
-            const float s = __builtin_fmaf(v.x, v.x, v.y * v.y);
-            const cfloat *Mk = M + 4 * NI * k;
-            float w00 = Mk[4 * (NI - 1) + 0], w01 = Mk[4 * (NI - 1) + 1];
-            float w10 = Mk[4 * (NI - 1) + 2], w11 = Mk[4 * (NI - 1) + 3];
-            for (int j = NI - 2; j >= 0; --j) {
-                w00 = __builtin_fmaf(w00, s, Mk[4 * j + 0]);
-                w01 = __builtin_fmaf(w01, s, Mk[4 * j + 1]);
-                w10 = __builtin_fmaf(w10, s, Mk[4 * j + 2]);
-                w11 = __builtin_fmaf(w11, s, Mk[4 * j + 3]);
-            }
-            zr = __builtin_fmaf(w00, v.x, zr);
-            zr = __builtin_fmaf(w01, v.y, zr);
-            zi = __builtin_fmaf(w10, v.x, zi);
-            zi = __builtin_fmaf(w11, v.y, zi);
-        }
-        p.out[row * p.ld + m] = make_float2(zr, zi);
-    }
-}
-
-// After a streaming call: hist <- last L-1 samples of (hist ++ in).
-__global__ void hist_update_kernel(const float2 *__restrict__ in, int64_t n, float2 *hist, int Lm1)
-{
-    const int i = threadIdx.x;
-    float2 v = make_float2(0.f, 0.f);
-    if (i < Lm1) {
-        const int64_t src = n - Lm1 + i;
-        v = src >= 0 ? in[src] : hist[Lm1 + src];
-    }
-    __syncthreads();
-    if (i < Lm1) hist[i] = v;
-}
-
 // ------------------------------------------------------- streaming copy ---
 // The forward kernel's memory walk without the filter (measurement of the
 // practical HBM ceiling of that walk): persistent waves, wave g copies chunks
@@ -261,10 +207,15 @@ const FwdTable &fwd_table()
         register_fwd_ni6(g_fwd);
         register_fwd_ni7(g_fwd);
         register_fwd_ni8(g_fwd);
-        for (int v = 0; v < kNumFwdVariants; ++v)
-            g_fwd.tile[v] = (v & 1 ? 64 : kBlock) * (2 << (v / 2));
     });
     return g_fwd;
+}
+
+// Samples per tile (one-shot) or per wave chunk (streaming) of variant v.
+static int64_t fwd_tile(int L, int v)
+{
+    if (L > kSpecL) return v & 1 ? 64 * 8 : kBlock * (v == 0 ? 2 : 4);   // register_fwd_one
+    return (int64_t)(v & 1 ? 64 : kBlock) * (2 << (v / 2));
 }
 
 int fwd_variant(const dpd_tune &t)
@@ -302,35 +253,51 @@ static size_t span_bytes(int64_t rows, int64_t n, int64_t ld)
     return (size_t)(((rows - 1) * ld + n) * (int64_t)sizeof(float2));
 }
 
-// Forward launch for an already-prepared device table M.
-dpd_status run_forward(const CoefMap &map, const dpd_tune &tune, const float *M, hipStream_t stream,
-                       const void *in, void *out, int64_t rows, int64_t n, int64_t ld,
-                       const void *hist)
+// Launch shape of a forward call on N samples whose plan was not tuned.  Below
+// 2^20 samples a call is a chain of latencies and the chip is not full: one-shot
+// tiles of two samples per thread (2^16 samples, NI = L = 4: 3.1 us against 4.4
+// for the streaming form, 3.3 at S = 4).  Up to 10 * 2^20 the in- and outputs
+// stay in the last-level cache and one-shot tiles of four samples, many short
+// blocks that hide each other's waits, beat the streaming form (2^23: 23.6
+// against 26.3 us; NI L <= 9 is light enough for S = 2: 21.2 against 24.4 at
+// NI = L = 2).  Beyond, memory bounds and the streaming form's ordered sweep
+// wins (2^24: 48 us against 58), with a third block per CU where the filter is
+// heavy (NI L >= 24: 77 against 81.5 us at NI = 5, L = 8; lighter ones lose:
+// 52 against 48 at NI = L = 4).
+static dpd_tune fwd_auto(const CoefMap &map, int64_t N)
 {
+    dpd_tune t = default_tune();
+    const int cost = map.NI * map.L;
+    if (N <= (int64_t)10 << 20) {
+        t.stage_lds = 0;
+        t.samples_per_thread = N < (int64_t)1 << 20 || cost <= 9 ? 2 : 4;
+    } else {
+        t.grid_mult = cost >= 24 ? 3 : 2;
+    }
+    return t;
+}
+
+// Forward launch for an already-prepared device table M, with the caller's
+// launch shape or (tune null) fwd_auto's; a history is replaced by the last
+// L - 1 inputs.
+dpd_status run_forward(const CoefMap &map, const dpd_tune *tune_in, const float *M, hipStream_t stream,
+                       const void *in, void *out, int64_t rows, int64_t n, int64_t ld,
+                       void *hist)
+{
+    const dpd_tune tune = tune_in != nullptr ? *tune_in : fwd_auto(map, rows * n);
     FwdParams p;
     p.in = (const float2 *)in;
     p.out = (float2 *)out;
     p.n = n;
     p.ld = ld;
     p.M = M;
-    p.hist = (const float2 *)hist;
-    const bool aligned = ((uintptr_t)in % 16 == 0) && ((uintptr_t)out % 16 == 0) &&
-                         (rows == 1 || ld % 2 == 0);
-    if (aligned && map.NI <= kSpecNI && map.L <= kSpecL) {
-        const FwdTable &t = fwd_table();
-        const int v = fwd_variant(tune);
-        const int64_t T = t.tile[v];
-        p.tiles_per_row = (n + T - 1) / T;
-        p.total_tiles = p.tiles_per_row * rows;
-        hipError_t e = t.fn[map.NI - 1][map.L - 1][v](p, stream, tune.grid_mult);
-        return e == hipSuccess ? DPD_OK : hip_fail(e);
-    }
-    p.tiles_per_row = 0;
-    p.total_tiles = rows * n;
-    const int64_t blocks = std::min<int64_t>((p.total_tiles + kBlock - 1) / kBlock, 1 << 20);
-    hipLaunchKernelGGL(fwd_generic_kernel, dim3((uint32_t)blocks), dim3(kBlock), 0, stream, p,
-                       map.NI, map.L);
-    hipError_t e = hipGetLastError();
+    p.hist = (float2 *)hist;
+    const FwdTable &t = fwd_table();
+    const int v = fwd_variant(tune);
+    const int64_t T = fwd_tile(map.L, v);
+    p.tiles_per_row = (n + T - 1) / T;
+    p.total_tiles = p.tiles_per_row * rows;
+    const hipError_t e = t.fn[map.NI - 1][map.L - 1][v](p, stream, tune.grid_mult);
     return e == hipSuccess ? DPD_OK : hip_fail(e);
 }
 
@@ -475,6 +442,7 @@ DPD_EXPORT dpd_status dpd_set_tune(dpd_plan *plan, const dpd_tune *tune)
 {
     if (plan == nullptr || tune == nullptr || !valid_tune(*tune)) return DPD_EINVAL;
     plan->tune = *tune;
+    plan->tuned = true;
     return DPD_OK;
 }
 
@@ -492,7 +460,7 @@ DPD_EXPORT dpd_status dpd_apply_rows(dpd_plan *plan, void *stream, const void *i
     if (rows == 1 && ld < n) ld = n;
     dpd_status st = check_io(in, out, rows, n, ld);
     if (st != DPD_OK || n == 0 || rows == 0) return st;
-    return run_forward(plan->map, plan->tune, plan->d_table, (hipStream_t)stream, in, out, rows, n,
+    return run_forward(plan->map, plan->tuned ? &plan->tune : nullptr, plan->d_table, (hipStream_t)stream, in, out, rows, n,
                        ld, nullptr);
 }
 
@@ -511,7 +479,7 @@ DPD_EXPORT dpd_status dpd_apply_coeffs(dpd_plan *plan, void *stream, const void 
     hipError_t e = launch_prep(plan->map, coeffs_dev, plan->d_table_call, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e);
     if (n == 0 || rows == 0) return DPD_OK;
-    return run_forward(plan->map, plan->tune, plan->d_table_call, (hipStream_t)stream, in, out, rows, n,
+    return run_forward(plan->map, plan->tuned ? &plan->tune : nullptr, plan->d_table_call, (hipStream_t)stream, in, out, rows, n,
                        ld, nullptr);
 }
 
@@ -525,13 +493,8 @@ DPD_EXPORT dpd_status dpd_apply_hist(dpd_plan *plan, void *stream, const void *i
     if (st != DPD_OK || n == 0) return st;
     const size_t hb = (size_t)Lm1 * sizeof(float2);
     if (overlap(hist, hb, in, (size_t)n * 8) || overlap(hist, hb, out, (size_t)n * 8)) return DPD_EINVAL;
-    st = run_forward(plan->map, plan->tune, plan->d_table, (hipStream_t)stream, in, out, 1, n, n,
-                     Lm1 > 0 ? hist : nullptr);
-    if (st != DPD_OK || Lm1 == 0) return st;
-    hipLaunchKernelGGL(hist_update_kernel, dim3(1), dim3(64), 0, (hipStream_t)stream,
-                       (const float2 *)in, n, (float2 *)hist, Lm1);
-    hipError_t e = hipGetLastError();
-    return e == hipSuccess ? DPD_OK : hip_fail(e);
+    return run_forward(plan->map, plan->tuned ? &plan->tune : nullptr, plan->d_table, (hipStream_t)stream, in, out, 1, n, n,
+                       Lm1 > 0 ? hist : nullptr);
 }
 
 DPD_EXPORT dpd_status dpd_copy(void *stream, const void *in, void *out, int64_t n)

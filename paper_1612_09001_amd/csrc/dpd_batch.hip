@@ -120,7 +120,7 @@ static dpd_status run_stream(dpd_batch *b, int s, hipStream_t st)
 {
     const dpd_stream_desc &d = b->desc[s];
     if (d.n == 0) return DPD_OK;
-    return run_forward(b->maps[s], default_tune(), b->d_tables + b->tab[s], st, d.in, d.out, 1, d.n, d.n,
+    return run_forward(b->maps[s], nullptr, b->d_tables + b->tab[s], st, d.in, d.out, 1, d.n, d.n,
                        nullptr);
 }
 

@@ -150,67 +150,6 @@ __device__ __forceinline__ void batch_load(BatchRegs<S> &R, const BatchDesc &D, 
     R.m = make_float4(m.x, m.y, m.z, m.w);
 }
 
-// fir_outputs with the table in LDS (CS): each tap's 4*NI floats are read as
-// broadcast 16-byte LDS loads one tap ahead of their use.  Scheduling
-// barriers between taps keep the compiler from hoisting every tap's reads to
-// the top (which would hold the whole table in registers).
-template <int NI>
-__device__ __forceinline__ void batch_tap_load(const float *CS, int k, float (&Mk)[4 * NI])
-{
-    const float4 *ck = reinterpret_cast<const float4 *>(CS + 4 * NI * k);
-#pragma unroll
-    for (int j = 0; j < NI; ++j) {
-        const float4 u = ck[j];
-        Mk[4 * j + 0] = u.x;
-        Mk[4 * j + 1] = u.y;
-        Mk[4 * j + 2] = u.z;
-        Mk[4 * j + 3] = u.w;
-    }
-}
-
-template <int NI, int L, int S>
-__device__ __forceinline__ void fir_outputs_lds(const float (&a)[S + L - 1], const float (&b)[S + L - 1],
-                                                const float (&s)[S + L - 1], const float *CS,
-                                                float (&zr)[S], float (&zi)[S])
-{
-    const float2 c = *reinterpret_cast<const float2 *>(CS + 4 * L * NI);
-#pragma unroll
-    for (int i = 0; i < S; ++i) {
-        zr[i] = c.x;
-        zi[i] = c.y;
-    }
-    float Mk[4 * NI];
-    batch_tap_load<NI>(CS, 0, Mk);
-#pragma unroll
-    for (int k = 0; k < L; ++k) {
-        float Mn[4 * NI];
-        if (k + 1 < L) batch_tap_load<NI>(CS, k + 1, Mn);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < S; ++i) {
-            const int w = i + (L - 1) - k;
-            float w00 = Mk[4 * (NI - 1) + 0], w01 = Mk[4 * (NI - 1) + 1];
-            float w10 = Mk[4 * (NI - 1) + 2], w11 = Mk[4 * (NI - 1) + 3];
-#pragma unroll
-            for (int j = NI - 2; j >= 0; --j) {
-                w00 = __builtin_fmaf(w00, s[w], Mk[4 * j + 0]);
-                w01 = __builtin_fmaf(w01, s[w], Mk[4 * j + 1]);
-                w10 = __builtin_fmaf(w10, s[w], Mk[4 * j + 2]);
-                w11 = __builtin_fmaf(w11, s[w], Mk[4 * j + 3]);
-            }
-            zr[i] = __builtin_fmaf(w00, a[w], zr[i]);
-            zr[i] = __builtin_fmaf(w01, b[w], zr[i]);
-            zi[i] = __builtin_fmaf(w10, a[w], zi[i]);
-            zi[i] = __builtin_fmaf(w11, b[w], zi[i]);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        if (k + 1 < L) {
-#pragma unroll
-            for (int e = 0; e < 4 * NI; ++e) Mk[e] = Mn[e];
-        }
-    }
-}
-
 // LDS layout shared by all classes: the padded layout of the longest filter,
 // so a chunk is staged the same way whatever its class.
 template <int S>

@@ -1,6 +1,6 @@
 // Instantiates the specialised forward kernels for one power level count
 // NI = DPD_NI (set on the compiler command line; one object per NI so the
-// instantiations build in parallel) and every L in 1..kSpecL.
+// instantiations build in parallel) and every L in 1..kMaxL.
 #include "dpd_fwd_kernels.h"
 
 #ifndef DPD_NI
@@ -22,6 +22,14 @@ void DPD_CAT(register_fwd_ni, DPD_NI)(FwdTable &t)
     register_fwd_one<DPD_NI, 6>(t);
     register_fwd_one<DPD_NI, 7>(t);
     register_fwd_one<DPD_NI, 8>(t);
+    register_fwd_one<DPD_NI, 9>(t);
+    register_fwd_one<DPD_NI, 10>(t);
+    register_fwd_one<DPD_NI, 11>(t);
+    register_fwd_one<DPD_NI, 12>(t);
+    register_fwd_one<DPD_NI, 13>(t);
+    register_fwd_one<DPD_NI, 14>(t);
+    register_fwd_one<DPD_NI, 15>(t);
+    register_fwd_one<DPD_NI, 16>(t);
 }
 
 }  // namespace dpd

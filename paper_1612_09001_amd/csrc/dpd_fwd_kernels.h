@@ -23,6 +23,11 @@
 namespace dpd {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
+// Two samples at a time from any sample's address: the hardware's 16-byte
+// global loads and stores need 4-byte alignment only, so rows that start at an
+// odd sample run the same instructions (a 1 KiB access then touches nine cache
+// lines instead of eight).
+typedef float v4f_s __attribute__((ext_vector_type(4), aligned(8)));
 
 // Coefficient tables are read through the constant address space: uniform,
 // read-only loads from it become scalar loads (SGPR operands of the FMAs).
@@ -154,8 +159,77 @@ __device__ __forceinline__ void fir_outputs_reg(const float (&a)[S + L - 1], con
     }
 }
 
+// fir_outputs with the table in LDS (CS): each tap's 4*NI floats are read as
+// broadcast 16-byte LDS loads one tap ahead of their use.  Scheduling
+// barriers between taps keep the compiler from hoisting every tap's reads to
+// the top (which would hold the whole table in registers).
+template <int NI>
+__device__ __forceinline__ void lds_tap_load(const float *CS, int k, float (&Mk)[4 * NI])
+{
+    const float4 *ck = reinterpret_cast<const float4 *>(CS + 4 * NI * k);
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+        const float4 u = ck[j];
+        Mk[4 * j + 0] = u.x;
+        Mk[4 * j + 1] = u.y;
+        Mk[4 * j + 2] = u.z;
+        Mk[4 * j + 3] = u.w;
+    }
+}
+
+template <int NI, int L, int S>
+__device__ __forceinline__ void fir_outputs_lds(const float (&a)[S + L - 1], const float (&b)[S + L - 1],
+                                                const float (&s)[S + L - 1], const float *CS,
+                                                float (&zr)[S], float (&zi)[S])
+{
+    const float2 c = *reinterpret_cast<const float2 *>(CS + 4 * L * NI);
+#pragma unroll
+    for (int i = 0; i < S; ++i) {
+        zr[i] = c.x;
+        zi[i] = c.y;
+    }
+    float Mk[4 * NI];
+    lds_tap_load<NI>(CS, 0, Mk);
+    int zo = 0;   // opaque zero of the next tap's address
+#pragma unroll
+    for (int k = 0; k < L; ++k) {
+        float Mn[4 * NI];
+        if (k + 1 < L) lds_tap_load<NI>(CS + zo, k + 1, Mn);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < S; ++i) {
+            const int w = i + (L - 1) - k;
+            float w00 = Mk[4 * (NI - 1) + 0], w01 = Mk[4 * (NI - 1) + 1];
+            float w10 = Mk[4 * (NI - 1) + 2], w11 = Mk[4 * (NI - 1) + 3];
+#pragma unroll
+            for (int j = NI - 2; j >= 0; --j) {
+                w00 = __builtin_fmaf(w00, s[w], Mk[4 * j + 0]);
+                w01 = __builtin_fmaf(w01, s[w], Mk[4 * j + 1]);
+                w10 = __builtin_fmaf(w10, s[w], Mk[4 * j + 2]);
+                w11 = __builtin_fmaf(w11, s[w], Mk[4 * j + 3]);
+            }
+            zr[i] = __builtin_fmaf(w00, a[w], zr[i]);
+            zr[i] = __builtin_fmaf(w01, b[w], zr[i]);
+            zi[i] = __builtin_fmaf(w10, a[w], zi[i]);
+            zi[i] = __builtin_fmaf(w11, b[w], zi[i]);
+        }
+        if (k + 2 < L) {
+            // the reads of tap k + 2 wait for this tap's results: the selector
+            // would move every tap's reads to the top, where the whole table
+            // takes registers
+#pragma unroll
+            for (int i = 0; i < S; ++i) asm volatile("" : "+v"(zo) : "v"(zr[i]), "v"(zi[i]));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (k + 1 < L) {
+#pragma unroll
+            for (int e = 0; e < 4 * NI; ++e) Mk[e] = Mn[e];
+        }
+    }
+}
+
 // Coefficient tables up to this many floats stay in registers in the
-// streaming kernel (larger ones are read as scalar operands).
+// streaming kernel (larger ones are read from LDS, tap by tap).
 constexpr int kRegCoefMax = 96;
 
 template <int W>
@@ -176,10 +250,10 @@ __device__ __forceinline__ void store_outputs(float2 *__restrict__ z, int64_t m0
                                               bool full, const float (&zr)[S], const float (&zi)[S])
 {
     if (full) {
-        v4f *z4 = reinterpret_cast<v4f *>(z + m0);
+        v4f_s *z4 = reinterpret_cast<v4f_s *>(z + m0);
 #pragma unroll
         for (int i = 0; i < S / 2; ++i) {
-            v4f v = {zr[2 * i], zi[2 * i], zr[2 * i + 1], zi[2 * i + 1]};
+            v4f_s v = {zr[2 * i], zi[2 * i], zr[2 * i + 1], zi[2 * i + 1]};
             __builtin_nontemporal_store(v, z4 + i);
         }
     } else {
@@ -192,6 +266,12 @@ __device__ __forceinline__ void store_outputs(float2 *__restrict__ z, int64_t m0
 // One-shot kernel (stage_lds = 0): each block computes one tile of kBlock*S
 // outputs; every thread loads its own S+L-1 window with 16-byte loads (the
 // halo part re-reads its neighbour's samples, which the vector L1 / L2 serve).
+// The top Horner level sits in VGPRs (an FMA takes one scalar operand), the
+// lower ones are scalar loads.  S = 2, the form of short calls, whose time is
+// the chain of memory latencies: straight from scalar loads beside the
+// window's, no barrier (3.06 us for 2^16 samples at NI = L = 4 against 3.13).
+// Larger S: through LDS, whose barrier starts the block's loads together
+// (2^23 samples: 23.6 us against 25.4).
 template <int NI, int L, int S>
 __global__ void __launch_bounds__(kBlock) fwd_tile_kernel(FwdParams p)
 {
@@ -200,37 +280,49 @@ __global__ void __launch_bounds__(kBlock) fwd_tile_kernel(FwdParams p)
     constexpr int HP = (L - 1 + 1) & ~1;   // halo rounded up to an even count
     constexpr int W = S + L - 1;
     constexpr int WL = HP + S;              // loaded samples (even)
-    __shared__ float ctop[4 * L];
-
+    constexpr bool DIRECT = S == 2;
+    __shared__ float ctop[DIRECT ? 1 : 4 * L];
     const int tid = threadIdx.x;
-    if (tid < 4 * L) ctop[tid] = p.M[(tid >> 2) * 4 * NI + 4 * (NI - 1) + (tid & 3)];
-    __syncthreads();
     float top[4 * L];
+    if constexpr (!DIRECT) {
+        if (tid < 4 * L) ctop[tid] = p.M[(tid >> 2) * 4 * NI + 4 * (NI - 1) + (tid & 3)];
+        __syncthreads();
 #pragma unroll
-    for (int e = 0; e < 4 * L; ++e) top[e] = ctop[e];
+        for (int e = 0; e < 4 * L; ++e) top[e] = ctop[e];
+    }
 
     for (int64_t step = xcd_remap(blockIdx.x, gridDim.x); step < p.total_tiles; step += gridDim.x) {
-        const int64_t row = step / p.tiles_per_row;
+        // a 64-bit division is a hundred instructions before the first load
+        const int64_t row = p.total_tiles >> 31 ? step / p.tiles_per_row
+                                                : (int64_t)((uint32_t)step / (uint32_t)p.tiles_per_row);
         const int64_t t0 = (step - row * p.tiles_per_row) * (int64_t)T;
         const float2 *__restrict__ x = p.in + row * p.ld;
         float2 *__restrict__ z = p.out + row * p.ld;
-        const float2 *__restrict__ hist = row == 0 ? p.hist : nullptr;
+        const float2 *hist = row == 0 ? p.hist : nullptr;
         const bool full = t0 + T <= p.n;
         const int64_t m0 = t0 + (int64_t)tid * S;   // first output of this thread
 
         float2 raw[WL];
         const int64_t lo = m0 - HP;
         if (full && lo >= 0) {
-            const float4 *x4 = reinterpret_cast<const float4 *>(x + lo);
+            const v4f_s *x4 = reinterpret_cast<const v4f_s *>(x + lo);
 #pragma unroll
             for (int i = 0; i < WL / 2; ++i) {
-                float4 v = x4[i];
+                const v4f_s v = x4[i];
                 raw[2 * i] = make_float2(v.x, v.y);
                 raw[2 * i + 1] = make_float2(v.z, v.w);
             }
         } else {
 #pragma unroll
             for (int i = 0; i < WL; ++i) raw[i] = sample_or_hist<L>(x, lo + i, p.n, hist);
+        }
+        const cfloat *M = as_const(p.M);
+        if constexpr (DIRECT) {
+#pragma unroll
+            for (int e = 0; e < 4 * L; ++e) {
+                top[e] = M[(e >> 2) * 4 * NI + 4 * (NI - 1) + (e & 3)];
+                asm("" : "+v"(top[e]));
+            }
         }
         float2 win[W];
 #pragma unroll
@@ -240,6 +332,18 @@ __global__ void __launch_bounds__(kBlock) fwd_tile_kernel(FwdParams p)
         float zr[S], zi[S];
         fir_outputs<NI, L, S>(a, b, s, top, as_const(p.M), zr, zi);
         if (m0 < p.n) store_outputs<S>(z, m0, p.n, full, zr, zi);
+        if (L > 1 && p.hist != nullptr && step == 0) {
+            // a carried history is read by this block alone; replace it once
+            // every thread has
+            __syncthreads();
+            if (tid < L - 1) {
+                const int64_t m = p.n - (L - 1) + tid;
+                const float2 v = m >= 0 ? p.in[m] : p.hist[L - 1 + m];
+                raw[0] = v;
+            }
+            __syncthreads();
+            if (tid < L - 1) p.hist[tid] = raw[0];
+        }
     }
 }
 
@@ -268,9 +372,15 @@ __device__ __forceinline__ void wave_lds_order()
 //     each lane reads its S+L-1 consecutive-sample window back, filters and
 //     stores 16-byte outputs.
 // The loop body has no divergent global accesses and no conditional loads, so
-// the compiler's counter waits stay exact.  The partial last chunk of each row
-// (when C does not divide n) is handled after the loop with guarded accesses.
-// No block-wide barrier after the coefficient staging.
+// the compiler's counter waits stay exact.  When C does not divide n, the last
+// chunk of a row is the row's last C samples: the samples it shares with the
+// chunk before come out the same there (each output is computed by itself, in
+// one order), and the two waves store the same bits.  Only rows shorter than
+// C + L - 1 samples take the guarded code after the loop for their end (a last
+// chunk starting inside the first L - 1 samples would need part of the
+// history).  No block-wide barrier after the coefficient staging.
+// A carried history (dpd_apply_hist) is read only by the wave of row 0's first
+// chunk, wave 0, which replaces it by the last L - 1 inputs once it has read it.
 template <int S>
 struct ChunkRegs {
     float4 v[S / 2];
@@ -301,40 +411,42 @@ __global__ void __launch_bounds__(kBlock) fwd_stream_kernel(FwdParams p)
     constexpr int HS = L - 1;                        // halo samples
     constexpr int NC = 4 * L * NI + 2;               // coefficient table floats
     constexpr bool REG = NC <= kRegCoefMax;          // whole table in registers
-    __shared__ float ctab[REG ? NC : 4 * L];
+    __shared__ __align__(16) float ctab[NC];
     __shared__ __align__(16) float2 xs[WAVES][PL::SLOTS];
     __shared__ __align__(16) float ss[WAVES][PL::SLOTS];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform per wave
-    if constexpr (REG) {
-        if (tid < NC) ctab[tid] = p.M[tid];
-    } else {
-        if (tid < 4 * L) ctab[tid] = p.M[(tid >> 2) * 4 * NI + 4 * (NI - 1) + (tid & 3)];
-    }
+    for (int e = tid; e < NC; e += kBlock) ctab[e] = p.M[e];
     __syncthreads();
-    float top[4 * L];
     float coef[REG ? NC : 1];
     if constexpr (REG) {
 #pragma unroll
         for (int e = 0; e < NC; ++e) coef[e] = ctab[e];
-    } else {
-#pragma unroll
-        for (int e = 0; e < 4 * L; ++e) top[e] = ctab[e];
     }
-    const cfloat *M = as_const(p.M);
 
     float2 *X = xs[wv];
     float *SX = ss[wv];
     const int64_t rows = p.total_tiles / p.tiles_per_row;
-    const int64_t tpr = p.n / C;                 // full chunks per row
+    // chunks per row of the main loop, the last one moved back to the row's end
+    const bool whole = p.n % C == 0 || p.n >= C + HS;
+    const int64_t tpr = whole ? (p.n + C - 1) / C : p.n / C;
+    const int64_t t_end = p.n - C;
+    const auto start = [&](int64_t k) { return k * C < t_end ? k * C : t_end; };
     const int64_t total = rows * tpr;
     const int64_t nw = (int64_t)gridDim.x * WAVES;
     const int64_t gw = (int64_t)xcd_remap(blockIdx.x, gridDim.x) * WAVES + wv;
     // halo sample this lane fetches: d = hl - HS in [-(L-1), -1]
     const int hl = HS > 0 ? (lane < HS ? lane : HS - 1) : 0;
     float2 hist_v = make_float2(0.f, 0.f);
-    if (HS > 0 && p.hist != nullptr) hist_v = p.hist[hl];
+    if (HS > 0 && p.hist != nullptr && gw == 0) {
+        hist_v = p.hist[hl];
+        if (lane < HS) {
+            const int64_t m = p.n - HS + lane;
+            const float2 v = m >= 0 ? p.in[m] : p.hist[HS + m];
+            p.hist[lane] = v;
+        }
+    }
 
     // raw sample for halo sample hl - HS of the chunk starting at t0 (lane hl
     // selects its own sample; the compiler makes it one per-lane load).  At a
@@ -396,8 +508,13 @@ __global__ void __launch_bounds__(kBlock) fwd_stream_kernel(FwdParams p)
         }
         if constexpr (REG)
             fir_outputs_reg<NI, L, S>(a, b, s, coef, zr, zi);
-        else
-            fir_outputs<NI, L, S>(a, b, s, top, M, zr, zi);
+        else {
+            // An opaque zero keeps the table reads inside the chunk loop:
+            // hoisted, the whole table would take registers.
+            int z = 0;
+            asm volatile("" : "+v"(z));
+            fir_outputs_lds<NI, L, S>(a, b, s, ctab + z, zr, zi);
+        }
     };
 
     // Store the S outputs of every lane of a full chunk.  S = 2: each lane's
@@ -414,19 +531,19 @@ __global__ void __launch_bounds__(kBlock) fwd_stream_kernel(FwdParams p)
 #pragma unroll
             for (int i = 0; i < S; ++i) X[lb + i] = make_float2(zr[i], zi[i]);
             wave_lds_order();
-            v4f *z4 = reinterpret_cast<v4f *>(zrow + t0);
+            v4f_s *z4 = reinterpret_cast<v4f_s *>(zrow + t0);
 #pragma unroll
             for (int i = 0; i < NV; ++i) {
                 const int j = 2 * (lane + 64 * i);
                 const int q = PL::OFF + j + j / S;
                 const float2 u = X[q], w = X[q + 1];
-                const v4f v = {u.x, u.y, w.x, w.y};
+                const v4f_s v = {u.x, u.y, w.x, w.y};
                 __builtin_nontemporal_store(v, z4 + lane + 64 * i);
             }
         }
     };
 
-    // ---- main loop over full chunks gw, gw + nw, ...
+    // ---- main loop over whole chunks gw, gw + nw, ...
     if (gw < total) {
         // chunk c <-> (row, k); advancing by nw chunks without dividing
         const int64_t dr = nw / tpr, dk = nw - (nw / tpr) * tpr;
@@ -447,12 +564,12 @@ __global__ void __launch_bounds__(kBlock) fwd_stream_kernel(FwdParams p)
         // (measured: 47.8 -> 47.2 us at the 2^24 headline, outputs unchanged).
         auto load_full = [&](ChunkRegs<S> &buf, const Cur &u) {
             __builtin_amdgcn_s_setprio(2);
-            const int64_t t0 = u.k * C;
-            const float4 *x4 = reinterpret_cast<const float4 *>(p.in + u.row * p.ld + t0);
+            const int64_t t0 = start(u.k);
+            const v4f_s *x4 = reinterpret_cast<const v4f_s *>(p.in + u.row * p.ld + t0);
 #pragma unroll
             for (int i = 0; i < NV; ++i) {
                 // read once: nontemporal (streaming) loads
-                const v4f t = __builtin_nontemporal_load(reinterpret_cast<const v4f *>(x4) + lane + 64 * i);
+                const v4f_s t = __builtin_nontemporal_load(x4 + lane + 64 * i);
                 buf.v[i] = make_float4(t.x, t.y, t.z, t.w);
             }
             buf.h = halo_raw_full(u.row, t0);
@@ -460,8 +577,9 @@ __global__ void __launch_bounds__(kBlock) fwd_stream_kernel(FwdParams p)
         };
         auto step = [&](const ChunkRegs<S> &buf, const Cur &u) {
             float zr[S], zi[S];
-            filter_chunk(buf, u.row, u.k * C, zr, zi);
-            store_chunk(p.out + u.row * p.ld, u.k * C, zr, zi);
+            const int64_t t0 = start(u.k);
+            filter_chunk(buf, u.row, t0, zr, zi);
+            store_chunk(p.out + u.row * p.ld, t0, zr, zi);
         };
         // Two chunks per trip with the next one always in flight; the loop
         // body is straight-line code (exact counter waits) and the last one
@@ -491,7 +609,7 @@ __global__ void __launch_bounds__(kBlock) fwd_stream_kernel(FwdParams p)
         }
     }
 
-    // ---- the partial last chunk of each row (when C does not divide n)
+    // ---- the end of rows too short for a moved last chunk
     if (tpr * C < p.n) {
         for (int64_t rw = gw; rw < rows; rw += nw) {
             const int64_t t0 = tpr * C;
@@ -549,15 +667,24 @@ hipError_t launch_fwd(const FwdParams &p, hipStream_t stream, int grid_mult)
     return hipGetLastError();
 }
 
+// Up to kSpecL taps: every launch shape.  More taps: one-shot at S = 2 and S = 4,
+// streaming at S = 8.
 template <int NI, int L>
 void register_fwd_one(FwdTable &t)
 {
+    if constexpr (L > kSpecL) {
+        for (int v = 0; v < kNumFwdVariants; ++v)
+            t.fn[NI - 1][L - 1][v] = (v & 1)  ? &launch_fwd<NI, L, 8, true>
+                                     : v == 0 ? &launch_fwd<NI, L, 2, false>
+                                              : &launch_fwd<NI, L, 4, false>;
+    } else {
     t.fn[NI - 1][L - 1][0] = &launch_fwd<NI, L, 2, false>;
     t.fn[NI - 1][L - 1][1] = &launch_fwd<NI, L, 2, true>;
     t.fn[NI - 1][L - 1][2] = &launch_fwd<NI, L, 4, false>;
     t.fn[NI - 1][L - 1][3] = &launch_fwd<NI, L, 4, true>;
     t.fn[NI - 1][L - 1][4] = &launch_fwd<NI, L, 8, false>;
     t.fn[NI - 1][L - 1][5] = &launch_fwd<NI, L, 8, true>;
+    }
 }
 
 }  // namespace dpd

@@ -10,7 +10,8 @@ namespace dpd {
 // Largest power level NI = (max order + 1) / 2 (orders up to 15) and taps.
 constexpr int kMaxNI = 8;
 constexpr int kMaxL = 16;
-// Specialised (fully unrolled) kernels exist for NI <= kSpecNI, L <= kSpecL.
+// Specialised (fully unrolled) kernels exist for NI <= kSpecNI, L <= kSpecL; the
+// streaming forward kernel for every L.
 constexpr int kSpecNI = 8;
 constexpr int kSpecL = 8;
 constexpr int kBlock = 256;
@@ -49,14 +50,14 @@ struct FwdParams {
     int64_t tiles_per_row;
     int64_t total_tiles;   // rows * tiles_per_row
     const float *M;        // precombined table
-    const float2 *hist;    // L-1 samples preceding row 0, or nullptr
+    float2 *hist;          // L-1 samples preceding row 0, or nullptr; the kernel leaves the
+                           // last L-1 samples of hist ++ in there
 };
 
 typedef hipError_t (*FwdLaunch)(const FwdParams &, hipStream_t, int grid_mult);
 
 struct FwdTable {
-    FwdLaunch fn[kSpecNI][kSpecL][kNumFwdVariants];
-    int tile[kNumFwdVariants];   // samples per tile (one-shot) or per wave chunk (streaming)
+    FwdLaunch fn[kSpecNI][kMaxL][kNumFwdVariants];
 };
 
 // Registration hooks, one per power-level translation unit.

@@ -13,6 +13,7 @@ struct dpd_plan {
     dpd::CoefMap map;
     int32_t K = 0;
     dpd_tune tune;
+    bool tuned = false;          // dpd_set_tune was called: use tune, else the rule by size
     std::vector<float> raw;      // host copy of the 2K coefficient floats
     float *d_table = nullptr;    // precombined table (device)
     float *d_table_call = nullptr;  // table of the calls that pass device coefficients
@@ -30,9 +31,9 @@ dpd_status make_map(const int32_t *mo, int32_t nm, const int32_t *co, int32_t nc
                     CoefMap &map);
 hipError_t launch_prep(const CoefMap &map, const void *raw, float *M, hipStream_t stream,
                        const int32_t *flag = nullptr);
-dpd_status run_forward(const CoefMap &map, const dpd_tune &tune, const float *M, hipStream_t stream,
+dpd_status run_forward(const CoefMap &map, const dpd_tune *tune_in, const float *M, hipStream_t stream,
                        const void *in, void *out, int64_t rows, int64_t n, int64_t ld,
-                       const void *hist);
+                       void *hist);
 dpd_status check_io(const void *in, const void *out, int64_t rows, int64_t n, int64_t ld);
 dpd_tune default_tune();
 bool valid_tune(const dpd_tune &t);

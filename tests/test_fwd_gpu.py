@@ -335,3 +335,66 @@ def test_set_coeffs_async_is_stream_ordered(torch, dpd, orc):
     plan2 = dpd.Plan(mo, co, L, hs[0])
     plan2.set_coeffs(hs[2])
     assert np.array_equal(_host(plan2.apply(xd)), _host(outs[2]))
+
+
+@pytest.mark.parametrize("mo,co,L", [([1, 3, 5, 7], [1, 3, 5, 7], 4), ([1, 3, 5, 7, 9], [1, 3], 12),
+                                     ([1, 3, 5, 7], [1, 5], 8), ([1, 3], [1], 16), ([1], [1], 1)])
+@pytest.mark.parametrize("off", [0, 1])
+def test_lengths_alignments_and_shapes_agree(torch, dpd, orc, mo, co, L, off):
+    """Rows around the edges of every launch shape's chunk (its moved last chunk,
+    its guarded end), at 16- and 8-byte aligned starts and an odd stride: each
+    shape gives the oracle's outputs, the same bits as the others, and writes
+    nothing else."""
+    h = signals.aph_coeffs(mo, co, L, config_id=94)
+    rows = 3
+    for n in (1, 2, 7, 127, 128, 129, 143, 511, 512, 513, 527, 528, 1025, 2049):
+        ld = n + 1 + (n & 1)            # odd: every second row starts 8-byte aligned
+        xs = np.stack([signals.ofdm_16qam(ld, config_id=94, stream_id=r) for r in range(rows)])
+        ref = [orc.forward(xs[r, :n], mo, co, L, h) for r in range(rows)]
+        buf = torch.zeros(rows * ld + 2, dtype=torch.complex64, device="cuda")
+        buf[off:off + rows * ld] = _dev(torch, xs).reshape(-1)
+        first = None
+        for tune in [None] + ALL_TUNES:
+            plan = dpd.Plan(mo, co, L, h)
+            if tune is not None:
+                plan.set_tune(samples_per_thread=tune[0], stage_lds=tune[1], grid_mult=2)
+            out = torch.full_like(buf, complex(7.0, -7.0))
+            dpd.dpd_apply_rows(plan.handle, dpd.current_stream(), buf.data_ptr() + 8 * off, out.data_ptr() + 8 * off,
+                               rows, n, ld)
+            o = _host(out)
+            if first is None:
+                first = o
+                body = o[off:off + rows * ld].reshape(rows, ld)
+                for r in range(rows):
+                    assert_parity(body[r, :n], ref[r], "n %d row %d" % (n, r))
+                mask = np.ones(o.size, bool)
+                for r in range(rows):
+                    mask[off + r * ld:off + r * ld + n] = False
+                assert np.all(o[mask] == np.complex64(complex(7.0, -7.0))), n
+            else:
+                assert np.array_equal(o.view(np.uint32), first.view(np.uint32)), (n, tune)
+
+
+@pytest.mark.parametrize("tune", [None] + ALL_TUNES)
+@pytest.mark.parametrize("L", [2, 4, 9, 16])
+def test_history_over_odd_chunks(torch, dpd, L, tune):
+    """Chunks shorter than the history, of one sample and around a launch shape's
+    chunk, at odd offsets: the outputs and the carried history are those of one
+    call, bit for bit."""
+    mo, co = [1, 3, 5], [1, 3]
+    h = signals.aph_coeffs(mo, co, L, config_id=95)
+    lens = [1, 3, 2, 140, 511, 513, 17, 2049, 5, 1]
+    x = _dev(torch, signals.ofdm_16qam(sum(lens), config_id=95))
+    plan = dpd.Plan(mo, co, L, h)
+    whole = plan.apply(x)
+    if tune is not None:
+        plan.set_tune(samples_per_thread=tune[0], stage_lds=tune[1], grid_mult=2)
+    hist = torch.zeros(L - 1, dtype=torch.complex64, device="cuda")
+    z = torch.empty_like(x)
+    t = 0
+    for m in lens:
+        plan.apply_hist(x[t:t + m], hist, out=z[t:t + m])
+        t += m
+        want = torch.cat([torch.zeros(L - 1, dtype=torch.complex64, device="cuda"), x[:t]])[-(L - 1):]
+        assert torch.equal(torch.view_as_real(hist), torch.view_as_real(want)), t
+    assert torch.equal(torch.view_as_real(z), torch.view_as_real(whole))
