@@ -17,9 +17,9 @@
  * Conventions shared by every entry point
  *   - Samples are interleaved complex64 (float re, float im; 8 bytes), in
  *     device memory owned by the caller.  Pointers must be 8-byte aligned;
- *     the forward calls take any such address and row stride at full speed,
- *     elsewhere 16-byte alignment (and an even row stride) selects the vector
- *     fast path.
+ *     dpd_apply* and dpd_backward take any such address and row stride at
+ *     full speed, elsewhere 16-byte alignment (and an even row stride)
+ *     selects the vector fast path.
  *   - Coefficients use the stacking of section 2.2: for each main-branch order
  *     (in the order passed to dpd_create) its L taps, then for each
  *     conjugate-branch order its L taps, then c.  K = (n_main + n_conj)*L + 1
@@ -154,9 +154,8 @@ dpd_status dpd_apply_rows(dpd_plan *plan, void *stream, const void *in, void *ou
 /* dpd_apply_coeffs -- as dpd_apply_rows, but the coefficients are read from a
  * device array of K complex64 (section 2.2 layout) in stream order, without a
  * host round trip (used by training).  They are precombined into a second
- * table of the plan, used only by calls that pass device coefficients (this
- * one and dpd_backward with coeffs_dev): the plan's own coefficients stay as
- * they were.  Such calls on one plan that overlap in time (different
+ * table of the plan, used only by this call: the plan's own coefficients stay
+ * as they were.  Such calls on one plan that overlap in time (different
  * streams) race on that second table; order them, or use one plan each. */
 dpd_status dpd_apply_coeffs(dpd_plan *plan, void *stream, const void *coeffs_dev,
                             const void *in, void *out, int64_t rows, int64_t n, int64_t ld);
@@ -173,11 +172,10 @@ dpd_status dpd_apply_hist(dpd_plan *plan, void *stream, const void *in, void *ou
 /* --------------------------------------------------------------- backward --
  * Gradient of a real loss E through Eq. (1) (not in the paper).  Complex
  * gradients follow the convention dE/dRe + j dE/dIm (the one PyTorch uses).
- *   coeffs_dev   K complex64 on the device, or NULL to use the plan's (device
- *                coefficients go through the plan's second table, as in
- *                dpd_apply_coeffs; the plan's own coefficients are untouched;
- *                read only when grad_x is requested: dE/dcoeffs does not
- *                depend on the coefficients)
+ *   coeffs_dev   K complex64 on the device, or NULL to use the plan's (the
+ *                kernel precombines device coefficients itself; the plan's
+ *                own coefficients are untouched; read only when grad_x is
+ *                requested: dE/dcoeffs does not depend on the coefficients)
  *   x            inputs of the forward call, rows x n with row stride ld
  *   grad_z       dE/dz for the outputs, same shape
  *   grad_x       receives dE/dx (same shape), or NULL to skip it

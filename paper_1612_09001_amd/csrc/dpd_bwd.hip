@@ -1,5 +1,5 @@
-// Host side of the backward pass (dpd_backward, dpd_backward_ws_size) plus
-// the generic backward kernels (any L <= 16) and the FP64 finalisation.
+// Host side of the backward pass (dpd_backward, dpd_backward_ws_size) and the
+// FP64 finalisation.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -15,9 +15,6 @@
 namespace dpd {
 
 int num_cus();
-
-constexpr int kGenericBlocks = 1024;   // fixed grid of the generic kernels
-constexpr int kGroup = 16;             // coefficient-gradient entries per pass
 
 static BwdTable g_bwd;
 static std::once_flag g_bwd_once;
@@ -41,7 +38,7 @@ static const BwdTable &bwd_table()
 // Resident blocks per CU of a specialised backward kernel (cached).
 static int bwd_occupancy(int NI, int L, int want)
 {
-    static int cache[kSpecNI][kSpecL][3] = {};
+    static int cache[kSpecNI][kMaxL][3] = {};
     static std::mutex mu;
     std::lock_guard<std::mutex> lk(mu);
     int &o = cache[NI - 1][L - 1][want];
@@ -53,92 +50,6 @@ static int bwd_occupancy(int NI, int L, int want)
         o = v;
     }
     return o;
-}
-
-// ------------------------------------------------------- generic kernels ---
-
-// dE/dx, one sample per thread, runtime NI and L.
-__global__ void __launch_bounds__(kBlock) bwd_dx_generic(BwdParams p, int NI, int L)
-{
-    const cfloat *M = as_const(p.M);
-    const int64_t total = p.rows * p.n;
-    for (int64_t idx = (int64_t)blockIdx.x * kBlock + threadIdx.x; idx < total;
-         idx += (int64_t)gridDim.x * kBlock) {
-        const int64_t row = idx / p.n, m = idx - row * p.n;
-        const float2 v = p.x[row * p.ld + m];
-        const float a = v.x, b = v.y, s = __builtin_fmaf(a, a, b * b);
-        float Pa = 0.f, Pb = 0.f, Q = 0.f;
-        for (int j = NI - 1; j >= 0; --j) {
-            float ua = 0.f, ub = 0.f;
-            for (int k = 0; k < L && m + k < p.n; ++k) {
-                const float2 g = p.gz[row * p.ld + m + k];
-                const cfloat *Mk = M + 4 * (k * NI + j);
-                ua = __builtin_fmaf(Mk[0], g.x, ua);
-                ua = __builtin_fmaf(Mk[2], g.y, ua);
-                ub = __builtin_fmaf(Mk[1], g.x, ub);
-                ub = __builtin_fmaf(Mk[3], g.y, ub);
-            }
-            Pa = __builtin_fmaf(Pa, s, ua);
-            Pb = __builtin_fmaf(Pb, s, ub);
-            if (j > 0) Q = __builtin_fmaf(Q, s, (float)j * __builtin_fmaf(a, ua, b * ub));
-        }
-        p.gx[row * p.ld + m] = make_float2(__builtin_fmaf(2.f * Q, a, Pa), __builtin_fmaf(2.f * Q, b, Pb));
-    }
-}
-
-// dE/dM entries [g*kGroup, (g+1)*kGroup) for the samples of block b (a
-// contiguous range of the flattened rows); one partial per (block, entry).
-__global__ void __launch_bounds__(kBlock) bwd_dc_generic(BwdParams p, int NI, int L)
-{
-    __shared__ double red[kBlock];
-    const int E = 4 * L * NI + 2;
-    const int64_t total = p.rows * p.n;
-    const int64_t per = (total + gridDim.x - 1) / gridDim.x;
-    const int64_t lo = (int64_t)blockIdx.x * per;
-    const int64_t hi = lo + per < total ? lo + per : total;
-    // FP32 sums over at most 64 samples per thread, then FP64
-    float acc[kGroup];
-    double accd[kGroup];
-    for (int q = 0; q < kGroup; ++q) acc[q] = 0.f, accd[q] = 0.0;
-    int cnt = 0;
-    for (int64_t idx = lo + threadIdx.x; idx < hi; idx += kBlock) {
-        if (++cnt == 64) {
-            for (int q = 0; q < kGroup; ++q) accd[q] += acc[q], acc[q] = 0.f;
-            cnt = 0;
-        }
-        const int64_t row = idx / p.n, m = idx - row * p.n;
-        const float2 v = p.x[row * p.ld + m];
-        const float s = __builtin_fmaf(v.x, v.x, v.y * v.y);
-        for (int q = 0; q < kGroup; ++q) {
-            const int e = blockIdx.y * kGroup + q;
-            if (e >= E) break;
-            if (e >= E - 2) {
-                const float2 g = p.gz[row * p.ld + m];
-                acc[q] += e == E - 2 ? g.x : g.y;
-                continue;
-            }
-            const int rc = e & 3, jk = e >> 2, k = jk / NI, j = jk - k * NI;
-            if (m + k >= p.n) continue;
-            const float2 g = p.gz[row * p.ld + m + k];
-            float r = 1.f;
-            for (int t = 0; t < j; ++t) r *= s;
-            const float gc = (rc < 2) ? g.x : g.y;
-            const float pc = (rc & 1) ? r * v.y : r * v.x;
-            acc[q] = __builtin_fmaf(gc, pc, acc[q]);
-        }
-    }
-    for (int q = 0; q < kGroup; ++q) {
-        const int e = blockIdx.y * kGroup + q;
-        if (e >= E) break;
-        red[threadIdx.x] = accd[q] + (double)acc[q];
-        __syncthreads();
-        for (int w = kBlock / 2; w > 0; w >>= 1) {
-            if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) p.partials[(int64_t)blockIdx.x * E + e] = (float)red[0];
-        __syncthreads();
-    }
 }
 
 // Coefficient-gradient finalisation: block q sums, in FP64, the partials of
@@ -165,15 +76,12 @@ __global__ void __launch_bounds__(kBlock) bwd_finalize(const float *__restrict__
     for (int i = 0; i < c; ++i) gcoef[idx[i]] = g[i];
 }
 
-static bool spec_ok(const CoefMap &m) { return m.NI <= kSpecNI && m.L <= kSpecL; }
-
-static int64_t spec_grid_cap() { return (int64_t)num_cus() * 8; }
+static int64_t grid_cap() { return (int64_t)num_cus() * 8; }
 
 size_t bwd_ws_bytes(const CoefMap &map)
 {
     const int64_t E = 4 * map.L * map.NI + 2;
-    const int64_t blocks = std::max<int64_t>(spec_grid_cap(), kGenericBlocks);
-    return (size_t)(blocks * E * (int64_t)sizeof(float) + 256);
+    return (size_t)(grid_cap() * E * (int64_t)sizeof(float) + 256);
 }
 
 hipError_t launch_bwd_finalize(const float *partials, int nblk, const CoefMap &map, float2 *grad_coeffs,
@@ -219,14 +127,6 @@ static dpd_status backward_impl(dpd_plan *plan, void *stream, const void *coeffs
         };
         if (ov(grad_x, x) || ov(grad_x, grad_z)) return DPD_EINVAL;
     }
-    // only dx reads the coefficients: dE/dcoeffs is the correlation of grad_z
-    // with the basis of x alone
-    const float *table = plan->d_table;
-    if (coeffs_dev != nullptr && want_dx) {
-        hipError_t e = launch_prep(map, coeffs_dev, plan->d_table_call, st);
-        if (e != hipSuccess) return hip_fail(e);
-        table = plan->d_table_call;
-    }
     if (!want_dx && !want_dc) return DPD_OK;
 
     BwdParams p;
@@ -234,43 +134,40 @@ static dpd_status backward_impl(dpd_plan *plan, void *stream, const void *coeffs
     p.gz = (const float2 *)grad_z;
     p.gx = (float2 *)grad_x;
     p.partials = (float *)ws;
+    p.E = 4 * map.L * map.NI + 2;
     p.n = n;
     p.ld = ld;
     p.rows = rows;
-    p.M = table;
+    // only dx reads the coefficients: dE/dcoeffs is the correlation of grad_z
+    // with the basis of x alone
+    p.M = plan->d_table;
+    p.raw = (const float2 *)coeffs_dev;
+    p.map = map;
     int nblk = 0;
     if (!empty) {
-        const bool aligned = (uintptr_t)x % 16 == 0 && (uintptr_t)grad_z % 16 == 0 &&
-                             (uintptr_t)grad_x % 16 == 0 && (rows == 1 || ld % 2 == 0);
-        if (aligned && spec_ok(map)) {
+        const int64_t C = 64 * kBwdS;
+        p.tpr = n / C;
+        const int64_t chunks = rows * ((n + C - 1) / C);
+        const BwdTable &t = bwd_table();
+        const auto grid_of = [&](int L, int want) {
+            const int64_t cap = (int64_t)num_cus() * std::min(8, bwd_occupancy(map.NI, L, want));
+            return (int)std::max<int64_t>(1, std::min(cap, (chunks + 3) / 4));
+        };
+        hipError_t e = hipSuccess;
+        if (map.L <= kSpecL) {
             const int want = want_dx && want_dc ? 2 : (want_dc ? 1 : 0);
-            const int64_t C = 64 * kBwdS;
-            p.tpr = n / C;
-            const int64_t chunks = rows * ((n + C - 1) / C);
-            const int64_t cap = (int64_t)num_cus() * std::min(8, bwd_occupancy(map.NI, map.L, want));
-            const int64_t grid = std::max<int64_t>(1, std::min(cap, (chunks + 3) / 4));
-            hipError_t e = bwd_table().fn[map.NI - 1][map.L - 1][want](p, st, (int)grid);
-            if (e != hipSuccess) return hip_fail(e);
-            nblk = (int)grid;
+            nblk = grid_of(map.L, want);
+            e = t.fn[map.NI - 1][map.L - 1][want](p, st, nblk);
         } else {
-            p.tpr = 0;
-            if (want_dx) {
-                const int64_t blocks = std::min<int64_t>((rows * n + kBlock - 1) / kBlock, 1 << 20);
-                hipLaunchKernelGGL(bwd_dx_generic, dim3((uint32_t)blocks), dim3(kBlock), 0, st, p,
-                                   map.NI, map.L);
-                hipError_t e = hipGetLastError();
-                if (e != hipSuccess) return hip_fail(e);
-            }
+            if (want_dx) e = t.fn[map.NI - 1][map.L - 1][0](p, st, grid_of(map.L, 0));
             if (want_dc) {
-                const int E = 4 * map.L * map.NI + 2;
-                const int groups = (E + kGroup - 1) / kGroup;
-                hipLaunchKernelGGL(bwd_dc_generic, dim3(kGenericBlocks, groups), dim3(kBlock), 0, st, p,
-                                   map.NI, map.L);
-                hipError_t e = hipGetLastError();
-                if (e != hipSuccess) return hip_fail(e);
-                nblk = kGenericBlocks;
+                // two passes over the taps, the same blocks in both
+                nblk = grid_of(kSpecL, 1);
+                if (e == hipSuccess) e = t.fn[map.NI - 1][kSpecL - 1][1](p, st, nblk);
+                if (e == hipSuccess) e = t.tail[map.NI - 1][map.L - kSpecL - 1](p, st, nblk);
             }
         }
+        if (e != hipSuccess) return hip_fail(e);
     }
     if (want_dc) {
         hipLaunchKernelGGL(bwd_finalize, dim3((uint32_t)(map.L * map.NI + 1)), dim3(kBlock), 0, st,

@@ -1,5 +1,5 @@
 // Instantiates the specialised backward kernels for NI = DPD_NI (set on the
-// compiler command line) and every L in 1..kSpecL.
+// compiler command line) and every L in 1..kMaxL.
 #include "dpd_bwd_kernels.h"
 
 #ifndef DPD_NI
@@ -21,6 +21,14 @@ void DPD_CAT(register_bwd_ni, DPD_NI)(BwdTable &t)
     register_bwd_one<DPD_NI, 6>(t);
     register_bwd_one<DPD_NI, 7>(t);
     register_bwd_one<DPD_NI, 8>(t);
+    register_bwd_one<DPD_NI, 9>(t);
+    register_bwd_one<DPD_NI, 10>(t);
+    register_bwd_one<DPD_NI, 11>(t);
+    register_bwd_one<DPD_NI, 12>(t);
+    register_bwd_one<DPD_NI, 13>(t);
+    register_bwd_one<DPD_NI, 14>(t);
+    register_bwd_one<DPD_NI, 15>(t);
+    register_bwd_one<DPD_NI, 16>(t);
 }
 
 }  // namespace dpd

@@ -23,6 +23,7 @@
 
 #include "dpd_fwd_kernels.h"
 #include "dpd_reduce.h"
+#include "dpd_table.h"
 
 namespace dpd {
 
@@ -31,16 +32,26 @@ struct BwdParams {
     const float2 *gz;
     float2 *gx;           // nullptr: no input gradient
     float *partials;      // [gridDim.x][E] (E = 4*L*NI + 2), nullptr: no coeff gradient
+    int32_t E;            // E of the whole filter (a pass may cover some of its taps)
     int64_t n, ld, rows;
     int64_t tpr;          // full chunks per row (n / (64*S)); the ragged end is extra
     const float *M;       // precombined table
+    const float2 *raw;    // or the K raw coefficients, precombined by every block
+    CoefMap map;
 };
 
 typedef hipError_t (*BwdLaunch)(const BwdParams &, hipStream_t, int grid);
 
+// Filters of up to kSpecL taps: one pass, want 0 = dx, 1 = dcoef, 2 = both.
+// Longer ones: dx in one pass (want 0), the coefficient gradient in two, taps
+// 0..7 as want 1 of kSpecL taps and taps 8.. by `tail` (their accumulators
+// would not fit the registers at once).  Measured: 32 rows of 20001 samples, six
+// taps, 13.4 us where odd row starts took one thread per sample and two passes
+// over the rows per sixteen entries, 161 us.
 struct BwdTable {
-    BwdLaunch fn[kSpecNI][kSpecL][3];   // [.][.][want: 0 = dx, 1 = dcoef, 2 = both]
-    const void *kern[kSpecNI][kSpecL][3];
+    BwdLaunch fn[kSpecNI][kMaxL][3];
+    const void *kern[kSpecNI][kMaxL][3];
+    BwdLaunch tail[kSpecNI][kSpecL];   // [.][taps beyond kSpecL - 1], dcoef
 };
 
 void register_bwd_ni1(BwdTable &);
@@ -136,29 +147,35 @@ struct BwdTag {
 // the power levels j (ascending) produces both gradients: U_j by taps for dx
 // (P = sum s^j U_j and 2Q = sum 2j s^(j-1) v.U_j accumulated with explicit
 // powers; dx = P + 2Q v), and G (x) s^j v into the per-lane coefficient
-// accumulators.
-template <int NI, int L, bool DX, bool DC>
+// accumulators.  K0: the first tap of a pass over taps K0 .. K0 + L - 1 of a
+// longer filter (coefficient gradient only).  Rows may start at any sample:
+// 16-byte accesses need no 16-byte alignment here (v4f_s).
+template <int NI, int L, bool DX, bool DC, int K0 = 0>
 __global__ void __launch_bounds__(kBlock) bwd_kernel(BwdParams p)
 {
+    static_assert(!DX || K0 == 0, "the input gradient needs every tap");
+    static_assert(K0 % kBwdS == 0, "the window of a pass starts on a pad group");
     constexpr int S = kBwdS;
     constexpr int C = 64 * S;
     constexpr int W = S + L - 1;
     constexpr int NV = S / 2;
     constexpr int WAVES = kBlock / 64;
     constexpr int NM = 4 * L * NI;                              // matrix floats (c has no gradient path here)
-    constexpr int E = NM + 2;
-    constexpr int HS = L - 1;                                   // right halo
+    constexpr int E = NM + (K0 == 0 ? 2 : 0);                   // c belongs to the first pass
+    constexpr int HS = K0 + L - 1;                              // right halo
     constexpr int GSLOTS = C + HS + (C + HS) / S + 1;
     constexpr int XSLOTS = C + C / S;
     __shared__ __align__(16) float2 gs[WAVES][GSLOTS];
     __shared__ __align__(16) float2 xsh[WAVES][XSLOTS];
-    __shared__ __align__(16) float mt[NM];
+    __shared__ __align__(16) float mt[DX ? NM : 1];
     __shared__ double red[DC ? WAVES * E : 1];   // per-wave FP64 totals of the coefficient gradient
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    for (int e = tid; e < NM; e += kBlock) mt[e] = p.M[e];
-    __syncthreads();
+    if constexpr (DX) {
+        for (int e = tid; e < NM; e += kBlock) mt[e] = table_entry(p.M, p.raw, p.map, e);
+        __syncthreads();
+    }
     float2 *G = gs[wv];
     float2 *X = xsh[wv];
     // slot of chunk-relative sample d: one pad after every S
@@ -191,16 +208,16 @@ __global__ void __launch_bounds__(kBlock) bwd_kernel(BwdParams p)
     };
     // full chunk at (row, t0): every load unconditional
     auto load_full = [&](Regs &R, int64_t row, int64_t t0) {
-        const v4f *g4 = reinterpret_cast<const v4f *>(p.gz + row * p.ld + t0);
-        const v4f *x4 = reinterpret_cast<const v4f *>(p.x + row * p.ld + t0);
+        const v4f_s *g4 = reinterpret_cast<const v4f_s *>(p.gz + row * p.ld + t0);
+        const v4f_s *x4 = reinterpret_cast<const v4f_s *>(p.x + row * p.ld + t0);
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
-            const v4f u = __builtin_nontemporal_load(g4 + lane + 64 * i);
+            const v4f_s u = __builtin_nontemporal_load(g4 + lane + 64 * i);
             R.g[i] = make_float4(u.x, u.y, u.z, u.w);
         }
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
-            const v4f u = __builtin_nontemporal_load(x4 + lane + 64 * i);
+            const v4f_s u = __builtin_nontemporal_load(x4 + lane + 64 * i);
             R.x[i] = make_float4(u.x, u.y, u.z, u.w);
         }
         if (HS > 0) {
@@ -248,7 +265,7 @@ __global__ void __launch_bounds__(kBlock) bwd_kernel(BwdParams p)
         float ga[W], gb[W];
 #pragma unroll
         for (int w = 0; w < W; ++w) {
-            const float2 g = G[slot(lane * S + w)];
+            const float2 g = G[slot(lane * S + w) + K0 + K0 / S];   // sample K0 on
             ga[w] = g.x;
             gb[w] = g.y;
         }
@@ -278,7 +295,8 @@ __global__ void __launch_bounds__(kBlock) bwd_kernel(BwdParams p)
             }
 #pragma unroll
             for (int k = 0; k < L; ++k) {
-                const float4 m = M4[k * NI + j];   // [[m.x, m.y], [m.z, m.w]]
+                float4 m;   // [[m.x, m.y], [m.z, m.w]]
+                if constexpr (DX) m = M4[k * NI + j];
 #pragma unroll
                 for (int i = 0; i < S; ++i) {
                     const float a = ga[i + k], b = gb[i + k];
@@ -328,7 +346,7 @@ __global__ void __launch_bounds__(kBlock) bwd_kernel(BwdParams p)
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-        if constexpr (DC) {
+        if constexpr (DC && K0 == 0) {
 #pragma unroll
             for (int i = 0; i < S; ++i) {
                 acc[E - 2] += ga[i];
@@ -349,12 +367,12 @@ __global__ void __launch_bounds__(kBlock) bwd_kernel(BwdParams p)
 #pragma unroll
                 for (int i = 0; i < S; ++i) G[slot(lane * S + i)] = make_float2(dxa[i], dxb[i]);
                 wave_lds_order();
-                v4f *o4 = reinterpret_cast<v4f *>(gxr + t0);
+                v4f_s *o4 = reinterpret_cast<v4f_s *>(gxr + t0);
 #pragma unroll
                 for (int i = 0; i < NV; ++i) {
                     const int j = 2 * (lane + 64 * i);
                     const float2 u = G[slot(j)], w = G[slot(j) + 1];
-                    const v4f v = {u.x, u.y, w.x, w.y};
+                    const v4f_s v = {u.x, u.y, w.x, w.y};
                     __builtin_nontemporal_store(v, o4 + lane + 64 * i);
                 }
             } else {
@@ -414,15 +432,16 @@ __global__ void __launch_bounds__(kBlock) bwd_kernel(BwdParams p)
             double t = 0.0;
 #pragma unroll
             for (int w = 0; w < WAVES; ++w) t += red[w * E + e];
-            p.partials[(int64_t)blockIdx.x * E + e] = (float)t;
+            const int at = e < NM ? 4 * NI * K0 + e : p.E - 2 + (e - NM);
+            p.partials[(int64_t)blockIdx.x * p.E + at] = (float)t;
         }
     }
 }
 
-template <int NI, int L, bool DX, bool DC>
+template <int NI, int L, bool DX, bool DC, int K0 = 0>
 hipError_t launch_bwd(const BwdParams &p, hipStream_t stream, int grid)
 {
-    hipLaunchKernelGGL((bwd_kernel<NI, L, DX, DC>), dim3((uint32_t)grid), dim3(kBlock), 0, stream, p);
+    hipLaunchKernelGGL((bwd_kernel<NI, L, DX, DC, K0>), dim3((uint32_t)grid), dim3(kBlock), 0, stream, p);
     return hipGetLastError();
 }
 
@@ -430,11 +449,14 @@ template <int NI, int L>
 void register_bwd_one(BwdTable &t)
 {
     t.fn[NI - 1][L - 1][0] = &launch_bwd<NI, L, true, false>;
-    t.fn[NI - 1][L - 1][1] = &launch_bwd<NI, L, false, true>;
-    t.fn[NI - 1][L - 1][2] = &launch_bwd<NI, L, true, true>;
     t.kern[NI - 1][L - 1][0] = (const void *)&bwd_kernel<NI, L, true, false>;
-    t.kern[NI - 1][L - 1][1] = (const void *)&bwd_kernel<NI, L, false, true>;
-    t.kern[NI - 1][L - 1][2] = (const void *)&bwd_kernel<NI, L, true, true>;
+    if constexpr (L <= kSpecL) {
+        t.fn[NI - 1][L - 1][1] = &launch_bwd<NI, L, false, true>;
+        t.fn[NI - 1][L - 1][2] = &launch_bwd<NI, L, true, true>;
+        t.kern[NI - 1][L - 1][1] = (const void *)&bwd_kernel<NI, L, false, true>;
+        t.kern[NI - 1][L - 1][2] = (const void *)&bwd_kernel<NI, L, true, true>;
+        t.tail[NI - 1][L - 1] = &launch_bwd<NI, L, false, true, kSpecL>;
+    }
 }
 
 }  // namespace dpd

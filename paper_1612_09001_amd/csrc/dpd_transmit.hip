@@ -28,6 +28,7 @@
 #include "dpd_cascade.h"
 #include "dpd_fwd_kernels.h"
 #include "dpd_plan.h"
+#include "dpd_table.h"
 
 #define DPD_EXPORT extern "C" __attribute__((visibility("default")))
 
@@ -50,25 +51,6 @@ struct TxParams {
     float *partials;         // one loss partial per block
     int vec;                 // rows start 16-byte aligned: whole octets use 16-byte accesses
 };
-
-// Entry e of the predistorter's precombined table (4 L NI matrix floats, then
-// c): read from the plan's table, or formed from the raw coefficients with
-// the arithmetic of the table kernel (hr+gr, gi-hi, hi+gi, hr-gr), so both give
-// the same bits.
-__device__ __forceinline__ float tx_table_entry(const TxParams &p, int e)
-{
-    if (p.raw == nullptr) return p.M[e];
-    const int L = p.map.L, NI = p.map.NI;
-    if (e >= 4 * L * NI) {
-        const float2 c = p.raw[(p.map.n_main + p.map.n_conj) * L];
-        return e == 4 * L * NI ? c.x : c.y;
-    }
-    const int k = e / (4 * NI), r = e - k * 4 * NI, j = r >> 2, q = r & 3;
-    float2 h = make_float2(0.f, 0.f), g = make_float2(0.f, 0.f);
-    if (p.map.main_idx[j] >= 0) h = p.raw[p.map.main_idx[j] * L + k];
-    if (p.map.conj_idx[j] >= 0) g = p.raw[(p.map.n_main + p.map.conj_idx[j]) * L + k];
-    return q == 0 ? h.x + g.x : q == 1 ? g.y - h.y : q == 2 ? h.y + g.y : h.x - g.x;
-}
 
 // The predistorter's filter for tables too large for registers: the top
 // Horner level of every tap in VGPRs (`top`), the lower levels of each tap
@@ -144,7 +126,7 @@ __global__ void __launch_bounds__(kBlock) transmit_fwd_kernel(TxParams p)
     // VGPRs.  Stage A is memoryless with one power level: u = c + M0 z.
     const int tid = threadIdx.x;
     if (tid < NC)
-        mtab[tid] = tx_table_entry(p, tid);
+        mtab[tid] = table_entry(p.M, p.raw, p.map, tid);
     else if (tid < NC + NB)
         tab[tid - NC] = p.B[tid - NC];
     else if (tid < NC + NB + 6)
@@ -310,7 +292,7 @@ __global__ void __launch_bounds__(kBlock) transmit_stream_kernel(TxParams p)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (tid < NC)
-        mtab[tid] = tx_table_entry(p, tid);
+        mtab[tid] = table_entry(p.M, p.raw, p.map, tid);
     else if (REG && tid < NC + NB)
         tab[tid - NC] = p.B[tid - NC];
     else if (REG && tid < NC + NB + 6)

@@ -182,3 +182,60 @@ def test_config5_shape_full(torch, dpd, orc):
     G = signals.cgauss((rows, n), config_id=5)
     h = signals.aph_coeffs(mo, co, L, config_id=5)
     _check(torch, dpd, orc, x, G, mo, co, L, h, what="config5")
+
+
+@pytest.mark.parametrize("mo,co,L", [([1, 3, 5, 7], [1, 3, 5, 7], 4), ([1, 3, 5], [1], 9),
+                                     ([1, 3, 5, 7, 9], [1, 3], 12), ([1, 3, 5, 7, 9, 11, 13, 15], [1, 3], 16)])
+def test_long_filters_and_odd_starts(torch, dpd, orc, mo, co, L):
+    """Filters of more than eight taps (the coefficient gradient in two passes over
+    the taps) and rows at 8-byte aligned starts with an odd stride, at lengths
+    around the 256-sample chunk and its halo; each gradient alone gives the
+    bits it has in the call for both where the passes are the same."""
+    h = signals.aph_coeffs(mo, co, L, config_id=86)
+    plan = dpd.Plan(mo, co, L, h)
+    rows = 3
+    for n in (1, 5, 8, 16, 255, 257, 263, 271, 512, 1030):
+        ld = n + 1 + (n & 1)
+        x = np.stack([signals.ofdm_16qam(ld, config_id=86, stream_id=r) for r in range(rows)])
+        G = signals.cgauss((rows, ld), config_id=86, stream_id=n)
+        rx, rc = np.zeros((rows, n), np.complex128), 0
+        for r in range(rows):
+            a, b = orc.backward(x[r, :n], mo, co, L, h, G[r, :n])
+            rx[r] = a
+            rc = rc + b
+        def odd(v):   # the rows behind one sample: 8-byte aligned
+            t = torch.zeros(rows * ld + 1, dtype=torch.complex64, device="cuda")
+            t[1:] = _dev(torch, v).reshape(-1)
+            return t[1:].view(rows, ld)[:, :n]
+        xd, gd = odd(x), odd(G)
+        gx = torch.full_like(odd(x).as_strided((rows * ld,), (1,)), complex(7.0, -7.0))
+        ws = torch.empty(dpd.dpd_backward_ws_size(plan.handle, rows, n), dtype=torch.uint8, device="cuda")
+        gc = torch.empty(plan.K, dtype=torch.complex64, device="cuda")
+        st = dpd.current_stream()
+        out = {}
+        for want in ("both", "dx", "dc"):
+            gx.fill_(complex(7.0, -7.0))
+            gc.fill_(0)
+            dpd.dpd_backward(plan.handle, st, 0, xd.data_ptr(), gd.data_ptr(), gx.data_ptr() if want != "dc" else 0,
+                             gc.data_ptr() if want != "dx" else 0, rows, n, ld, ws.data_ptr(), ws.numel())
+            out[want] = (gx.cpu().numpy().reshape(rows, ld).copy(), gc.cpu().numpy().copy())
+        assert_parity(out["both"][0][:, :n].reshape(-1), rx.reshape(-1), "dx n=%d" % n)
+        assert_dcoef(out["both"][1], rc, "dcoef n=%d" % n)
+        assert_dcoef(out["dc"][1], rc, "dcoef alone n=%d" % n)
+        assert np.all(out["both"][0][:, n:] == np.complex64(complex(7.0, -7.0)))
+        assert_parity(out["dx"][0][:, :n].reshape(-1), rx.reshape(-1), "dx alone n=%d" % n)
+        if L > 8:
+            assert np.array_equal(out["dx"][0], out["both"][0]) and np.array_equal(out["dc"][1], out["both"][1])
+
+
+def test_device_coefficients_give_the_plans_bits(torch, dpd):
+    """Kernels that form the table from device coefficients use the arithmetic of
+    the plan's table: dx bit for bit."""
+    for mo, co, L in (([1, 3, 5, 7], [1, 5], 4), ([1, 3, 5], [1, 3, 5], 13)):
+        h = signals.aph_coeffs(mo, co, L, config_id=87)
+        plan, other = dpd.Plan(mo, co, L, h), dpd.Plan(mo, co, L, np.zeros_like(h))
+        x, G = _dev(torch, signals.ofdm_16qam(3001, config_id=87)), _dev(torch, signals.cgauss(3001, config_id=87))
+        a, ac = plan.backward(x, G)
+        b, bc = other.backward(x, G, coeffs=_dev(torch, h))
+        assert torch.equal(torch.view_as_real(a), torch.view_as_real(b))
+        assert torch.equal(torch.view_as_real(ac), torch.view_as_real(bc))
