@@ -224,10 +224,10 @@ typedef struct dpd_stream_desc {
 } dpd_stream_desc;
 
 /* dpd_batch_create -- validate the descriptors, cut every stream into chunks
- * of 64*S samples (S = tune->samples_per_thread; a stream's last chunk may be
- * shorter), list them most expensive class first, upload the list (32 bytes
- * per chunk), and size the persistent grid.
- * `tune` may be NULL for the default launch shape.  The descriptor pointers
+ * of 64*S samples (S = tune->samples_per_thread; the last one moved back to
+ * the stream's end, streams shorter than a chunk apart), list them most
+ * expensive class first, upload the list (32 bytes per chunk), and size the
+ * persistent grid.  `tune` may be NULL for a launch shape by total size.  The descriptor pointers
  * must stay valid for the life of the batch.  Synchronous on the host (the
  * chunk list and zeroed tables are in device memory on return; no device-wide
  * wait). */

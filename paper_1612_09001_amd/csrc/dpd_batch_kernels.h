@@ -3,8 +3,10 @@
 //
 // The host cuts every stream into chunks of C = 64*S samples and lists them
 // in one array of 32-byte chunk descriptors: all full chunks first, streams
-// ordered most expensive class first (per-sample cost ~ NI * L), then the
-// ragged last chunk of each stream (a second, small launch filters those),
+// ordered most expensive class first (per-sample cost ~ NI * L) -- where C does
+// not divide a stream, its last chunk is its last C samples (the samples shared
+// with the chunk before come out the same in both, stored with the same bits)
+// -- then the streams shorter than C (a second, small launch filters those),
 // then one idle entry.  The persistent grid walks the full chunks the way the
 // single-stream kernel walks one stream: wave g
 // takes entries g, g + nw, g + 2 nw, ... (nw = waves in the grid), so
@@ -28,6 +30,10 @@
 
 namespace dpd {
 
+// Streams may start at any sample (8-byte alignment): see v4f_s.
+typedef const v4f_s __attribute__((address_space(1))) gcv4f_s;
+typedef v4f_s __attribute__((address_space(1))) gv4f_s;
+
 constexpr int kBatchMaxNI = 5;   // orders up to 9 in the persistent kernel
 constexpr int kBatchMaxL = 8;
 constexpr int kBatchHalo = kBatchMaxL - 1;   // samples before a chunk fetched for every class
@@ -40,7 +46,7 @@ struct BatchChunk {
     float2 *out;        // first output sample of the chunk
     int32_t tab;        // float offset of the stream's table (16-byte aligned)
     uint32_t meta;      // class | hist << 8 | nc4 << 16 (see BatchDesc)
-    int32_t valid;      // samples in the chunk (C except for a stream's ragged end)
+    int32_t valid;      // samples in the chunk (C except for a stream shorter than C)
     int32_t pad_;
 };
 static_assert(sizeof(BatchChunk) == 32, "descriptor is read as 8 dwords");
@@ -63,7 +69,7 @@ struct BatchPrepJob {
 static_assert(sizeof(BatchPrepJob) == 32, "job layout");
 
 struct BatchParams {
-    const BatchChunk *chunks;   // [0, n_full) full, [n_full, n_chunks) ragged, [n_chunks] idle
+    const BatchChunk *chunks;   // [0, n_full) full, [n_full, n_chunks) short streams, [n_chunks] idle
     int64_t n_full;
     int64_t n_chunks;
     const float *tables;
@@ -121,10 +127,10 @@ __device__ __forceinline__ void batch_load(BatchRegs<S> &R, const BatchDesc &D, 
 {
     constexpr int NV = S / 2;
     if constexpr (FULL) {
-        const gcv4f *x4 = (const gcv4f *)D.in;
+        gcv4f_s *x4 = (gcv4f_s *)D.in;
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
-            const v4f u = __builtin_nontemporal_load(x4 + lane + 64 * i);
+            const v4f_s u = __builtin_nontemporal_load(x4 + lane + 64 * i);
             R.v[i] = make_float4(u.x, u.y, u.z, u.w);
         }
     } else {
@@ -222,8 +228,8 @@ __device__ __forceinline__ void batch_step(const BatchDesc &D, float2 *X0, float
             if (lane * S + i < D.valid) D.out[lane * S + i] = o;
         }
     } else if constexpr (S == 2) {
-        const v4f o = {zr[0], zi[0], zr[1], zi[1]};
-        __builtin_nontemporal_store(o, (gv4f *)D.out + lane);
+        const v4f_s o = {zr[0], zi[0], zr[1], zi[1]};
+        __builtin_nontemporal_store(o, (gv4f_s *)D.out + lane);
     } else {
         // outputs back through LDS so every store writes 1 KiB contiguously
         wave_lds_order();
@@ -231,13 +237,13 @@ __device__ __forceinline__ void batch_step(const BatchDesc &D, float2 *X0, float
 #pragma unroll
         for (int i = 0; i < S; ++i) X[ob + i] = make_float2(zr[i], zi[i]);
         wave_lds_order();
-        gv4f *z4 = (gv4f *)D.out;
+        gv4f_s *z4 = (gv4f_s *)D.out;
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
             const int j = 2 * (lane + 64 * i);
             const int q = PL::OFF + j + j / S;
             const float2 u = X[q], w = X[q + 1];
-            const v4f o = {u.x, u.y, w.x, w.y};
+            const v4f_s o = {u.x, u.y, w.x, w.y};
             __builtin_nontemporal_store(o, z4 + lane + 64 * i);
         }
     }
@@ -335,9 +341,11 @@ __global__ void __launch_bounds__(kBlock) batch_kernel(BatchParams bp)
     }
 }
 
-// The ragged last chunks of the streams (entries [n_full, n_chunks)), one per
+// The streams shorter than a chunk (entries [n_full, n_chunks)), one per
 // wave: a second, small launch, so that the guarded code of a ragged chunk
-// does not raise the register count of the streaming kernel.
+// does not raise the register count of the streaming kernel.  When every
+// stream's ragged end went this way the launch took 7-9 us of the 256-stream
+// workload's 425.
 template <int S>
 __global__ void __launch_bounds__(kBlock) batch_tail_kernel(BatchParams bp)
 {

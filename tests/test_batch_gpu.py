@@ -181,3 +181,32 @@ def test_config4_every_stream_full(torch, mods, config4, tune):
     for s, (n, _, _) in enumerate(wl.specs):
         assert_parity(z[wl.offsets[s]:wl.offsets[s] + n], refs[s], "stream %d %s" % (s, tune))
     b.close()
+
+
+@pytest.mark.parametrize("S", [None, 2, 4, 8])
+def test_packed_streams_at_chunk_edges(torch, S):
+    """Streams packed back to back (every other start 8-byte aligned), lengths one
+    around each chunk size and its multiples, all in one batch: the bits of a
+    plan's own call per stream, and nothing written between them."""
+    from paper_1612_09001_amd import dpd
+    from paper_1612_09001_amd.batch import Batch
+
+    lens = [1, 3, 127, 128, 129, 135, 255, 256, 257, 263, 511, 512, 513, 519, 1025, 1537, 3001]
+    gap = 1
+    total = sum(lens) + gap * len(lens)
+    x = torch.from_numpy(signals.ofdm_16qam(total, config_id=46)).cuda()
+    z = torch.full_like(x, complex(7.0, -7.0))
+    streams, refs, t = [], [], 0
+    for i, n in enumerate(lens):
+        orders, L = signals.odd_orders((5, 7, 9, 11)[i % 4]), 1 + i % 9      # orders to 11 and L = 9: separate launches
+        h = signals.aph_coeffs(orders, orders, L, config_id=46, stream_id=i)
+        streams.append({"in": x[t:t + n], "out": z[t:t + n], "main_orders": orders, "conj_orders": orders, "L": L,
+                        "coeffs": torch.from_numpy(h).cuda()})
+        refs.append((t, n, dpd.Plan(orders, orders, L, h).apply(x[t:t + n].clone())))
+        t += n + gap
+    b = Batch(streams, tune=None if S is None else dict(samples_per_thread=S, grid_mult=2))
+    b.apply()
+    want = torch.full_like(x, complex(7.0, -7.0))
+    for t, n, r in refs:
+        want[t:t + n] = r
+    assert torch.equal(torch.view_as_real(z), torch.view_as_real(want))
