@@ -607,13 +607,14 @@ hipError_t launch_transmit_forward(const dpd_plan *P, const dpd_plan *A, const d
     p.vec = ((uintptr_t)x % 16 == 0 && (uintptr_t)z % 16 == 0 && (uintptr_t)grad_y % 16 == 0 &&
              (rows == 1 || ld % 2 == 0)) ? 1 : 0;
     // whole 512-sample chunks on 16-byte aligned rows: the streaming form,
-    // at most two resident blocks per CU; else one thread per eight
+    // at most three resident blocks per CU (the learning workload's pass: 86.8
+    // us, 92.6 with two); else one thread per eight
     // samples.  One round of resident blocks either way (a second partial
     // round would double the tail).
     const bool stream_form = p.vec && n % 512 == 0;
     const TxKernel kern = (stream_form ? tx_table().stream : tx_table().fwd)[P->map.NI - 1][P->map.L - 1];
     const int occ = tx_occupancy(P->map.NI, P->map.L, stream_form ? 1 : 0, (const void *)kern);
-    const int64_t cap = (int64_t)num_cus() * (stream_form ? std::min(occ, 2) : occ);
+    const int64_t cap = (int64_t)num_cus() * (stream_form ? std::min(occ, 3) : occ);
     const int64_t work = stream_form ? (rows * (n / 512) + 3) / 4 : (rows * p.qpr + kBlock - 1) / kBlock;
     const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(kLossBlocks, cap), work));
     hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), 0, hs, p);
