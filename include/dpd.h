@@ -324,10 +324,10 @@ dpd_status dpd_transmit_loss_grad(dpd_plan *P, const dpd_plan *A, const dpd_plan
  * gradient, dE/dcoeffs of Eq. (1) for the inputs x (as dpd_backward with
  * grad_x NULL computes it; the coefficients of P are not read).  In one
  * kernel when A is memoryless with order 1 in each branch, B has orders
- * {1, 3, 5} and 3 taps, P orders up to 9 and up to 8 taps, n is a multiple of
- * 256 and x, z, grad_y (and grad_z) are 16-byte aligned with an even row
- * stride: dE/dz then stays on chip.  Otherwise the two passes run with dE/dz
- * in grad_z, which must then be given (DPD_EUNSUPPORTED if it is NULL).
+ * {1, 3, 5} and 3 taps, P orders up to 9 and up to 8 taps; otherwise the two
+ * passes run with dE/dz in grad_z.  grad_z may be NULL only for these stages
+ * and when n is a multiple of 256 and x, z, grad_y are 16-byte aligned with an
+ * even row stride (else DPD_EUNSUPPORTED).
  *   x, z, grad_y  device complex64, rows x n at stride ld: the predistorter's
  *                 input and output and dE/dy (dpd_transmit_loss_grad writes z
  *                 and grad_y)
@@ -342,12 +342,11 @@ dpd_status dpd_transmit_backward(const dpd_plan *P, const dpd_plan *A, const dpd
                                  void *grad_coeffs, int64_t rows, int64_t n, int64_t ld, void *ws,
                                  size_t ws_bytes);
 
-/* dpd_learn_step -- one whole coefficient-learning step in one call (three
- * launches): the one-pass forward of dpd_transmit_loss_grad with the
- * coefficients coeffs_dev, the one-pass backward of dpd_transmit_backward,
- * then one launch that finalises the loss and the gradient (FP64, as those
- * calls do) and applies the Adam update of dpd_adam_step to coeffs_dev in
- * place.  Results are bitwise those of the three calls followed by
+/* dpd_learn_step -- one whole coefficient-learning step in one call (two
+ * launches): dpd_transmit_loss_grad with the coefficients coeffs_dev and
+ * dpd_transmit_backward as one pass over x, then one launch that finalises the
+ * loss and the gradient (FP64, as those calls do) and applies the Adam update
+ * of dpd_adam_step to coeffs_dev in place.  Results are bitwise those of the three calls followed by
  * dpd_adam_step.  Arguments as there:
  *   coeffs_dev       K complex64 (device), read, then updated
  *   adam_m, adam_v   2K floats each (device), Adam moments (zero before
@@ -358,8 +357,7 @@ dpd_status dpd_transmit_backward(const dpd_plan *P, const dpd_plan *A, const dpd
  *                    update), or NULL
  *   grad_coeffs      receives dE/dcoeffs (K complex64), or NULL
  *   ws, ws_bytes     at least dpd_learn_step_ws_size(P) bytes
- * Built for the shapes of the one-pass kernels (stages as in
- * dpd_transmit_loss_grad; n a multiple of 256; x, z, grad_y 16-byte aligned
+ * Built for the stages of dpd_transmit_loss_grad ( n a multiple of 256; x, z, grad_y 16-byte aligned
  * with an even row stride): others are DPD_EUNSUPPORTED (use the separate
  * calls).  coeffs_dev, adam_m, adam_v and grad_coeffs must not overlap.
  * Allocates nothing; no host synchronization. */

@@ -36,8 +36,8 @@ UNITS += [("dpd_bwd.hip", [], "dpd_bwd.o")]
 UNITS += [("dpd_batch_inst.hip", ["-DDPD_BATCH_S=%d" % s], "dpd_batch_s%d.o" % s) for s in (2, 4, 8)]
 UNITS += [("dpd_batch.hip", [], "dpd_batch.o")]
 UNITS += [("dpd_train.hip", [], "dpd_train.o")]
-UNITS += [("dpd_transmit.hip", [], "dpd_transmit.o")]
-UNITS += [("dpd_transmit_bwd.hip", [], "dpd_transmit_bwd.o")]
+UNITS += [("dpd_learn_inst.hip", ["-DDPD_NI=%d" % k], "dpd_learn_ni%d.o" % k) for k in range(1, 6)]
+UNITS += [("dpd_learn.hip", [], "dpd_learn.o")]
 UNITS += [("dpd_ls.hip", [], "dpd_ls.o")]
 
 

@@ -1,5 +1,5 @@
 // Pieces of the transmitter-cascade kernels shared by the training
-// translation units (dpd_train.hip, dpd_transmit.hip, dpd_transmit_bwd.hip).
+// translation units (dpd_train.hip, dpd_learn*).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -201,19 +201,6 @@ hipError_t launch_loss_finalize(const float *partials, int nblk, double inv_n, f
 // per-block partials into K complex gradients.
 size_t bwd_ws_bytes(const CoefMap &map);
 
-// Argument checks of the one-pass forward of the learning step (the stages
-// it is built for, sizes, alignment, overlaps; not the workspace).
-dpd_status check_transmit_forward(const dpd_plan *P, const dpd_plan *A, const dpd_plan *B, const void *x,
-                                  const void *z, const void *grad_y, int64_t rows, int64_t n, int64_t ld,
-                                  float scale);
-
-// The one-pass forward of the learning step (dpd_transmit.hip): launches it
-// with the plan's coefficients, or with the K device coefficients coeffs_dev
-// (each block precombines them itself), loss partials into `partials`; *nblk
-// receives the number of partials written.  Arguments already validated.
-hipError_t launch_transmit_forward(const dpd_plan *P, const dpd_plan *A, const dpd_plan *B, hipStream_t hs,
-                                   const void *coeffs_dev, const void *x, void *z, void *grad_y, int64_t rows,
-                                   int64_t n, int64_t ld, float scale, float *partials, int *nblk);
 hipError_t launch_bwd_finalize(const float *partials, int nblk, const CoefMap &map, float2 *grad_coeffs,
                                hipStream_t st);
 

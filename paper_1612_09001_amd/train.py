@@ -2,16 +2,15 @@
 
 ``FusedTrainer.step()`` runs one full-batch gradient step entirely in libdpd
 kernels, on buffers allocated once.  With rows of whole 256-sample chunks it
-is one library call, ``dpd_learn_step`` (three launches):
+is one library call, ``dpd_learn_step`` (two launches):
 
-  z, E, dE/dy                the predistorter (its table precombined from the
-                             device coefficients by every block), the synthetic transmitter
-                             u = IQ(z), y = PA(u) (pa.py) and the loss
-                             E = mean |y/G - x|^2 with its gradient in one
-                             pass (u and y never stored, z written once)
-  dE/dcoeffs                 the adjoint of PA and IQ and the coefficient
-                             gradient of the predistorter in one pass (dE/dz
-                             never stored)
+  z, E, dE/dy, dE/dcoeffs    the predistorter (its table precombined from the
+                             device coefficients by every block), the synthetic
+                             transmitter u = IQ(z), y = PA(u) (pa.py), the loss
+                             E = mean |y/G - x|^2 with its gradient, the
+                             adjoint of PA and IQ and the coefficient gradient
+                             of the predistorter, all in one pass over x (u, y
+                             and dE/dz never stored)
   finalisation + Adam        loss and gradient summed in FP64, Adam applied
                              to the K complex coefficients in place
 
@@ -19,8 +18,8 @@ With ``device_step=True`` the call is ``dpd_learn_step_dev``: Adam's step
 count lives on the device and the call advances it, so ``step()`` can be
 captured into a HIP graph and replayed (every replay takes the next step).
 
-Other row lengths run the same passes as separate calls
-(dpd_transmit_loss_grad, dpd_transmit_backward through a dE/dz buffer,
+Other row lengths run the same kernels as separate calls
+(dpd_transmit_loss_grad, dpd_transmit_backward with a dE/dz buffer,
 dpd_adam_step).  ``one_pass=False`` runs the predistorter as its own launch
 before the fused transmitter (dpd_apply_coeffs, dpd_cascade_loss_grad,
 dpd_cascade_backward, dpd_backward); ``fused_transmitter=False`` runs the
@@ -105,8 +104,8 @@ class FusedTrainer:
                                 1.0 / self.pa.gain, P(self.loss), P(self.gc), P(self.ws), self.ws_bytes)
             return self.loss
         if self.fused_transmitter and self.one_pass:
-            # forward in one pass, backward in another: dE/dz stays on chip where
-            # the shapes allow (else dpd_transmit_backward goes through self.gz)
+            # forward in one pass, backward in another (which takes a dE/dz buffer
+            # at these row lengths)
             _dpd.dpd_transmit_loss_grad(self.plan.handle, iq, pa, st, P(self.coeffs), P(self.x), P(self.z), R, N, ld,
                                         1.0 / self.pa.gain, P(self.loss), P(self.gy), P(self.ws), self.ws_bytes)
             gz = 0 if N % 256 == 0 else P(self.gz)
