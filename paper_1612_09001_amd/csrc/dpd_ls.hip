@@ -52,7 +52,10 @@ constexpr int kLsSlabMin = 1024;
 constexpr int kLsMaxDp = 192;       // padded real features (2K+2 rounded up to 16): K <= 95
 constexpr int kLsMaxNt = kLsMaxDp / 16;
 constexpr int kLsWaves = kBlock / 64;
-constexpr int kLsGroup = 64;        // slabs per first-level FP64 sum
+// Slabs per first-level FP64 sum: fewer on small inputs, so that the sums fill the
+// chip; with many slabs the pass is bound by reading the partials (2048 at K =
+// 81: 138 MB in 21 us).
+constexpr int64_t ls_group(int64_t nslabs) { return nslabs <= 256 ? 16 : 64; }
 
 // Entries of a basis row (roles): Re psi_j, Im psi_j, -Im psi_j for each
 // power level j, the constant, a zero and the target (Re, Im).
@@ -132,7 +135,7 @@ __device__ __forceinline__ void ls_gram_step(v4f_ls *acc, const bf16x8_ls *a, co
      ...);
 }
 
-// Pair groups of the Gram kernel for NT column tiles: one (every wave holds
+// Pair groups of a Gram block for NT column tiles: one (every wave holds
 // all NT (NT + 1) / 2 tile accumulators) while they fit in 128 registers,
 // else two (two waves per group).
 constexpr int ls_pair_groups(int nt) { return nt * (nt + 1) / 2 * 4 <= 128 ? 1 : 2; }
@@ -201,7 +204,8 @@ __device__ __forceinline__ void ls_gram_tile(v4f_ls *acc, const uint32_t *Xf, co
 // the other of two LDS buffers (one barrier per tile): wave w the power levels
 // [w lpw, (w + 1) lpw), the last wave also the constant and target words.  At
 // the end the GK partial tiles of each pair are summed through LDS (fixed
-// order) and written out.  The pair list is a compile-time
+// order; as many pairs per barrier as the buffers hold) and written out.  The
+// pair list is a compile-time
 // constant: the matrix loop has no conditionals (a guarded accumulation
 // becomes a branch whose merge copies every accumulator) and every wave runs
 // the same code.
@@ -336,27 +340,33 @@ __device__ __forceinline__ void ls_gram_wave(const LsParams &p, uint32_t (*X)[kL
     if (m0 < nl)
         ls_gram_tile<NT, Q0, PW, GK, true>(acc, &X[cur * kLsRows][0], addr, kw, g2, nl - m0, []() {});
     // Sum the GK partial tiles of each pair: the four waves put their
-    // accumulators (pair u of their group) in LDS, then the waves of a group
+    // accumulators of PB pairs (of their group) in LDS, then the waves of a group
     // each add up 4 / GK of the register slots, in wave order.  Tile element
     // (4 (l / 16) + v, l % 16) is register v of lane l.
-    float *buf = reinterpret_cast<float *>(&X[0][0]);   // 4 x 256 floats (kLsRows x kLsBStride >= 1024 words)
+    float *buf = reinterpret_cast<float *>(&X[0][0]);
+    constexpr int PB = 2 * kLsRows * kLsBStride / (kLsWaves * 256);   // pairs the two tile buffers hold
     float *out = p.partials + (slab * NP + Q0) * 256;
-    for (int u = 0; u < PP; ++u) {
-        __syncthreads();   // the matrix reads of the last tile / the previous pair's sums are done
-        if (u < PW) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) buf[wv * 256 + lane * 4 + v] = acc[u][v];
-        }
+    for (int u0 = 0; u0 < PP; u0 += PB) {
+        __syncthreads();   // the matrix reads of the last tile / the previous pairs' sums are done
+#pragma unroll
+        for (int u = u0; u < u0 + PB; ++u)
+            if (u < PW)
+                *reinterpret_cast<v4f_ls *>(buf + ((u - u0) * kLsWaves + wv) * 256 + lane * 4) = acc[u];
         __syncthreads();
-        if (u < PW) {
-            constexpr int VPW = 4 / GK;   // register slots per wave
 #pragma unroll
-            for (int vv = 0; vv < VPW; ++vv) {
-                const int v = kw * VPW + vv;
-                float t = 0.f;
+        for (int u = u0; u < u0 + PB; ++u) {
+            if (u < PW) {
+                constexpr int VPW = 4 / GK;   // register slots per wave
 #pragma unroll
-                for (int w = 0; w < GK; ++w) t += buf[(G * GK + w) * 256 + lane * 4 + v];
-                out[u * 256 + (4 * (lane >> 4) + v) * 16 + (lane & 15)] = t;
+                for (int vv = 0; vv < VPW; ++vv) {
+                    const int v = kw * VPW + vv;
+                    float t = 0.f;
+#pragma unroll
+                    for (int w = 0; w < GK; ++w)
+                        t += buf[((u - u0) * kLsWaves + G * GK + w) * 256 + lane * 4 + v];
+                    out[u * 256 + (4 * (lane >> 4) + v) * 16 + (lane & 15)] = t;
+                }
             }
         }
     }
@@ -368,7 +378,7 @@ __device__ __forceinline__ void ls_gram_wave(const LsParams &p, uint32_t (*X)[kL
 template <int NT>
 __global__ void __launch_bounds__(kBlock) ls_gram_kernel(LsParams p)
 {
-    static_assert(kLsRows * kLsBStride >= kLsWaves * 256, "LDS tile too small for the final sums");
+    static_assert(2 * kLsRows * kLsBStride >= kLsWaves * 256, "LDS tiles too small for the final sums");
     __shared__ __align__(16) uint32_t X[2 * kLsRows][kLsBStride];   // two tile buffers
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t slab = blockIdx.x;
@@ -387,24 +397,203 @@ __global__ void __launch_bounds__(kBlock) ls_gram_kernel(LsParams p)
     }
 }
 
+// The same sums with a slab spread over GK blocks, for inputs of few slabs, where
+// one block per slab leaves each SIMD a single wave that waits on every build,
+// LDS read and barrier in turn.  Block kw of a slab takes the 8-sample steps kw,
+// kw + GK, ... that wave kw of ls_gram_kernel takes, in the same order, its four
+// waves a quarter of the tile pairs each; its GK-th of the samples (and the L -
+// 1 before each step) is all of the basis it builds.  The GK partial tiles of a
+// pair are added up in FP32 by ls_reduce1_kernel, in the order of the waves, so
+// every bit is as from one block.
+// A tile is eight steps: LDS row i (8 + H) + r holds sample r - H of step i.
+template <int NT, int G>
+__device__ __forceinline__ void ls_sub_wave(const LsParams &p, uint32_t *X, int rows, int kw, int64_t part,
+                                            int64_t s0, int64_t send, const float2 *yr, const float2 *tr)
+{
+    constexpr int NP = NT * (NT + 1) / 2;
+    constexpr int GK = kLsWaves / ls_pair_groups(NT);
+    constexpr int PP = (NP + kLsWaves - 1) / kLsWaves;
+    constexpr int Q0 = G * PP < NP ? G * PP : NP;
+    constexpr int PW = NP - Q0 < PP ? NP - Q0 : PP;   // pairs of this wave (none past the list)
+    constexpr int RI = 3;                             // rows a lane builds at most: 8 (8 + 15) / 64
+    const int lane = threadIdx.x & 63;
+    const int H = p.L - 1;
+    v4f_ls acc[PW > 0 ? PW : 1];
+#pragma unroll
+    for (int u = 0; u < (PW > 0 ? PW : 1); ++u) acc[u] = v4f_ls{0.f, 0.f, 0.f, 0.f};
+    const int g2 = 2 * (lane >> 4), c = lane & 15;
+    int addr[NT];
+#pragma unroll
+    for (int b = 0; b < NT; ++b) addr[b] = g2 * kLsBStride + p.off[16 * b + c];
+    const int step = (8 + H) * kLsBStride;
+
+    const bool last = G == kLsWaves - 1;
+    const int lpw = (p.NI + kLsWaves - 1) / kLsWaves;
+    const int j0 = G * lpw, nj = std::min(p.NI - j0, lpw);
+    constexpr int UJ = (kMaxNI + kLsWaves - 1) / kLsWaves;
+    int sre[UJ], sim[UJ], sng[UJ];
+#pragma unroll
+    for (int u = 0; u < UJ; ++u) {
+        const int j = (j0 + u) & (kMaxNI - 1);
+        sre[u] = p.slot[j];
+        sim[u] = p.slot[kLsRIm + j];
+        sng[u] = p.slot[kLsRNegIm + j];
+    }
+    const float2 *ys = yr + s0, *ts = tr + s0;
+    const int nl = (int)(send - s0);
+    const int lo = s0 >= kMaxL ? -kMaxL : (int)-s0;
+    // sample of each row this lane builds, relative to the tile's first
+    int so[RI];
+#pragma unroll
+    for (int e = 0; e < RI; ++e) {
+        const int row = lane + 64 * e, i = row / (8 + H);
+        so[e] = 8 * (GK * i + kw) + (row - i * (8 + H)) - H;
+    }
+    float2 y[RI], t[RI];
+    const auto fetch = [&](int m0) {
+#pragma unroll
+        for (int e = 0; e < RI; ++e) {
+            const int q = m0 + so[e];
+            const bool ok = lane + 64 * e < rows && q >= lo && q < nl;
+            y[e] = ok ? ys[q] : make_float2(0.f, 0.f);
+            if (last) t[e] = ok && q >= 0 ? ts[q] : make_float2(0.f, 0.f);
+        }
+    };
+    const auto put = [](uint32_t *x, int e, uint32_t w) { *reinterpret_cast<uint2 *>(x + 2 * e) = make_uint2(w, w); };
+    const auto build = [&](int m0, uint32_t *B) {
+#pragma unroll
+        for (int e = 0; e < RI; ++e) {
+            if (lane + 64 * e >= rows) continue;
+            uint32_t *x = B + (lane + 64 * e) * kLsBStride;
+            const float vx = p.y_scale * y[e].x, vy = p.y_scale * y[e].y;
+            const float s2 = __builtin_fmaf(vx, vx, vy * vy);
+            float pw = 1.f;
+            for (int f = 0; f < j0; ++f) pw *= s2;
+#pragma unroll
+            for (int u = 0; u < UJ; ++u) {
+                if (u < nj) {
+                    uint32_t wa, wb;
+                    ls_pack2(pw * vx, pw * vy, wa, wb);
+                    put(x, sre[u], wa);
+                    put(x, sim[u], wb);
+                    put(x, sng[u], wb ^ 0x80008000u);
+                    pw *= s2;
+                }
+            }
+            if (last) {
+                uint32_t ta, tb;
+                ls_pack2(t[e].x, t[e].y, ta, tb);
+                put(x, p.slot[kLsROne], m0 + so[e] < nl ? ls_pack(1.f) : 0u);
+                put(x, p.slot[kLsRZero], 0u);
+                put(x, p.slot[kLsRT], ta);
+                put(x, p.slot[kLsRT + 1], tb);
+            }
+        }
+    };
+    constexpr int SPAN = kLsTile * GK;   // samples of the slab a tile spans
+    fetch(0);
+    build(0, X);
+    __syncthreads();
+    int cur = 0;
+    for (int m0 = 0; m0 < nl; m0 += SPAN, cur ^= 1) {
+        const uint32_t *B = X + cur * rows * kLsBStride;
+        const int mn = m0 + SPAN;
+        if (mn < nl) {
+            fetch(mn);
+            build(mn, X + (cur ^ 1) * rows * kLsBStride);
+        }
+        if constexpr (PW > 0) {
+            // the steps past the slab's end contribute nothing: their row-side
+            // operands are zeroed sample by sample
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int m = m0 + 8 * (GK * i + kw) + g2;
+                const bool ok0 = m < nl, ok1 = m + 1 < nl;
+                bf16x8_ls a[NT], cb[NT];
+#pragma unroll
+                for (int b = 0; b < NT; ++b) {
+                    const uint32_t *q = B + addr[b] + i * step;
+                    const uint2 p0 = *reinterpret_cast<const uint2 *>(q);
+                    const uint2 p1 = *reinterpret_cast<const uint2 *>(q + kLsBStride);
+                    const u32x4_ls av = u32x4_ls{ok0 ? p0.x : 0u, ok0 ? p0.y : 0u, ok1 ? p1.x : 0u, ok1 ? p1.y : 0u};
+                    const u32x4_ls bv = {__builtin_amdgcn_perm(p0.x, p0.x, 0x01000100u),
+                                         __builtin_amdgcn_perm(p0.y, p0.y, 0x03020302u),
+                                         __builtin_amdgcn_perm(p1.x, p1.x, 0x01000100u),
+                                         __builtin_amdgcn_perm(p1.y, p1.y, 0x03020302u)};
+                    a[b] = __builtin_bit_cast(bf16x8_ls, av);
+                    cb[b] = __builtin_bit_cast(bf16x8_ls, bv);
+                }
+                ls_gram_step<NT, Q0>(acc, a, cb, std::make_integer_sequence<int, PW>{});
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        __syncthreads();
+    }
+    float *out = p.partials + (part * NP + Q0) * 256;
+#pragma unroll
+    for (int u = 0; u < PW; ++u)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) out[u * 256 + (4 * (lane >> 4) + v) * 16 + (lane & 15)] = acc[u][v];
+}
+
+template <int NT>
+__global__ void __launch_bounds__(kBlock) ls_sub_kernel(LsParams p)
+{
+    extern __shared__ __align__(16) uint32_t ls_sub_lds[];   // two buffers of 8 (L + 7) rows
+    constexpr int GK = kLsWaves / ls_pair_groups(NT);
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t part = blockIdx.x, slab = part / GK;
+    const int kw = (int)(part - slab * GK);
+    const int64_t row = slab / p.slabs_per_row;
+    const int64_t s0 = (slab - row * p.slabs_per_row) * p.slab;
+    const float2 *yr = p.y + row * p.ld;
+    const float2 *tr = p.t + row * p.ld;
+    const int64_t send = std::min<int64_t>(s0 + p.slab, p.n);
+    const int rows = 8 * (p.L + 7);
+    if (wv == 0)
+        ls_sub_wave<NT, 0>(p, ls_sub_lds, rows, kw, part, s0, send, yr, tr);
+    else if (wv == 1)
+        ls_sub_wave<NT, 1>(p, ls_sub_lds, rows, kw, part, s0, send, yr, tr);
+    else if (wv == 2)
+        ls_sub_wave<NT, 2>(p, ls_sub_lds, rows, kw, part, s0, send, yr, tr);
+    else
+        ls_sub_wave<NT, 3>(p, ls_sub_lds, rows, kw, part, s0, send, yr, tr);
+}
+
+// First level: the slabs of a group summed in FP64 in slab order, each slab's
+// value the FP32 sum of its SUB partial tiles in order.
+template <int SUB>
 __global__ void __launch_bounds__(kBlock) ls_reduce1_kernel(const float *__restrict__ partials, int64_t nslabs,
-                                                            int64_t E, double *__restrict__ r1)
+                                                            int64_t group, int64_t E, double *__restrict__ r1)
 {
     const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (e >= E) return;
     const int64_t g = blockIdx.y;
-    const int64_t s1 = std::min<int64_t>(nslabs, (g + 1) * kLsGroup);
-    // eight loads in flight at a time, the sum in slab order
+    const int64_t s1 = std::min<int64_t>(nslabs, (g + 1) * group);
+    // eight loads in flight at a time
+    constexpr int U = 8 / SUB;
     double t = 0.0;
-    int64_t sl = g * kLsGroup;
-    for (; sl + 8 <= s1; sl += 8) {
-        float v[8];
+    int64_t sl = g * group;
+    for (; sl + U <= s1; sl += U) {
+        float v[U][SUB];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = partials[(sl + i) * E + e];
+        for (int i = 0; i < U; ++i)
 #pragma unroll
-        for (int i = 0; i < 8; ++i) t += (double)v[i];
+            for (int q = 0; q < SUB; ++q) v[i][q] = partials[((sl + i) * SUB + q) * E + e];
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            float f = v[i][0];
+#pragma unroll
+            for (int q = 1; q < SUB; ++q) f += v[i][q];
+            t += (double)f;
+        }
     }
-    for (; sl < s1; ++sl) t += (double)partials[sl * E + e];
+    for (; sl < s1; ++sl) {
+        float f = partials[sl * SUB * E + e];
+#pragma unroll
+        for (int q = 1; q < SUB; ++q) f += partials[(sl * SUB + q) * E + e];
+        t += (double)f;
+    }
     r1[g * E + e] = t;
 }
 
@@ -577,75 +766,78 @@ __device__ __forceinline__ double ls_rsqrt(double x)
 //
 // The columns form a serial chain -- pivot, 1 / sqrt, scale, update of the next
 // column -- which is what bounds the solve (the arithmetic of K = 81 is 2 us of
-// one CU).  So panels of kLsPanel columns are factored by wave 0 alone in
-// registers, lane = row, values of other rows by readlane: no LDS round trip
-// and no barrier inside a panel.  The other seven waves meanwhile subtract
-// the panel before from the columns past this one (2 x 2 entries per thread
-// over the triangle); then all waves bring the next panel's columns up to
-// date.  Two barriers per panel instead of one per column.
-// Measured on MI355X: K = 33 in 18 us (load 2, panels 13.5, substitution 2.5)
-// and K = 81 in 51 us; a left-looking column at a time took 30 us (four waves,
-// factor in LDS) and 348 us (one wave, factor in memory).  A panel column takes
-// about 600 cycles of one wave's issue (some 55 FP64 and readlane instructions).
+// one CU).  So panels of kLsPanel columns are factored in registers, lane = row,
+// values of the pivot rows by readlane: no LDS round trip and no barrier inside
+// a panel.  One wave takes the pivot rows and 56 below them; where there are
+// more, further waves take the pivot rows again and the next 56, so a panel's
+// time does not grow with K.  The waves left meanwhile subtract the panel before
+// from the columns past this one (2 x 2 entries per thread over the triangle);
+// then all waves bring the next panel's columns up to date.  Two or three
+// barriers per panel instead of one per column.
+// Measured on MI355X: K = 33 in 19 us and K = 81 in 45 us; a left-looking
+// column at a time took 30 us (four waves, factor in LDS) and 348 us (one wave,
+// factor in memory), one wave per panel for all rows 50 us at K = 81.  A panel
+// column takes about 600 cycles of one wave's issue (some 55 FP64 and readlane
+// instructions).
 // info = 0, or j + 1 when the pivot of column j is not positive (h is NaN).
 constexpr int kLsPanel = 8;
+constexpr int kLsPanelRows = 64 - kLsPanel;   // rows below the pivots per wave
 constexpr int kLsPanelWaves = 8;
 constexpr int kLsPanelMaxK = 139;
 constexpr size_t ls_panel_lds(int K) { return (size_t)(K + 1) * (K + 2) / 2 * sizeof(double2); }
 static_assert(ls_panel_lds(kLsPanelMaxK) + 2048 <= 160 * 1024, "the triangle does not fit LDS");
 
-// Columns j0 .. j0 + 7 by one wave (rows j0 + lane + 64 s); returns 0 or the
-// 1-based column of a pivot that is not positive.
-template <int S>
-__device__ __forceinline__ int ls_panel_factor(double2 *F, double *invd, int K, int j0, int lane)
+// Columns j0 .. j0 + 7 by wave w of the panel: lanes 0..7 hold the pivot rows j0
+// .. j0 + 7 (every wave factors them), the other lanes 56 rows below them.
+__device__ __forceinline__ int ls_panel_row(int j0, int w, int lane)
 {
-    const int R = K + 1;
-    double id = 0.0;
-    double2 a[S][kLsPanel];
+    return lane < kLsPanel ? j0 + lane : j0 + lane + w * kLsPanelRows;
+}
+
+__device__ __forceinline__ void ls_panel_load(const double2 *F, int K, int j0, int w, int lane,
+                                              double2 (&a)[kLsPanel])
+{
+    const int R = K + 1, r = ls_panel_row(j0, w, lane);
 #pragma unroll
     for (int q = 0; q < kLsPanel; ++q) {
         const int j = j0 + q, base = j * R - j * (j + 1) / 2;
-#pragma unroll
-        for (int s = 0; s < S; ++s) {
-            const int r = j0 + lane + 64 * s;
-            a[s][q] = j < K && r >= j && r < R ? F[base + r] : make_double2(0.0, 0.0);
-        }
+        a[q] = j < K && r >= j && r < R ? F[base + r] : make_double2(0.0, 0.0);
     }
+}
+
+// Factors the loaded columns and stores the rows that this wave answers for.
+// Returns 0 or the 1-based column of a pivot that is not positive.
+__device__ __forceinline__ int ls_panel_factor(double2 *F, double *invd, int K, int j0, int w, int lane,
+                                               double2 (&a)[kLsPanel])
+{
+    const int R = K + 1, r = ls_panel_row(j0, w, lane);
+    const bool own = r < R && (w == 0 || lane >= kLsPanel);
+    double id = 0.0;
     // Straight-line code: columns past K are zeros and come to NaN, which goes
     // nowhere, and a failed pivot only notes its column.
     int fail = 0;
 #pragma unroll
     for (int q = 0; q < kLsPanel; ++q) {
-        const double piv = ls_bcast(a[0][q].x, q);
+        const double piv = ls_bcast(a[q].x, q);
         fail = fail == 0 && j0 + q < K && !(piv > 0.0) ? j0 + q + 1 : fail;
         const double inv = ls_rsqrt(piv);
         if (lane == q) id = inv;
-#pragma unroll
-        for (int s = 0; s < S; ++s) {
-            a[s][q].x *= inv;
-            a[s][q].y *= inv;
-        }
+        a[q].x *= inv;
+        a[q].y *= inv;
 #pragma unroll
         for (int c = q + 1; c < kLsPanel; ++c) {
-            const double cx = ls_bcast(a[0][q].x, c), cy = ls_bcast(a[0][q].y, c);   // L[j0 + c][j0 + q]
-#pragma unroll
-            for (int s = 0; s < S; ++s) {
-                a[s][c].x = fma(-a[s][q].x, cx, a[s][c].x);
-                a[s][c].x = fma(-a[s][q].y, cy, a[s][c].x);
-                a[s][c].y = fma(-a[s][q].y, cx, a[s][c].y);
-                a[s][c].y = fma(a[s][q].x, cy, a[s][c].y);
-            }
+            const double cx = ls_bcast(a[q].x, c), cy = ls_bcast(a[q].y, c);   // L[j0 + c][j0 + q]
+            a[c].x = fma(-a[q].x, cx, a[c].x);
+            a[c].x = fma(-a[q].y, cy, a[c].x);
+            a[c].y = fma(-a[q].y, cx, a[c].y);
+            a[c].y = fma(a[q].x, cy, a[c].y);
         }
     }
-    if (lane < kLsPanel && j0 + lane < K) invd[j0 + lane] = id;
+    if (w == 0 && lane < kLsPanel && j0 + lane < K) invd[j0 + lane] = id;
 #pragma unroll
     for (int q = 0; q < kLsPanel; ++q) {
         const int j = j0 + q, base = j * R - j * (j + 1) / 2;
-#pragma unroll
-        for (int s = 0; s < S; ++s) {
-            const int r = j0 + lane + 64 * s;
-            if (j < K && r >= j && r < R) F[base + r] = a[s][q];
-        }
+        if (own && j < K && r >= j) F[base + r] = a[q];
     }
     return fail;
 }
@@ -683,7 +875,7 @@ __global__ void __launch_bounds__(64 * kLsPanelWaves) ls_solve_panel_kernel(cons
     const double delta = ridge * ls_wave_sum(tr) / K;
     if (tid == 0) bad = 0;
     // the lower triangle: wave w the rows w, w + 8, ..., lane = column, U rows in flight
-    constexpr int U = 8 / S + 1;
+    constexpr int U = S == 1 ? 9 : S == 2 ? 11 : 6;
     for (int r0 = w; r0 < R; r0 += U * kLsPanelWaves) {
         double2 v[U][S];
 #pragma unroll
@@ -708,50 +900,50 @@ __global__ void __launch_bounds__(64 * kLsPanelWaves) ls_solve_panel_kernel(cons
     __syncthreads();
 
     for (int j0 = 0; j0 < K; j0 += kLsPanel) {
-        if (w == 0) {
+        // the waves that the panel's rows below its pivots take
+        const int pw = (max(R - j0 - kLsPanel, 1) + kLsPanelRows - 1) / kLsPanelRows;
+        double2 a[kLsPanel];
+        if (w < pw) ls_panel_load(F, K, j0, w, lane, a);
+        if (pw > 1) __syncthreads();   // every wave has the pivot rows before wave 0 stores them
+        if (w < pw) {
             __builtin_amdgcn_s_setprio(3);   // the chain before the other wave of its SIMD
-            int fail;
-            if (S == 3 && R - j0 > 128)
-                fail = ls_panel_factor<S>(F, invd, K, j0, lane);
-            else if (S >= 2 && R - j0 > 64)
-                fail = ls_panel_factor<S >= 2 ? 2 : 1>(F, invd, K, j0, lane);
-            else
-                fail = ls_panel_factor<1>(F, invd, K, j0, lane);
-            if (lane == 0 && fail != 0) bad = fail;
+            const int fail = ls_panel_factor(F, invd, K, j0, w, lane, a);
+            if (w == 0 && lane == 0 && fail != 0) bad = fail;
             __builtin_amdgcn_s_setprio(0);
         } else if (j0 > 0) {
-            // the panel before this one out of the columns past this one
+            // the panel before this one out of the columns past this one: rows cs ..
+            // R - 1 in two halves, a thread taking i >= j of the first half and
+            // the entries (i, j), (i + m, j + m), (i + m, j) and (j + m, i), so
+            // that the lanes read consecutive rows
             const int cs = j0 + kLsPanel, jp = j0 - kLsPanel;
-            const int m = (R - cs + 1) / 2;   // pairs of rows / columns from cs on
-            for (int e = tid - 64; e < m * (m + 1) / 2 && cs < K; e += T - 64) {
-                int ti = (int)((sqrtf(8.f * (float)e + 1.f) - 1.f) * 0.5f);
-                ti += (ti + 1) * (ti + 2) / 2 <= e ? 1 : 0;
-                ti -= ti * (ti + 1) / 2 > e ? 1 : 0;
-                const int tj = e - ti * (ti + 1) / 2;
-                const int r0 = cs + 2 * ti, r1 = r0 + 1 < R ? r0 + 1 : R - 1;
-                const int c0 = cs + 2 * tj, c1 = c0 + 1 < R ? c0 + 1 : R - 1;
-                double2 s00 = make_double2(0.0, 0.0), s01 = s00, s10 = s00, s11 = s00;
+            const int m = (R - cs + 1) / 2;
+            for (int e = tid - 64 * pw; e < m * (m + 1) / 2 && cs < K; e += T - 64 * pw) {
+                int i = (int)((sqrtf(8.f * (float)e + 1.f) - 1.f) * 0.5f);
+                i += (i + 1) * (i + 2) / 2 <= e ? 1 : 0;
+                i -= i * (i + 1) / 2 > e ? 1 : 0;
+                const int j = e - i * (i + 1) / 2;
+                const int i0 = cs + i, j0r = cs + j, i1 = i0 + m, j1 = j0r + m;
+                const int i1c = i1 < R ? i1 : R - 1, j1c = j1 < R ? j1 : R - 1;
+                double2 sij = make_double2(0.0, 0.0), smm = sij, smj = sij, sji = sij;
 #pragma unroll
                 for (int q = 0; q < kLsPanel; ++q) {
                     const double2 *P = F + base(jp + q);
-                    const double2 a0 = P[r0], a1 = P[r1], x0 = P[c0], x1 = P[c1];
-                    ls_sub(s00, a0, x0);
-                    ls_sub(s01, a0, x1);
-                    ls_sub(s10, a1, x0);
-                    ls_sub(s11, a1, x1);
+                    const double2 ai = P[i0], am = P[i1c], aj = P[j0r], an = P[j1c];
+                    ls_sub(sij, ai, aj);
+                    ls_sub(smm, am, an);
+                    ls_sub(smj, am, aj);
+                    ls_sub(sji, an, ai);
                 }
-                const auto add = [&](int r, int c, double2 s) {
-                    double2 &f = F[base(c) + r];
-                    f = make_double2(f.x + s.x, f.y + s.y);
+                const auto add = [&](int r, int c, double2 v) {
+                    if (r < R && c < K) {
+                        double2 &f = F[base(c) + r];
+                        f = make_double2(f.x + v.x, f.y + v.y);
+                    }
                 };
-                if (c0 < K) {
-                    add(r0, c0, s00);
-                    if (r0 + 1 < R) add(r0 + 1, c0, s10);
-                }
-                if (c0 + 1 < K) {
-                    if (r0 >= c0 + 1) add(r0, c0 + 1, s01);
-                    if (r0 + 1 < R) add(r0 + 1, c0 + 1, s11);
-                }
+                add(i0, j0r, sij);
+                add(i1, j1, smm);
+                add(i1, j0r, smj);
+                if (i != j) add(j1, i0, sji);
             }
         }
         __syncthreads();
@@ -976,15 +1168,24 @@ __global__ void __launch_bounds__(kBlock) ls_zero_kernel(double2 *__restrict__ p
 typedef void (*LsGramKernel)(LsParams);
 
 template <int... P>
-static const LsGramKernel *ls_gram_table_of(std::integer_sequence<int, P...>)
+static LsGramKernel ls_gram_of(int nt, bool sub, std::integer_sequence<int, P...>)
 {
-    static const LsGramKernel t[] = {&ls_gram_kernel<P + 1>...};
-    return t;
+    static const LsGramKernel whole[] = {&ls_gram_kernel<P + 1>...};
+    static const LsGramKernel part[] = {&ls_sub_kernel<P + 1>...};
+    return sub ? part[nt - 1] : whole[nt - 1];
 }
 
-static const LsGramKernel *ls_gram_table()
+// Blocks per slab.  One block's four waves load each operand block once for all
+// their pairs; spread over GK blocks, the four waves of each load them again for
+// a quarter of the pairs, so that pays only while there are too few slabs to give
+// the SIMDs work: up to half a slab per CU with GK = 4 (K = 33, 8 and 128 slabs:
+// 23.1 -> 15.4 and 26.4 -> 21.7 us a call; 256: 27.4 -> 29.1) and one with GK =
+// 2 (K = 81, 8 and 256 slabs: 47 -> 33 and 57 -> 53 us; 512: worse).
+int num_cus();
+static int ls_sub(int nt, int64_t nslabs)
 {
-    return ls_gram_table_of(std::make_integer_sequence<int, kLsMaxNt>{});
+    const int gk = kLsWaves / ls_pair_groups(nt);
+    return nslabs * gk <= 2 * num_cus() ? gk : 1;
 }
 
 struct LsShape {
@@ -1008,7 +1209,6 @@ struct LsWs {
 
 // Samples per block: 8192 on large inputs; smaller (down to 1024) when that
 // leaves fewer than ~6 blocks per CU, so small fits still fill the chip.
-int num_cus();
 static int64_t ls_slab(int64_t rows, int64_t n)
 {
     const int64_t want = (int64_t)num_cus() * 6;
@@ -1022,11 +1222,11 @@ static LsWs ls_ws(const LsShape &s, int64_t rows, int64_t n)
     const int64_t slab = ls_slab(rows, n);
     const int64_t spr = (n + slab - 1) / slab;
     const int64_t nslabs = std::max<int64_t>(rows * spr, 1);
-    const int64_t groups = (nslabs + kLsGroup - 1) / kLsGroup;
+    const int64_t group = ls_group(nslabs), groups = (nslabs + group - 1) / group;
     const int64_t E = (int64_t)s.npairs * 256;
     auto up = [](size_t v) { return (v + 255) & ~(size_t)255; };
     LsWs w;
-    w.partials = up((size_t)(nslabs * E) * sizeof(float));
+    w.partials = up((size_t)(nslabs * ls_sub(s.nt, nslabs) * E) * sizeof(float));
     w.r1 = up((size_t)(groups * E) * sizeof(double));
     w.total = w.partials + w.r1;
     return w;
@@ -1189,13 +1389,17 @@ DPD_EXPORT dpd_status dpd_ls_normal(dpd_plan *plan, void *stream, const void *y,
     std::copy(plan->ls_slot, plan->ls_slot + kLsRoles, p.slot);
     ls_offsets(map, s, p.slot, p.off);
     if (nslabs >= ((int64_t)1 << 31)) return DPD_EUNSUPPORTED;
-    hipLaunchKernelGGL(ls_gram_table()[s.nt - 1], dim3((uint32_t)nslabs), dim3(kBlock), 0, st, p);
+    const int sub = ls_sub(s.nt, nslabs);
+    const size_t lds = sub > 1 ? (size_t)2 * 8 * (map.L + 7) * kLsBStride * sizeof(uint32_t) : 0;
+    hipLaunchKernelGGL(ls_gram_of(s.nt, sub > 1, std::make_integer_sequence<int, kLsMaxNt>{}),
+                       dim3((uint32_t)(nslabs * sub)), dim3(kBlock), lds, st, p);
     e = hipGetLastError();
-    const int64_t groups = (nslabs + kLsGroup - 1) / kLsGroup;
+    const int64_t group = ls_group(nslabs), groups = (nslabs + group - 1) / group;
     const uint32_t eb = (uint32_t)((E + kBlock - 1) / kBlock);
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(ls_reduce1_kernel, dim3(eb, (uint32_t)groups), dim3(kBlock), 0, st,
-                           (const float *)partials, nslabs, E, r1);
+        const auto reduce = sub == 4 ? &ls_reduce1_kernel<4> : sub == 2 ? &ls_reduce1_kernel<2> : &ls_reduce1_kernel<1>;
+        hipLaunchKernelGGL(reduce, dim3(eb, (uint32_t)groups), dim3(kBlock), 0, st, (const float *)partials, nslabs,
+                           group, E, r1);
         e = hipGetLastError();
     }
     if (e == hipSuccess) {

@@ -411,3 +411,29 @@ def test_graph_replay(torch, dpd):
         torch.cuda.synchronize()
         assert torch.equal(A, ref_a) and torch.equal(h, ref_h), "replay %d" % r
         assert int(info.item()) == 0
+
+
+@pytest.mark.parametrize("mo,co,L", [([1], [], 1), ([1, 3, 5], [1, 3], 2), ([1, 3, 5, 7], [1, 3, 5, 7], 4),
+                                     ([1, 3, 5], [1, 3], 16), ([1, 3, 5, 7, 9], [1, 3, 5, 7, 9], 9)])
+def test_normal_equations_of_few_slabs(torch, dpd, orc, mo, co, L):
+    """Inputs of few slabs spread each slab's steps over several blocks: lengths
+    around a step, a tile and a slab against the oracle, and bit for bit the sums
+    of the same samples as rows of a larger input of many slabs."""
+    h = signals.aph_coeffs(mo, co, L, config_id=96)
+    plan = dpd.Plan(mo, co, L, h)
+    for n in (1, 7, 8, 9, 17, 127, 255, 256, 257, 1023, 1024, 1025, 3001):
+        y, t = signals.ofdm_16qam(n, config_id=96), signals.ofdm_16qam(n, config_id=97)
+        A, b = plan.ls_normal(torch.from_numpy(y).cuda(), torch.from_numpy(t).cuda())
+        Ar, br = orc.ls_normal(y, mo, co, L, t)
+        ea, eb, _, _ = ls_errors(A.cpu().numpy(), b.cpu().numpy(), Ar, br, np.sum(np.abs(t) ** 2))
+        assert ea <= LS_REL_MAX and eb <= LS_REL_MAX, (n, ea, eb)
+        # one row of data among rows of zeros (but for the constant column: no
+        # target and no basis there), more slabs than are spread
+        rows = 1 + 2 * torch.cuda.get_device_properties(0).multi_processor_count
+        Y = torch.zeros(rows, n, dtype=torch.complex64, device="cuda")
+        T = torch.zeros_like(Y)
+        Y[1], T[1] = torch.from_numpy(y).cuda(), torch.from_numpy(t).cuda()
+        B, d = plan.ls_normal(Y, T)
+        K = plan.K
+        assert torch.equal(torch.view_as_real(A[:K - 1]), torch.view_as_real(B[:K - 1])), n
+        assert torch.equal(torch.view_as_real(b), torch.view_as_real(d)), n
