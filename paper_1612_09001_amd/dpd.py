@@ -393,8 +393,11 @@ def _torch():
 
 
 def current_stream() -> int:
+    """torch's current stream on the current device.  Read as the raw handle:
+    torch.cuda.current_stream() builds a Stream object, 2.9 us of a call whose
+    launch takes 3.5 (17 us on autograd's thread), against 0.3 us."""
     torch = _torch()
-    return int(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _dev_c64(t, name):
@@ -498,11 +501,15 @@ class Plan:
         torch = _torch()
         x = _dev_c64(x, "x")
         gz = _dev_c64(grad_z, "grad_z")
-        x2 = x.reshape(1, -1) if x.dim() == 1 else x
-        g2 = gz.reshape(1, -1) if gz.dim() == 1 else gz
-        if x2.shape != g2.shape or x2.stride() != g2.stride() or x2.stride(1) != 1:
-            raise ValueError("x and grad_z must have the same row-major layout")
-        rows, n, ld = x2.shape[0], x2.shape[1], x2.stride(0)
+        x2, g2 = x, gz
+        if x.shape == gz.shape and x.stride() == gz.stride() == (1,):   # two streams: no views to build
+            rows, n, ld = 1, x.numel(), x.numel()
+        else:
+            x2 = x.reshape(1, -1) if x.dim() == 1 else x
+            g2 = gz.reshape(1, -1) if gz.dim() == 1 else gz
+            if x2.shape != g2.shape or x2.stride() != g2.stride() or x2.stride(1) != 1:
+                raise ValueError("x and grad_z must have the same row-major layout")
+            rows, n, ld = x2.shape[0], x2.shape[1], x2.stride(0)
         gx = torch.empty_like(x) if want_dx else None
         gc = torch.empty(self.K, dtype=torch.complex64, device=x.device) if want_dcoeffs else None
         ws_bytes = dpd_backward_ws_size(self.handle, rows, n)

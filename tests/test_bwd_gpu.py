@@ -239,3 +239,22 @@ def test_device_coefficients_give_the_plans_bits(torch, dpd):
         b, bc = other.backward(x, G, coeffs=_dev(torch, h))
         assert torch.equal(torch.view_as_real(a), torch.view_as_real(b))
         assert torch.equal(torch.view_as_real(ac), torch.view_as_real(bc))
+
+
+def test_streams_and_layouts_of_the_wrappers(torch, dpd):
+    """current_stream() is torch's, also in a stream context and on autograd's
+    thread; Plan.backward takes the layouts it took and refuses the others."""
+    assert dpd.current_stream() == torch.cuda.current_stream().cuda_stream
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        assert dpd.current_stream() == s.cuda_stream != torch.cuda.default_stream().cuda_stream
+    plan = dpd.Plan([1, 3], [1], 2, np.ones(7, dtype=np.complex64))
+    x = torch.randn(600, dtype=torch.complex64, device="cuda")
+    g = torch.randn(600, dtype=torch.complex64, device="cuda")
+    gx, gc = plan.backward(x, g)
+    for a, b in ((x.view(1, 600), g.view(1, 600)), (x, g.view(1, 600))):
+        gx2, gc2 = plan.backward(a, b)
+        assert torch.equal(gx2.reshape(-1), gx) and torch.equal(gc2, gc)
+    for a, b in ((x[::2], g[::2]), (x[:300], g[::2]), (x, g[:300]), (x.view(300, 2).t(), g.view(300, 2).t())):
+        with pytest.raises(ValueError):
+            plan.backward(a, b)
