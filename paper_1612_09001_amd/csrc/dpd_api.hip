@@ -261,9 +261,10 @@ static size_t span_bytes(int64_t rows, int64_t n, int64_t ld)
 // blocks that hide each other's waits, beat the streaming form (2^23: 23.6
 // against 26.3 us; NI L <= 9 is light enough for S = 2: 21.2 against 24.4 at
 // NI = L = 2).  Beyond, memory bounds and the streaming form's ordered sweep
-// wins (2^24: 48 us against 58), with a third block per CU where the filter is
-// heavy (NI L >= 24: 77 against 81.5 us at NI = 5, L = 8; lighter ones lose:
-// 52 against 48 at NI = L = 4).
+// wins (2^24: 48 us against 58), with four blocks per CU (as many as fit) where
+// the filter is heavy (NI L >= 24: 2^24 at NI = 5, L = 8 75 us against 81 with
+// two, 2^26 271 against 311; lighter ones gain nothing: 46.1 and 46.0 at NI = L =
+// 4).
 static dpd_tune fwd_auto(const CoefMap &map, int64_t N)
 {
     dpd_tune t = default_tune();
@@ -272,7 +273,7 @@ static dpd_tune fwd_auto(const CoefMap &map, int64_t N)
         t.stage_lds = 0;
         t.samples_per_thread = N < (int64_t)1 << 20 || cost <= 9 ? 2 : 4;
     } else {
-        t.grid_mult = cost >= 24 ? 3 : 2;
+        t.grid_mult = cost >= 24 ? 4 : 2;
     }
     return t;
 }

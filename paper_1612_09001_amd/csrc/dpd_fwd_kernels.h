@@ -228,8 +228,74 @@ __device__ __forceinline__ void fir_outputs_lds(const float (&a)[S + L - 1], con
     }
 }
 
+// fir_outputs with half of the table as scalar operands (M, the first column of
+// each matrix) and half in VGPRs (from LDS, CS).  An FMA with a scalar operand
+// cannot issue together with another wave's, FMAs of VGPRs alone draw more power
+// and lower the clock (16 FMAs by each of two waves: 66 cycles all scalar, 46 to
+// 49 all VGPR, 42 half and half), and half the table halves the LDS reads.  Each
+// tap's entries are read when its turn comes: at four waves per SIMD the others
+// cover the wait, and one buffer of them is what lets four fit (126 registers at NI
+// = 5, L = 8, S = 8, against 156 with two buffers in VGPRs).
+typedef float cvec4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef const __attribute__((address_space(4))) cvec4 ccvec4;
+
+template <int NI, int L, int S>
+__device__ __forceinline__ void fir_outputs_split(const float (&a)[S + L - 1], const float (&b)[S + L - 1],
+                                                  const float (&s)[S + L - 1], const float *CS, const cfloat *M,
+                                                  float (&zr)[S], float (&zi)[S])
+{
+    const float2 c = *reinterpret_cast<const float2 *>(CS + 4 * L * NI);
+#pragma unroll
+    for (int i = 0; i < S; ++i) {
+        zr[i] = c.x;
+        zi[i] = c.y;
+    }
+    // opaque zeros of the next tap's addresses
+    int zv = 0, zs = 0;
+    asm volatile("" : "+v"(zv));
+    asm volatile("" : "+s"(zs));
+#pragma unroll
+    for (int k = 0; k < L; ++k) {
+        float v0[NI], v1[NI], s0[NI], s1[NI];   // columns 1 and 0 of M_{j,k}
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+            const int e = 4 * (NI * k + j);
+            v0[j] = CS[zv + e + 1];
+            v1[j] = CS[zv + e + 3];
+            const cvec4 u = *(ccvec4 *)(M + zs + e);
+            s0[j] = u.x;
+            s1[j] = u.z;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < S; ++i) {
+            const int w = i + (L - 1) - k;
+            float w00 = s0[NI - 1], w01 = v0[NI - 1], w10 = s1[NI - 1], w11 = v1[NI - 1];
+#pragma unroll
+            for (int j = NI - 2; j >= 0; --j) {
+                w00 = __builtin_fmaf(w00, s[w], s0[j]);
+                w01 = __builtin_fmaf(w01, s[w], v0[j]);
+                w10 = __builtin_fmaf(w10, s[w], s1[j]);
+                w11 = __builtin_fmaf(w11, s[w], v1[j]);
+            }
+            zr[i] = __builtin_fmaf(w00, a[w], zr[i]);
+            zr[i] = __builtin_fmaf(w01, b[w], zr[i]);
+            zi[i] = __builtin_fmaf(w10, a[w], zi[i]);
+            zi[i] = __builtin_fmaf(w11, b[w], zi[i]);
+        }
+        if (k + 1 < L) {
+            // the reads of the next tap wait for this one's results (as in
+            // fir_outputs_lds)
+#pragma unroll
+            for (int i = 0; i < S; ++i) asm volatile("" : "+v"(zv) : "v"(zr[i]), "v"(zi[i]));
+            asm volatile("" : "+s"(zs) : "v"(zr[0]));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
 // Coefficient tables up to this many floats stay in registers in the
-// streaming kernel (larger ones are read from LDS, tap by tap).
+// streaming kernel (larger ones are read tap by tap, see fir_outputs_split).
 constexpr int kRegCoefMax = 96;
 
 template <int W>
@@ -266,12 +332,15 @@ __device__ __forceinline__ void store_outputs(float2 *__restrict__ z, int64_t m0
 // One-shot kernel (stage_lds = 0): each block computes one tile of kBlock*S
 // outputs; every thread loads its own S+L-1 window with 16-byte loads (the
 // halo part re-reads its neighbour's samples, which the vector L1 / L2 serve).
-// The top Horner level sits in VGPRs (an FMA takes one scalar operand), the
-// lower ones are scalar loads.  S = 2, the form of short calls, whose time is
-// the chain of memory latencies: straight from scalar loads beside the
-// window's, no barrier (3.06 us for 2^16 samples at NI = L = 4 against 3.13).
-// Larger S: through LDS, whose barrier starts the block's loads together
-// (2^23 samples: 23.6 us against 25.4).
+// S = 4: half of the table as scalar operands, half from LDS (fir_outputs_split;
+// 2^22 samples at NI = 5: L = 12 25.7 us against 28.1 with all but the top Horner
+// level scalar, L = 16 32.1 against 36.5; 2^23 at NI = L = 4 the same).  Otherwise
+// the top level sits in VGPRs (an FMA takes one scalar operand) and the lower
+// ones are scalar loads.  S = 2, the form of short calls, whose time is the chain
+// of memory latencies: top level straight from scalar loads beside the window's,
+// no barrier (3.06 us for 2^16 samples at NI = L = 4 against 3.13).  Larger S:
+// through LDS, whose barrier starts the block's loads together (2^23 samples:
+// 23.6 us against 25.4).
 template <int NI, int L, int S>
 __global__ void __launch_bounds__(kBlock) fwd_tile_kernel(FwdParams p)
 {
@@ -281,14 +350,19 @@ __global__ void __launch_bounds__(kBlock) fwd_tile_kernel(FwdParams p)
     constexpr int W = S + L - 1;
     constexpr int WL = HP + S;              // loaded samples (even)
     constexpr bool DIRECT = S == 2;
-    __shared__ float ctop[DIRECT ? 1 : 4 * L];
+    constexpr bool SPLIT = S == 4;
+    constexpr int NC = SPLIT ? 4 * L * NI + 2 : 4 * L;   // table floats in LDS
+    __shared__ __align__(16) float ctab[DIRECT ? 1 : NC];
     const int tid = threadIdx.x;
     float top[4 * L];
     if constexpr (!DIRECT) {
-        if (tid < 4 * L) ctop[tid] = p.M[(tid >> 2) * 4 * NI + 4 * (NI - 1) + (tid & 3)];
+        for (int e = tid; e < NC; e += kBlock)
+            ctab[e] = p.M[SPLIT ? e : (e >> 2) * 4 * NI + 4 * (NI - 1) + (e & 3)];
         __syncthreads();
+        if constexpr (!SPLIT) {
 #pragma unroll
-        for (int e = 0; e < 4 * L; ++e) top[e] = ctop[e];
+            for (int e = 0; e < 4 * L; ++e) top[e] = ctab[e];
+        }
     }
 
     for (int64_t step = xcd_remap(blockIdx.x, gridDim.x); step < p.total_tiles; step += gridDim.x) {
@@ -316,6 +390,12 @@ __global__ void __launch_bounds__(kBlock) fwd_tile_kernel(FwdParams p)
 #pragma unroll
             for (int i = 0; i < WL; ++i) raw[i] = sample_or_hist<L>(x, lo + i, p.n, hist);
         }
+        float2 win[W];
+#pragma unroll
+        for (int w = 0; w < W; ++w) win[w] = raw[HP - (L - 1) + w];
+        float a[W], b[W], s[W];
+        split_window<W>(win, a, b, s);
+        float zr[S], zi[S];
         const cfloat *M = as_const(p.M);
         if constexpr (DIRECT) {
 #pragma unroll
@@ -324,13 +404,10 @@ __global__ void __launch_bounds__(kBlock) fwd_tile_kernel(FwdParams p)
                 asm("" : "+v"(top[e]));
             }
         }
-        float2 win[W];
-#pragma unroll
-        for (int w = 0; w < W; ++w) win[w] = raw[HP - (L - 1) + w];
-        float a[W], b[W], s[W];
-        split_window<W>(win, a, b, s);
-        float zr[S], zi[S];
-        fir_outputs<NI, L, S>(a, b, s, top, as_const(p.M), zr, zi);
+        if constexpr (SPLIT)
+            fir_outputs_split<NI, L, S>(a, b, s, ctab, M, zr, zi);
+        else
+            fir_outputs<NI, L, S>(a, b, s, top, M, zr, zi);
         if (m0 < p.n) store_outputs<S>(z, m0, p.n, full, zr, zi);
         if (L > 1 && p.hist != nullptr && step == 0) {
             // a carried history is read by this block alone; replace it once
@@ -355,6 +432,26 @@ __device__ __forceinline__ void wave_lds_order()
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Wave priority of a persistent wave with `left` of `all` chunks to go: more for
+// waves that are behind.  The waves of a SIMD are served oldest first, so without
+// it one runs ahead and the last works alone at the end, where a single wave
+// issues half of what two do.  2^26 samples at NI = 5, L = 8: 294 -> 282 us with
+// three blocks per CU; with four and fir_outputs_split 271 (NI = 4, L = 8: 262 ->
+// 235; NI = 4, L = 6: 225 -> 198; L = 16: 538 -> 485, three blocks).
+__device__ __forceinline__ void progress_prio(int64_t left, int64_t all)
+{
+    if (2 * left > all) {
+        if (4 * left > 3 * all)
+            __builtin_amdgcn_s_setprio(3);
+        else
+            __builtin_amdgcn_s_setprio(2);
+    } else if (4 * left > all) {
+        __builtin_amdgcn_s_setprio(1);
+    } else {
+        __builtin_amdgcn_s_setprio(0);
+    }
 }
 
 // Streaming kernel (stage_lds = 1).  Persistent grid of waves; at every step
@@ -399,8 +496,17 @@ struct PadLayout {
     }
 };
 
+// Blocks per CU the registers are held to: four where the table is read tap by tap
+// and the window is small enough (NI = 5, L = 8 would take one register more than
+// 128; larger filters would spill).
+template <int NI, int L>
+constexpr int fwd_stream_blocks()
+{
+    return 4 * L * NI + 2 > kRegCoefMax && L <= kSpecL && NI + L <= 14 ? 4 : 1;
+}
+
 template <int NI, int L, int S>
-__global__ void __launch_bounds__(kBlock) fwd_stream_kernel(FwdParams p)
+__global__ void __launch_bounds__(kBlock, (fwd_stream_blocks<NI, L>())) fwd_stream_kernel(FwdParams p)
 {
     static_assert(S % 2 == 0, "S must be even (16-byte loads and stores)");
     constexpr int C = 64 * S;
@@ -508,13 +614,8 @@ __global__ void __launch_bounds__(kBlock) fwd_stream_kernel(FwdParams p)
         }
         if constexpr (REG)
             fir_outputs_reg<NI, L, S>(a, b, s, coef, zr, zi);
-        else {
-            // An opaque zero keeps the table reads inside the chunk loop:
-            // hoisted, the whole table would take registers.
-            int z = 0;
-            asm volatile("" : "+v"(z));
-            fir_outputs_lds<NI, L, S>(a, b, s, ctab + z, zr, zi);
-        }
+        else
+            fir_outputs_split<NI, L, S>(a, b, s, ctab, as_const(p.M), zr, zi);
     };
 
     // Store the S outputs of every lane of a full chunk.  S = 2: each lane's
@@ -559,11 +660,13 @@ __global__ void __launch_bounds__(kBlock) fwd_stream_kernel(FwdParams p)
             }
             return u;
         };
+        int64_t left = (total - 1 - gw) / nw + 1;    // chunks of this wave
+        const int64_t all = left;
         // The prefetch issues at raised wave priority, so a wave reaching it
         // is not held behind the other waves' filter work on the SIMD
         // (measured: 47.8 -> 47.2 us at the 2^24 headline, outputs unchanged).
         auto load_full = [&](ChunkRegs<S> &buf, const Cur &u) {
-            __builtin_amdgcn_s_setprio(2);
+            __builtin_amdgcn_s_setprio(3);
             const int64_t t0 = start(u.k);
             const v4f_s *x4 = reinterpret_cast<const v4f_s *>(p.in + u.row * p.ld + t0);
 #pragma unroll
@@ -573,7 +676,7 @@ __global__ void __launch_bounds__(kBlock) fwd_stream_kernel(FwdParams p)
                 buf.v[i] = make_float4(t.x, t.y, t.z, t.w);
             }
             buf.h = halo_raw_full(u.row, t0);
-            __builtin_amdgcn_s_setprio(0);
+            progress_prio(left, all);
         };
         auto step = [&](const ChunkRegs<S> &buf, const Cur &u) {
             float zr[S], zi[S];
@@ -584,7 +687,6 @@ __global__ void __launch_bounds__(kBlock) fwd_stream_kernel(FwdParams p)
         // Two chunks per trip with the next one always in flight; the loop
         // body is straight-line code (exact counter waits) and the last one
         // or two chunks are peeled off, so nothing is read past the run.
-        int64_t left = (total - 1 - gw) / nw + 1;    // chunks of this wave
         Cur cur;
         cur.row = gw / tpr;
         cur.k = gw - cur.row * tpr;
