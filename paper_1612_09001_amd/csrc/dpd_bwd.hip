@@ -154,7 +154,18 @@ static dpd_status backward_impl(dpd_plan *plan, void *stream, const void *coeffs
             return (int)std::max<int64_t>(1, std::min(cap, (chunks + 3) / 4));
         };
         hipError_t e = hipSuccess;
-        if (map.L <= kSpecL) {
+        // Both gradients of a filter whose registers leave one block per CU: on
+        // long inputs two kernels of two and more blocks are faster, though they
+        // read the samples twice (NI = 4, L = 8, 2^24 samples: 194 us and 169; NI = 5,
+        // L = 8: 254 and 218; 2^22, where the input stays in the last-level cache
+        // but the second launch costs: 57 and 60, 75 and 70).
+        const bool apart = want_dx && want_dc && map.L <= kSpecL && rows * n >= (int64_t)6 << 20 &&
+                           bwd_occupancy(map.NI, map.L, 2) == 1;
+        if (apart) {
+            e = t.fn[map.NI - 1][map.L - 1][0](p, st, grid_of(map.L, 0));
+            nblk = grid_of(map.L, 1);
+            if (e == hipSuccess) e = t.fn[map.NI - 1][map.L - 1][1](p, st, nblk);
+        } else if (map.L <= kSpecL) {
             const int want = want_dx && want_dc ? 2 : (want_dc ? 1 : 0);
             nblk = grid_of(map.L, want);
             e = t.fn[map.NI - 1][map.L - 1][want](p, st, nblk);

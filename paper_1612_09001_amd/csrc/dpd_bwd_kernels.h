@@ -135,6 +135,15 @@ struct BwdTag {
     static constexpr bool value = B;
 };
 
+// Blocks per CU the registers are held to.  One wave per SIMD issues half of what
+// two do, so the kernel of both gradients is held to two blocks wherever that
+// costs no spills in its loop (2^24 samples: NI = 4, L = 7 167 -> 126 us; NI = 5, L
+// = 6 187 -> 135; NI = 5, L = 8, not held, 254 us would be 458).
+constexpr int bwd_blocks(int NI, int L, bool both)
+{
+    return both && 4 * L * NI + 2 + L <= 136 ? 2 : 1;
+}
+
 // Persistent grid over the full chunks (C = 64*S samples) of all rows, wave g
 // taking chunks g, g + nw, ... (rows flattened), then the ragged row ends.
 // Per chunk the wave stages G (the chunk plus the L-1 samples after it; zero
@@ -151,7 +160,7 @@ struct BwdTag {
 // longer filter (coefficient gradient only).  Rows may start at any sample:
 // 16-byte accesses need no 16-byte alignment here (v4f_s).
 template <int NI, int L, bool DX, bool DC, int K0 = 0>
-__global__ void __launch_bounds__(kBlock) bwd_kernel(BwdParams p)
+__global__ void __launch_bounds__(kBlock, bwd_blocks(NI, L, DX && DC)) bwd_kernel(BwdParams p)
 {
     static_assert(!DX || K0 == 0, "the input gradient needs every tap");
     static_assert(K0 % kBwdS == 0, "the window of a pass starts on a pad group");

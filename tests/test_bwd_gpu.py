@@ -258,3 +258,25 @@ def test_streams_and_layouts_of_the_wrappers(torch, dpd):
     for a, b in ((x[::2], g[::2]), (x[:300], g[::2]), (x, g[:300]), (x.view(300, 2).t(), g.view(300, 2).t())):
         with pytest.raises(ValueError):
             plan.backward(a, b)
+
+
+@pytest.mark.parametrize("over", [0, -1])
+def test_both_gradients_of_a_long_heavy_input(torch, dpd, over):
+    """Either side of the length from which a filter with one resident block per
+    CU takes one kernel per gradient: there the bits are those of the separate
+    calls, below it the single kernel agrees with them."""
+    rows, n = 3, (2 << 20) + over
+    mo = [1, 3, 5, 7]
+    plan = dpd.Plan(mo, mo, 8, signals.aph_coeffs(mo, mo, 8, config_id=95))
+    gen = torch.Generator(device="cuda").manual_seed(95)
+    x = torch.randn(rows, n, dtype=torch.complex64, device="cuda", generator=gen) * 0.2
+    g = torch.randn(rows, n, dtype=torch.complex64, device="cuda", generator=gen)
+    gx, gc = plan.backward(x, g)
+    gx1, _ = plan.backward(x, g, want_dcoeffs=False)
+    _, gc1 = plan.backward(x, g, want_dx=False)
+    if over >= 0:
+        assert torch.equal(torch.view_as_real(gx), torch.view_as_real(gx1))
+        assert torch.equal(torch.view_as_real(gc), torch.view_as_real(gc1))
+    else:
+        assert_parity(gx.cpu().numpy().reshape(-1), gx1.cpu().numpy().reshape(-1).astype(np.complex128), "dx")
+        assert_dcoef(gc.cpu().numpy(), gc1.cpu().numpy().astype(np.complex128), "dcoef")
