@@ -465,7 +465,10 @@ __device__ __forceinline__ void ls_sub_wave(const LsParams &p, uint32_t *X, int 
         for (int e = 0; e < RI; ++e) {
             if (lane + 64 * e >= rows) continue;
             uint32_t *x = B + (lane + 64 * e) * kLsBStride;
-            const float vx = p.y_scale * y[e].x, vy = p.y_scale * y[e].y;
+            float vx = p.y_scale * y[e].x, vy = p.y_scale * y[e].y;
+            // rounded here: wave 0's pw is 1 at compile time, and the products
+            // would be contracted into the remainders that ls_pack2 takes
+            asm("" : "+v"(vx), "+v"(vy));
             const float s2 = __builtin_fmaf(vx, vx, vy * vy);
             float pw = 1.f;
             for (int f = 0; f < j0; ++f) pw *= s2;

@@ -437,3 +437,26 @@ def test_normal_equations_of_few_slabs(torch, dpd, orc, mo, co, L):
         K = plan.K
         assert torch.equal(torch.view_as_real(A[:K - 1]), torch.view_as_real(B[:K - 1])), n
         assert torch.equal(torch.view_as_real(b), torch.view_as_real(d)), n
+
+
+@pytest.mark.parametrize("scale", [0.1, 3.0])
+@pytest.mark.parametrize("orders,L", [(([1, 3, 5], [1, 3]), 1), (([1, 3, 5, 7], [1]), 15), (([1, 3, 5, 7], [1, 3, 5, 7]), 4),
+                                      (([1, 3, 5, 7, 9], [1, 3, 5, 7, 9]), 8)])
+def test_few_slabs_with_an_input_scale(torch, dpd, orders, L, scale):
+    """The spread form of few-slab inputs rounds a scaled input as the other one
+    does: the same bits (one row among rows of zeros takes the other form)."""
+    mo, co = orders
+    plan = dpd.Plan(mo, co, L, signals.aph_coeffs(mo, co, L))
+    n = 1000
+    gen = torch.Generator(device="cuda").manual_seed(98)
+    y = torch.randn(n, dtype=torch.complex64, device="cuda", generator=gen)
+    t = torch.randn(n, dtype=torch.complex64, device="cuda", generator=gen)
+    A, b = plan.ls_normal(y, t, scale)
+    rows = 1 + 2 * torch.cuda.get_device_properties(0).multi_processor_count
+    Y = torch.zeros(rows, n, dtype=torch.complex64, device="cuda")
+    T = torch.zeros_like(Y)
+    Y[1], T[1] = y, t
+    B, d = plan.ls_normal(Y, T, scale)
+    K = plan.K
+    assert torch.equal(torch.view_as_real(A[:K - 1]), torch.view_as_real(B[:K - 1]))
+    assert torch.equal(torch.view_as_real(b), torch.view_as_real(d))
