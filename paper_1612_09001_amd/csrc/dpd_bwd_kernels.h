@@ -136,12 +136,14 @@ struct BwdTag {
 };
 
 // Blocks per CU the registers are held to.  One wave per SIMD issues half of what
-// two do, so the kernel of both gradients is held to two blocks wherever that
-// costs no spills in its loop (2^24 samples: NI = 4, L = 7 167 -> 126 us; NI = 5, L
-// = 6 187 -> 135; NI = 5, L = 8, not held, 254 us would be 458).
+// two do, so the kernel of both gradients is held to two blocks where it would
+// just miss them and that costs no spills in its loop (2^24 samples: NI = 4, L = 7
+// 167 -> 126 us; NI = 5, L = 6 187 -> 135; NI = 5, L = 8, not held, 254 us would be
+// 458).  Up to 110 accumulators two blocks fit by themselves.
 constexpr int bwd_blocks(int NI, int L, bool both)
 {
-    return both && 4 * L * NI + 2 + L <= 136 ? 2 : 1;
+    const int E = 4 * L * NI + 2;
+    return both && E > 110 && E + L <= 136 ? 2 : 1;
 }
 
 // Persistent grid over the full chunks (C = 64*S samples) of all rows, wave g
