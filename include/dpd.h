@@ -243,8 +243,8 @@ dpd_status dpd_batch_apply(dpd_batch *batch, void *stream);
  * same kernels as dpd_apply (for comparison against the persistent form). */
 dpd_status dpd_batch_apply_each(dpd_batch *batch, void *stream);
 
-/* dpd_batch_info -- number of chunks (full and ragged) in the persistent
- * launch and its number of blocks. */
+/* dpd_batch_info -- number of chunks (streams shorter than one included) and
+ * number of blocks of the persistent launch. */
 dpd_status dpd_batch_info(const dpd_batch *batch, int64_t *n_tiles, int32_t *n_blocks);
 
 /* dpd_batch_destroy -- frees the batch; freeing device memory waits for the

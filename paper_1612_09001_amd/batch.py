@@ -1,8 +1,9 @@
 """Batched multi-stream apply (many antennas, uneven lengths, own coefficients).
 
 ``Batch`` wraps ``dpd_batch_create`` / ``dpd_batch_apply``: one coefficient
-precombine launch, one persistent launch over the full chunks of all streams
-and one small launch for their ragged ends; graph-capturable (no allocation,
+precombine launch, one persistent launch over the chunks of all streams (a
+stream's last chunk moved back to its end) and, where streams are shorter than a
+chunk, one small launch for those; graph-capturable (no allocation,
 no host synchronization, no device state carried between calls).
 ``BatchWorkload`` builds the multi-antenna workload in two device arenas
 (inputs, outputs) with 16-byte aligned stream offsets plus one coefficient

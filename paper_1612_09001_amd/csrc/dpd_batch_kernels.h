@@ -368,7 +368,7 @@ __global__ void __launch_bounds__(kBlock) batch_tail_kernel(BatchParams bp)
 }
 
 // grid: blocks of the streaming kernel (0: no full chunk); tail_grid: blocks
-// of the ragged-chunk kernel (0: none).
+// of the short-stream kernel (0: none).
 typedef hipError_t (*BatchLaunch)(const BatchParams &, hipStream_t, int grid, int tail_grid);
 struct BatchTable {
     BatchLaunch fn[kNumSIdx];
