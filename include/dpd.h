@@ -184,8 +184,10 @@ dpd_status dpd_apply_hist(dpd_plan *plan, void *stream, const void *in, void *ou
  *   ws, ws_bytes device workspace of at least dpd_backward_ws_size() bytes
  * Deterministic: the same inputs give bitwise the same gradients.  Rows start
  * from zero history.  dE/dcoeffs is summed in FP32 over at most 128 samples
- * per lane, then in FP64, so its accuracy does not degrade with rows * n (any
- * size that fits in memory, 64-bit indices throughout). */
+ * per lane and the 64 lanes of a wave, then in FP64 (rows that start or are
+ * strided off 16 bytes, and plans of more than 8 taps: FP32 over at most 64
+ * samples of one lane, all else FP64), so its accuracy does not degrade with
+ * rows * n (any size that fits in memory, 64-bit indices throughout). */
 dpd_status dpd_backward_ws_size(const dpd_plan *plan, int64_t rows, int64_t n, size_t *bytes);
 dpd_status dpd_backward(dpd_plan *plan, void *stream, const void *coeffs_dev, const void *x,
                         const void *grad_z, void *grad_x, void *grad_coeffs, int64_t rows,

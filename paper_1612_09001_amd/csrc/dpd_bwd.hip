@@ -143,6 +143,10 @@ static dpd_status backward_impl(dpd_plan *plan, void *stream, const void *coeffs
     p.M = plan->d_table;
     p.raw = (const float2 *)coeffs_dev;
     p.map = map;
+    const bool even = (uintptr_t)x % 16 == 0 && (uintptr_t)grad_z % 16 == 0 && (uintptr_t)grad_x % 16 == 0 &&
+                      (rows == 1 || ld % 2 == 0);
+    p.fine = !even || map.L > kSpecL;
+    p.flush = p.fine ? (int32_t)bwd_flush_fine(rows * n) : kBwdFlush;
     int nblk = 0;
     if (!empty) {
         const int64_t C = 64 * kBwdS;
@@ -159,8 +163,10 @@ static dpd_status backward_impl(dpd_plan *plan, void *stream, const void *coeffs
         // read the samples twice (NI = 4, L = 8, 2^24 samples: 194 us and 169; NI = 5,
         // L = 8: 254 and 218; 2^22, where the input stays in the last-level cache
         // but the second launch costs: 57 and 60, 75 and 70).
-        const bool apart = want_dx && want_dc && map.L <= kSpecL && rows * n >= (int64_t)6 << 20 &&
-                           bwd_occupancy(map.NI, map.L, 2) == 1;
+        // Likewise where only the kernel of dx alone sums by Horner.
+        const bool apart = want_dx && want_dc && map.L <= kSpecL &&
+                           ((rows * n >= (int64_t)6 << 20 && bwd_occupancy(map.NI, map.L, 2) == 1) ||
+                            (p.fine && !bwd_horner(map.NI, true, true)));
         if (apart) {
             e = t.fn[map.NI - 1][map.L - 1][0](p, st, grid_of(map.L, 0));
             nblk = grid_of(map.L, 1);

@@ -15,10 +15,10 @@
 // stacking happens in the FP64 finalisation kernel.
 //
 // Reduction of the coefficient gradient is deterministic: each lane sums its
-// own samples in a fixed order (FP32, at most kBwdFlush chunks at a time), the
-// wave reduces those sums in a fixed tree into its FP64 totals, the block adds
-// its waves' totals in order, one partial per block goes to the workspace, and
-// a single block sums the partials in FP64 in block order.
+// own samples in a fixed order (FP32, at most kBwdFlush chunks at a time, row
+// ends included), the wave adds those sums in a fixed tree to its FP64 totals, the
+// block adds its waves' totals in order, one partial per block goes to the
+// workspace, and a single block sums the partials in FP64 in block order.
 #pragma once
 
 #include "dpd_fwd_kernels.h"
@@ -35,6 +35,8 @@ struct BwdParams {
     int32_t E;            // E of the whole filter (a pass may cover some of its taps)
     int64_t n, ld, rows;
     int64_t tpr;          // full chunks per row (n / (64*S)); the ragged end is extra
+    int32_t flush;        // chunks that a lane's FP32 sums cover
+    int32_t fine;         // the sums over a wave's lanes in FP64 (else FP32)
     const float *M;       // precombined table
     const float2 *raw;    // or the K raw coefficients, precombined by every block
     CoefMap map;
@@ -64,9 +66,16 @@ void register_bwd_ni7(BwdTable &);
 void register_bwd_ni8(BwdTable &);
 
 constexpr int kBwdS = 4;   // consecutive samples per lane
-// Chunks a lane's FP32 coefficient-gradient sums cover before they are added
-// to the wave's FP64 totals (a power of two): 32 chunks = 128 samples per lane.
+// Chunks a lane's FP32 coefficient-gradient sums cover before the wave adds them
+// up and adds the result to its FP64 totals: 32 chunks = 128 samples per lane,
+// added up in FP32.  Rows at odd 8-byte starts or strides and filters of more than
+// kSpecL taps ("fine") are summed with less rounding: one chunk per 2^20 samples of
+// the input, at most 64 samples per lane, added up in FP64.
 constexpr int kBwdFlush = 32;
+constexpr int64_t bwd_flush_fine(int64_t samples)
+{
+    return samples >> 20 < 1 ? 1 : samples >> 20 < 16 ? samples >> 20 : 16;
+}
 
 // FP64 sums of table entry q's four coefficient-gradient partials (two for
 // q = L NI, the c entry) over nblk blocks: each thread its strided share of
@@ -146,6 +155,13 @@ constexpr int bwd_blocks(int NI, int L, bool both)
     return both && E > 110 && E + L <= 136 ? 2 : 1;
 }
 
+// dx by Horner in s, power levels from the highest down, or by explicit powers,
+// levels upwards.  Horner rounds less (relative error of dx against 64 bits 0.80e-7
+// over twelve shapes, explicit powers 0.86e-7); with both gradients it needs every
+// power of s at once, for which the kernels of six levels and more have no
+// registers left (2^22 samples at NI = L = 8: 112 us and 118).
+constexpr bool bwd_horner(int NI, bool dx, bool dc) { return dx && (!dc || NI <= 5); }
+
 // Persistent grid over the full chunks (C = 64*S samples) of all rows, wave g
 // taking chunks g, g + nw, ... (rows flattened), then the ragged row ends.
 // Per chunk the wave stages G (the chunk plus the L-1 samples after it; zero
@@ -155,10 +171,9 @@ constexpr int bwd_blocks(int NI, int L, bool both)
 // chunk's loads go out into the same registers before the staged chunk is
 // filtered, so the compiler's counter waits never cover the prefetch.  Each
 // lane owns S consecutive samples m and reads G_{m..m+S+L-2}.  One pass over
-// the power levels j (ascending) produces both gradients: U_j by taps for dx
-// (P = sum s^j U_j and 2Q = sum 2j s^(j-1) v.U_j accumulated with explicit
-// powers; dx = P + 2Q v), and G (x) s^j v into the per-lane coefficient
-// accumulators.  K0: the first tap of a pass over taps K0 .. K0 + L - 1 of a
+// the power levels j produces both gradients: U_j by taps for dx = P + 2 Q v (P =
+// sum s^j U_j, Q = sum j s^(j-1) v.U_j), and G (x) s^j v into the per-lane
+// coefficient accumulators.  K0: the first tap of a pass over taps K0 .. K0 + L - 1 of a
 // longer filter (coefficient gradient only).  Rows may start at any sample:
 // 16-byte accesses need no 16-byte alignment here (v4f_s).
 template <int NI, int L, bool DX, bool DC, int K0 = 0>
@@ -174,6 +189,7 @@ __global__ void __launch_bounds__(kBlock, bwd_blocks(NI, L, DX && DC)) bwd_kerne
     constexpr int NM = 4 * L * NI;                              // matrix floats (c has no gradient path here)
     constexpr int E = NM + (K0 == 0 ? 2 : 0);                   // c belongs to the first pass
     constexpr int HS = K0 + L - 1;                              // right halo
+    constexpr bool HORNER = bwd_horner(NI, DX, DC);
     constexpr int GSLOTS = C + HS + (C + HS) / S + 1;
     constexpr int XSLOTS = C + C / S;
     __shared__ __align__(16) float2 gs[WAVES][GSLOTS];
@@ -206,7 +222,10 @@ __global__ void __launch_bounds__(kBlock, bwd_blocks(NI, L, DX && DC)) bwd_kerne
     for (int g = 0; g < NGT; ++g) tot[g] = 0.0;
     auto flush = [&]() {
         if constexpr (DC) {
-            wave_sums_into<E>(acc, tot, lane);
+            if (p.fine)
+                wave_sums_into<double, E>(acc, tot, lane);
+            else
+                wave_sums_into<float, E>(acc, tot, lane);
 #pragma unroll
             for (int e = 0; e < E; ++e) acc[e] = 0.f;
         }
@@ -288,21 +307,33 @@ __global__ void __launch_bounds__(kBlock, bwd_blocks(NI, L, DX && DC)) bwd_kerne
             vb[i] = v.y;
             sq[i] = __builtin_fmaf(v.x, v.x, v.y * v.y);
         }
-        float Pa[S], Pb[S], Q[S], pw[S], pwl[S];
+        float Pa[S], Pb[S], Q[S];
+        float pws[HORNER && DC ? NI : 1][S];   // s^j of every level
+        float pw[S], pwl[S];                   // s^j, 2 j s^(j-1)
+        if constexpr (HORNER && DC) {
+#pragma unroll
+            for (int j = 1; j < NI; ++j)
+#pragma unroll
+                for (int i = 0; i < S; ++i) pws[j][i] = j == 1 ? sq[i] : pws[j - 1][i] * sq[i];
+        }
 #pragma unroll
         for (int i = 0; i < S; ++i) {
             Pa[i] = Pb[i] = Q[i] = 0.f;
-            pw[i] = 1.f;     // s^j
-            pwl[i] = 0.f;    // 2 j s^(j-1)
+            pw[i] = 1.f;
+            pwl[i] = 0.f;
         }
 #pragma unroll
-        for (int j = 0; j < NI; ++j) {
+        for (int jj = 0; jj < NI; ++jj) {
+            const int j = HORNER ? NI - 1 - jj : jj;
             float Ua[S], Ub[S], ba[S], bb[S];
 #pragma unroll
             for (int i = 0; i < S; ++i) {
                 Ua[i] = Ub[i] = 0.f;
-                ba[i] = pw[i] * va[i];
-                bb[i] = pw[i] * vb[i];
+                if constexpr (DC) {
+                    const float w = HORNER && j > 0 ? pws[HORNER ? j : 0][i] : pw[i];
+                    ba[i] = w * va[i];
+                    bb[i] = w * vb[i];
+                }
             }
 #pragma unroll
             for (int k = 0; k < L; ++k) {
@@ -328,17 +359,26 @@ __global__ void __launch_bounds__(kBlock, bwd_blocks(NI, L, DX && DC)) bwd_kerne
             }
 #pragma unroll
             for (int i = 0; i < S; ++i) {
-                if constexpr (DX) {
-                    // level 0 has s^0 = 1: P starts at U_0
-                    Pa[i] = j == 0 ? Ua[i] : __builtin_fmaf(pw[i], Ua[i], Pa[i]);
-                    Pb[i] = j == 0 ? Ub[i] : __builtin_fmaf(pw[i], Ub[i], Pb[i]);
-                    if (j > 0) {
-                        const float d = __builtin_fmaf(va[i], Ua[i], vb[i] * Ub[i]);
-                        Q[i] = j == 1 ? pwl[i] * d : __builtin_fmaf(pwl[i], d, Q[i]);
+                if constexpr (HORNER) {
+                    Pa[i] = j == NI - 1 ? Ua[i] : __builtin_fmaf(Pa[i], sq[i], Ua[i]);
+                    Pb[i] = j == NI - 1 ? Ub[i] : __builtin_fmaf(Pb[i], sq[i], Ub[i]);
+                    if (j > 0) {   // the factor 2 of Q comes at the end
+                        const float d = (float)j * __builtin_fmaf(va[i], Ua[i], vb[i] * Ub[i]);
+                        Q[i] = j == NI - 1 ? d : __builtin_fmaf(Q[i], sq[i], d);
                     }
-                    pwl[i] = (float)(2 * (j + 1)) * pw[i];   // 2 (j + 1) s^j: Q carries the factor 2 of dx
+                } else {
+                    if constexpr (DX) {
+                        // level 0 has s^0 = 1: P starts at U_0
+                        Pa[i] = j == 0 ? Ua[i] : __builtin_fmaf(pw[i], Ua[i], Pa[i]);
+                        Pb[i] = j == 0 ? Ub[i] : __builtin_fmaf(pw[i], Ub[i], Pb[i]);
+                        if (j > 0) {
+                            const float d = __builtin_fmaf(va[i], Ua[i], vb[i] * Ub[i]);
+                            Q[i] = j == 1 ? pwl[i] * d : __builtin_fmaf(pwl[i], d, Q[i]);
+                        }
+                        pwl[i] = (float)(2 * (j + 1)) * pw[i];   // 2 (j + 1) s^j: Q carries the factor 2 of dx
+                    }
+                    pw[i] *= sq[i];
                 }
-                pw[i] *= sq[i];
             }
             // One power level at a time: the empty asm statements consume this
             // level's results, so the instruction selector cannot sink its
@@ -368,8 +408,9 @@ __global__ void __launch_bounds__(kBlock, bwd_blocks(NI, L, DX && DC)) bwd_kerne
             float dxa[S], dxb[S];
 #pragma unroll
             for (int i = 0; i < S; ++i) {
-                dxa[i] = __builtin_fmaf(Q[i], va[i], Pa[i]);
-                dxb[i] = __builtin_fmaf(Q[i], vb[i], Pb[i]);
+                const float q = HORNER ? 2.f * Q[i] : Q[i];
+                dxa[i] = __builtin_fmaf(q, va[i], Pa[i]);
+                dxb[i] = __builtin_fmaf(q, vb[i], Pb[i]);
             }
             float2 *gxr = p.gx + row * p.ld;
             if constexpr (FULL) {
@@ -395,6 +436,7 @@ __global__ void __launch_bounds__(kBlock, bwd_blocks(NI, L, DX && DC)) bwd_kerne
         }
     };
 
+    int held = 0;                                // chunks in the FP32 sums
     const int64_t tpr = p.tpr;                   // full chunks per row
     const int64_t total = p.rows * tpr;
     const int64_t nw = (int64_t)gridDim.x * WAVES;
@@ -418,9 +460,13 @@ __global__ void __launch_bounds__(kBlock, bwd_blocks(NI, L, DX && DC)) bwd_kerne
             load_full(R, row, tix * C);
             compute(crow, ct0, BwdTag<true>{});
             stage(R, tix * C);
-            if ((i & (kBwdFlush - 1)) == kBwdFlush - 1) flush();
+            if (++held == p.flush) {
+                flush();
+                held = 0;
+            }
         }
         compute(row, tix * C, BwdTag<true>{});
+        ++held;
     }
     // ragged row ends continue the round-robin order (chunk c to wave c mod nw)
     if (p.n > tpr * C) {
@@ -428,7 +474,12 @@ __global__ void __launch_bounds__(kBlock, bwd_blocks(NI, L, DX && DC)) bwd_kerne
             Regs R;
             load_part(R, r, tpr * C);
             stage(R, tpr * C);
+            if (held == p.flush) {
+                flush();
+                held = 0;
+            }
             compute(r, tpr * C, BwdTag<false>{});
+            ++held;
         }
     }
 

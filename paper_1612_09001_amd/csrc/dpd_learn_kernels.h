@@ -231,7 +231,7 @@ __global__ void __launch_bounds__(kBlock, ln_blocks(MODE, 4 * L * NI + 2)) learn
     for (int g = 0; g < NGT; ++g) tot[g] = 0.0;
     const auto flush = [&]() {
         if constexpr (GRAD) {
-            wave_sums_into<E>(acc, tot, lane);
+            wave_sums_into<float, E>(acc, tot, lane);
 #pragma unroll
             for (int e = 0; e < E; ++e) acc[e] = 0.f;
         }

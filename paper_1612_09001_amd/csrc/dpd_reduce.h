@@ -45,29 +45,76 @@ __device__ __forceinline__ T wave_sum_to_lane63(T v)
     return v;
 }
 
-// N <= 64 per-lane values v[0..N) summed over the wave, transposed: lane l
-// returns the sum of v[l] over all 64 lanes (zero for l >= N); v is
-// overwritten.  Six butterfly stages; at the stage of lane stride o the
-// registers pair up (i, i + o) and each lane keeps the one its lane bit o
-// selects, adding its partner's copy of it, so every stage halves the
-// registers still live (at most 63 exchanges instead of N separate
-// reductions).  Fixed order: the same inputs give the same bits.
-template <int N>
-__device__ __forceinline__ float wave_transpose_sum(float (&v)[N], int lane)
+// a + b with the upper half of a's lanes (of each 2 O lanes) and the lower half
+// of b's exchanged first: lanes whose bit O is clear get a summed over that bit,
+// the others b.
+template <int O>
+__device__ __forceinline__ void half_swap(unsigned &x, unsigned &y)
+{
+    static_assert(O == 32 || O == 16, "the widths of the exchange instructions");
+    if constexpr (O == 32) {
+        const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+        x = r[0];
+        y = r[1];
+    } else {
+        const auto r = __builtin_amdgcn_permlane16_swap(x, y, false, false);
+        x = r[0];
+        y = r[1];
+    }
+}
+template <int O>
+__device__ __forceinline__ float swap_add(float a, float b)
+{
+    unsigned x = __float_as_uint(a), y = __float_as_uint(b);
+    half_swap<O>(x, y);
+    return __uint_as_float(x) + __uint_as_float(y);
+}
+template <int O>
+__device__ __forceinline__ double swap_add(double a, double b)
+{
+    const unsigned long long ua = (unsigned long long)__double_as_longlong(a);
+    const unsigned long long ub = (unsigned long long)__double_as_longlong(b);
+    unsigned al = (unsigned)ua, ah = (unsigned)(ua >> 32), bl = (unsigned)ub, bh = (unsigned)(ub >> 32);
+    half_swap<O>(al, bl);
+    half_swap<O>(ah, bh);
+    return __longlong_as_double((long long)(((unsigned long long)ah << 32) | al)) +
+           __longlong_as_double((long long)(((unsigned long long)bh << 32) | bl));
+}
+
+// The same over 16 lanes and less: each lane keeps the value that its bit O
+// selects and adds the copy of the lane that CTRL pairs it with.
+template <int O, int CTRL, class T>
+__device__ __forceinline__ T keep_add(T a, T b, int lane)
+{
+    const bool up = (lane & O) != 0;
+    return (up ? b : a) + dpp_from<CTRL, 0xf>(up ? a : b);
+}
+
+// N <= 64 per-lane FP32 values summed over the wave in T (float or double),
+// transposed: lane l returns the sum of v[l] over all 64 lanes (zero for l >= N).
+// Six butterfly stages, each halving the values still held: a lane keeps the one
+// that its lane bit selects and adds its partner's copy (at bit 2 lanes l and l ^
+// 7 are partners; the last two stages sum over the bits in which those differ).
+// No LDS.  Fixed order: the same inputs give the same bits.
+template <class T, int N>
+__device__ __forceinline__ T wave_transpose_sum(const float *v, int lane)
 {
     static_assert(N >= 1 && N <= 64, "one register per lane and group");
+    const auto at = [&](int e) { return e < N ? (T)v[e] : (T)0; };
+    T a[16];
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        const bool up = (lane & o) != 0;
-#pragma unroll
-        for (int i = 0; i < o && i < N; ++i) {
-            const float other = i + o < N ? v[i + o] : 0.f;
-            const float keep = up ? other : v[i];
-            const float send = up ? v[i] : other;
-            v[i] = keep + __shfl_xor(send, o);
-        }
+    for (int i = 0; i < 16; ++i) {
+        const T x = i < N ? swap_add<32>(at(i), at(i + 32)) : (T)0;
+        const T y = i + 16 < N ? swap_add<32>(at(i + 16), at(i + 48)) : (T)0;
+        a[i] = i < N ? swap_add<16>(x, y) : (T)0;
     }
-    return v[0];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) a[i] = keep_add<8, 0x128>(a[i], a[i + 8], lane);    // row_ror:8
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a[i] = keep_add<4, 0x141>(a[i], a[i + 4], lane);    // row_half_mirror
+#pragma unroll
+    for (int i = 0; i < 2; ++i) a[i] = keep_add<2, 0x4E>(a[i], a[i + 2], lane);     // quad_perm 2,3,0,1
+    return keep_add<1, 0xB1>(a[0], a[1], lane);                                     // quad_perm 1,0,3,2
 }
 
 // Calls f(std::integral_constant<int, G>) for G = 0 .. NG-1.
@@ -88,15 +135,15 @@ struct ForEachGroup<NG, NG> {
     }
 };
 
-// The wave sums of E per-lane accumulators added to FP64 totals held
-// transposed (entry 64 g + l in lane l of tot[g]); acc is consumed.
-template <int E>
-__device__ __forceinline__ void wave_sums_into(float (&acc)[E], double (&tot)[(E + 63) / 64], int lane)
+// The wave sums of E per-lane accumulators, formed in T, added to FP64 totals
+// held transposed (entry 64 g + l in lane l of tot[g]).
+template <class T, int E>
+__device__ __forceinline__ void wave_sums_into(const float (&acc)[E], double (&tot)[(E + 63) / 64], int lane)
 {
     auto one = [&](auto gc) {
         constexpr int g = decltype(gc)::value;
         constexpr int n = E - 64 * g < 64 ? E - 64 * g : 64;
-        tot[g] += (double)wave_transpose_sum<n>(*reinterpret_cast<float(*)[n]>(&acc[64 * g]), lane);
+        tot[g] += (double)wave_transpose_sum<T, n>(&acc[64 * g], lane);
     };
     ForEachGroup<0, (E + 63) / 64>::run(one);
 }

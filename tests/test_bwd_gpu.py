@@ -280,3 +280,42 @@ def test_both_gradients_of_a_long_heavy_input(torch, dpd, over):
     else:
         assert_parity(gx.cpu().numpy().reshape(-1), gx1.cpu().numpy().reshape(-1).astype(np.complex128), "dx")
         assert_dcoef(gc.cpu().numpy(), gc1.cpu().numpy().astype(np.complex128), "dcoef")
+
+
+@pytest.mark.parametrize("n", [62, 63])
+def test_gradient_sums_over_many_short_rows(torch, dpd, n):
+    """Rows shorter than a chunk, some 70 per wave: the FP32 sums of a lane cover at
+    most 128 samples.  x = 1 and G = 1 + 2^-17: FP32 sums of up to 128 of them are
+    exact (longer ones lose 2^-17 of every sample), after which six FP32 additions
+    over the wave (even n; none at odd row starts) and the roundings of a block's
+    partial and of the result bound the relative error by 8 u, u = 2^-24."""
+    rows, v = 1 << 19, 1.0 + 2.0 ** -17
+    plan = dpd.Plan([1], [], 1, np.ones(2, dtype=np.complex64))
+    x = torch.ones(rows, n, dtype=torch.complex64, device="cuda")
+    G = torch.full((rows, n), v, dtype=torch.complex64, device="cuda")
+    _, gc = plan.backward(x, G, want_dx=False)
+    want = rows * n * v
+    err = np.abs(gc.cpu().numpy() - want) / want
+    assert np.max(err) <= 8 * 2.0 ** -24, err
+
+
+@pytest.mark.parametrize("L,n,off", [(1, 10241, 0), (4, 10240, 1), (9, 10240, 0)])
+def test_gradient_sums_of_odd_rows_and_long_filters(torch, dpd, L, n, off):
+    """Rows at odd starts or strides and filters of more than eight taps: sums over
+    a wave's lanes in FP64.  dE/dc = sum G with G = +-1024, the sign alternating
+    every four samples, and 2^-10 more on the first four of every 256: the FP32
+    sums of a lane are exact, but their sum over 64 lanes in FP32 reaches 2^17
+    before it cancels and loses the 2^-8.  What remains is the rounding of each
+    block's partial (at most a row's end, 1024, or a few 2^-8) and of the result."""
+    rows = 3
+    plan = dpd.Plan([1], [], L, np.ones(L + 1, dtype=np.complex64))
+    m = np.arange(n)
+    row = np.where((m // 4) % 2 == 0, 1024.0, -1024.0) + np.where(m % 256 < 4, 2.0 ** -10, 0.0)
+    G = torch.zeros(rows * n + off, dtype=torch.complex64, device="cuda")[off:].view(rows, n)
+    G.copy_(torch.from_numpy(np.tile(row, (rows, 1)).astype(np.complex64)))
+    x = torch.zeros(rows * n + off, dtype=torch.complex64, device="cuda")[off:].view(rows, n)
+    _, gc = plan.backward(x, G, want_dx=False)
+    want = rows * row.sum()
+    blocks = -(-rows * -(-n // 256) // 4)
+    assert abs(complex(gc[L].item()) - want) <= 2 * 2.0 ** -24 * (1024.0 * rows + blocks), (gc[L], want)
+    assert torch.count_nonzero(gc[:L]) == 0
