@@ -42,7 +42,7 @@ static const LnTable &ln_table()
 static hipError_t ln_run(int mode, const dpd_plan *P, const dpd_plan *A, const dpd_plan *B, hipStream_t hs,
                          const void *coeffs_dev, const void *x, const void *z, const void *grad_y, void *grad_z,
                          int64_t rows, int64_t n, int64_t ld, float scale, float *lpart, float *gpart, int32_t *step,
-                         int *nblk)
+                         bool fine, int *nblk)
 {
     *nblk = 0;
     const int64_t N = rows * n;
@@ -64,6 +64,8 @@ static hipError_t ln_run(int mode, const dpd_plan *P, const dpd_plan *A, const d
     p.tpr = (n + kLnChunk - 1) / kLnChunk;
     p.scale = scale;
     p.gscale = (float)(2.0 * scale / (double)N);
+    p.fine = fine;
+    p.flush = fine ? (int32_t)std::min<int64_t>(std::max<int64_t>(N >> 18, kLnS + 1), 64) : kLnFlush;
     p.step = step;
     const int NI = P->map.NI, L = P->map.L;
     const int64_t cap = (int64_t)num_cus() * ln_blocks(kLnBoth, 4 * L * NI + 2);
@@ -179,7 +181,7 @@ DPD_EXPORT dpd_status dpd_transmit_loss_grad(dpd_plan *P, const dpd_plan *A, con
     hipError_t e = hipSuccess;
     if (N > 0)
         e = ln_run(kLnFwd, P, A, B, hs, coeffs_dev, x, z, grad_y, nullptr, rows, n, ld, scale, (float *)ws, nullptr,
-                   nullptr, &nblk);
+                   nullptr, false, &nblk);
     if (e != hipSuccess) return hip_fail(e);
     if (loss_dev != nullptr) {
         e = launch_loss_finalize((const float *)ws, nblk, N > 0 ? 1.0 / (double)N : 0.0, loss_dev, hs);
@@ -224,11 +226,12 @@ DPD_EXPORT dpd_status dpd_transmit_backward(const dpd_plan *P, const dpd_plan *A
         return dpd_backward(const_cast<dpd_plan *>(P), stream, nullptr, x, grad_z, nullptr, grad_coeffs, rows, n,
                             ld, ws, ws_bytes);
     }
+    const bool fine = (uintptr_t)x % 16 != 0 || (uintptr_t)grad_z % 16 != 0 || (rows > 1 && ld % 2 != 0);
     int nblk = 0;
     hipError_t e = hipSuccess;
     if (N > 0)
         e = ln_run(kLnBwd, P, A, B, hs, nullptr, x, z, grad_y, grad_z, rows, n, ld, 0.f, nullptr, (float *)ws, nullptr,
-                   &nblk);
+                   fine, &nblk);
     if (e != hipSuccess) return hip_fail(e);
     e = launch_bwd_finalize((const float *)ws, nblk, P->map, (float2 *)grad_coeffs, hs);
     return e == hipSuccess ? DPD_OK : hip_fail(e);
@@ -286,7 +289,8 @@ static dpd_status learn_step(dpd_plan *P, const dpd_plan *A, const dpd_plan *B, 
     int nblk = 0;
     hipError_t e;
     if (N > 0) {
-        e = ln_run(kLnBoth, P, A, B, hs, coeffs_dev, x, z, grad_y, nullptr, rows, n, ld, scale, lp, dc, step_dev, &nblk);
+        e = ln_run(kLnBoth, P, A, B, hs, coeffs_dev, x, z, grad_y, nullptr, rows, n, ld, scale, lp, dc, step_dev,
+                   false, &nblk);
     } else {
         if (step_dev != nullptr) hipLaunchKernelGGL(step_advance, dim3(1), dim3(1), 0, hs, step_dev);
         e = hipGetLastError();

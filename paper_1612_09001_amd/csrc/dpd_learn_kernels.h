@@ -30,8 +30,11 @@
 // inside a row evaluates the L + 3 samples before it directly, one per lane.
 // Samples past a row's end are zeros in x and contribute nothing (dE/dy = 0).
 //
-// The per-lane FP32 sums of the gradient cover at most 128 samples, then go to
-// the wave's FP64 totals; loss and gradient leave as one FP32 partial per block.
+// The per-lane FP32 sums of the gradient cover at most 128 samples, are added up
+// over the wave in FP32 and go to its FP64 totals; for rows at odd 8-byte starts or
+// strides ("fine", as in dpd_backward) they cover at most 64 samples, one per 2^18
+// of the input but at least a chunk's, and are added up in FP64.  Loss and gradient
+// leave as one FP32 partial per block.
 #pragma once
 
 #include "dpd_bwd_kernels.h"
@@ -46,7 +49,7 @@ constexpr int kLnMaxNI = 5;              // predistorter: orders up to 9
 constexpr int kLnMaxL = kSpecL;          // predistorter: up to 8 taps
 constexpr int kLnS = 8;                  // samples per lane
 constexpr int kLnChunk = 64 * kLnS;      // samples per wave chunk
-constexpr int kLnFlush = 128 / kLnS;     // chunks per FP32 gradient sum
+constexpr int kLnFlush = 128;            // samples per FP32 gradient sum of a lane (at most)
 enum { kLnFwd = 0, kLnBwd = 1, kLnBoth = 2, kLnModes = 3 };
 
 struct LnParams {
@@ -62,6 +65,8 @@ struct LnParams {
     int64_t rows, n, ld;
     int64_t tpr;             // chunks per row
     float scale, gscale;
+    int32_t flush;           // samples that a lane's FP32 gradient sums cover at most
+    int32_t fine;            // kLnBwd: the sums over a wave's lanes in FP64 (else FP32)
     int32_t *step;           // learning-step counter advanced by one (nullptr: none)
 };
 
@@ -231,7 +236,10 @@ __global__ void __launch_bounds__(kBlock, ln_blocks(MODE, 4 * L * NI + 2)) learn
     for (int g = 0; g < NGT; ++g) tot[g] = 0.0;
     const auto flush = [&]() {
         if constexpr (GRAD) {
-            wave_sums_into<float, E>(acc, tot, lane);
+            if (READ && p.fine)
+                wave_sums_into<double, E>(acc, tot, lane);
+            else
+                wave_sums_into<float, E>(acc, tot, lane);
 #pragma unroll
             for (int e = 0; e < E; ++e) acc[e] = 0.f;
         }
@@ -338,7 +346,7 @@ __global__ void __launch_bounds__(kBlock, ln_blocks(MODE, 4 * L * NI + 2)) learn
     // t0 - 2, then at t0 - 1), and G at t0 - D + lane (lanes < L - 1)
     float cz[4] = {0.f, 0.f, 0.f, 0.f}, cg[4] = {0.f, 0.f, 0.f, 0.f};
     float2 carry = make_float2(0.f, 0.f);
-    int chunks = 0;
+    int held = 0;   // samples in the FP32 sums
 
     // the samples before a run that starts inside a row, one per lane: lane j
     // (< L + 3) takes t0 - (L + 3) + j
@@ -400,6 +408,14 @@ __global__ void __launch_bounds__(kBlock, ln_blocks(MODE, 4 * L * NI + 2)) learn
     // one staged chunk
     const auto compute = [&](int64_t row, int64_t t0, bool last) {
         const int64_t base = row * p.ld;
+        if constexpr (GRAD) {
+            const int more = S + (last ? 1 : 0);
+            if (held + more > p.flush) {
+                flush();
+                held = 0;
+            }
+            held += more;
+        }
         float zr[S], zi[S], gr[S], gi[S];
         constexpr int ZW = S + LB - 1;
         float2 uu[ZW];   // u at 8l - 2 ..
@@ -555,10 +571,6 @@ __global__ void __launch_bounds__(kBlock, ln_blocks(MODE, 4 * L * NI + 2)) learn
                 va[0] = q.x;
                 vb[0] = q.y;
                 ln_accumulate<NI, L, 1>(acc, ga, gb, va, vb);
-            }
-            if (++chunks == kLnFlush) {
-                flush();
-                chunks = 0;
             }
         }
         if (last) {

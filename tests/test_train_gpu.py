@@ -390,3 +390,34 @@ def test_gradient_at_row_ends(torch, orc, orders, taps):
         g = ref.cpu().numpy().reshape(rows, n).astype(np.complex128)
         want = sum(orc.backward(host[0][r], *orders, taps, h0, g[r], want_dx=False)[1] for r in range(rows))
         assert_dcoef(gc.cpu().numpy(), want, "n=%d" % n)
+
+
+def test_gradient_sums_of_odd_rows(torch):
+    """The coefficient gradient of rows at an odd stride is summed over a wave's
+    lanes in FP64.  With stages that are the identity dE/dz is dE/dy, and dE/dc =
+    sum dE/dy: +-1024, the sign alternating every eight samples, and 2^-10 more on
+    the first eight of every 512.  The FP32 sums of a lane are exact; their sum over
+    64 lanes in FP32 reaches 2^17 before it cancels and loses the 2^-7.  What
+    remains is the rounding of each block's partial (at most 16 * 1024 where a run
+    of chunks starts or ends in a row, else a few 2^-7) and of the result."""
+    from paper_1612_09001_amd import dpd
+
+    rows, n, L = 3, 10241, 6
+    one = np.zeros(10, dtype=np.complex64)
+    one[0] = 1.0
+    P = dpd.Plan([1], [], L, np.ones(L + 1, dtype=np.complex64))
+    A, B = dpd.Plan([1], [1], 1, one[:3]), dpd.Plan([1, 3, 5], [], 3, one)
+    m = np.arange(n)
+    row = np.where((m // 8) % 2 == 0, 1024.0, -1024.0) + np.where(m % 512 < 8, 2.0 ** -10, 0.0)
+    gy = torch.from_numpy(np.tile(row, (rows, 1)).astype(np.complex64)).cuda()
+    x, z, gz = torch.zeros_like(gy), torch.full_like(gy, 0.25), torch.empty_like(gy)
+    gc = torch.empty(P.K, dtype=torch.complex64, device="cuda")
+    wsb = dpd.dpd_backward_ws_size(P.handle, rows, n)
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+    ptr = lambda t: t.data_ptr()
+    dpd.dpd_transmit_backward(P.handle, A.handle, B.handle, dpd.current_stream(), ptr(x), ptr(z), ptr(gy), ptr(gz), ptr(gc),
+                              rows, n, n, ptr(ws), wsb)
+    assert torch.equal(gz, gy)
+    want = rows * row.sum()
+    blocks = -(-rows * -(-n // 512) // 4)
+    assert abs(complex(gc[L].item()) - want) <= 2 * 2.0 ** -24 * (16 * 1024.0 * (rows + blocks) + abs(want)), (gc[L], want)
