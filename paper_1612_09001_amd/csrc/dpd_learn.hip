@@ -34,11 +34,28 @@ static const LnTable &ln_table()
     return t;
 }
 
+// How a pass walks the rows.  Four samples per lane: half the registers of a chunk's
+// windows and half its chain (64 rows of 2^18 samples, four against eight: one pass
+// 145 us and 139 at NI = 4, L = 6, 165 and 199 at L = 8, where eight spills; the
+// backward pass 97 and 100, 107 and 116; 4 x 4096: 15.6 and 18.2, 11.6 and 13.2).
+// Eight, which reads a lane's window again half as often, where one block per CU
+// has room for it (NI = 5, L = 8: one pass 255 and 270 us, backward 149 and 158) and
+// waves have more than a chunk or two (4 x 4096: 18.6 and 23.2), and in the forward
+// pass on rows of any length, whose sums no other pass has to match.
+static int ln_walk(int mode, int64_t rows, int64_t n, int E)
+{
+    if (n % 256 != 0) return mode == kLnBwd ? kLn4Any : kLn8Any;
+    return ln_blocks(kLnBoth, E) == 1 && n % 512 == 0 && rows * n > (int64_t)1 << 19 ? kLn8 : kLn4;
+}
+
 // One pass over the data; *nblk receives the number of blocks (and partials).
-// One round of resident blocks, the same in every mode -- the blocks per CU
-// that the kernels with a gradient are built for -- so that the partial sums,
-// and with them loss and gradient, come out the same whether the step runs as
-// one pass or two.  Arguments already validated.
+// One round of resident blocks, on rows of whole 256s the same in every mode --
+// the blocks per CU that the kernels with a gradient are built for -- so that the
+// partial sums, and with them loss and gradient, come out the same whether the step
+// runs as one pass or two.  (With more than 130 accumulators that is one block per
+// CU: the forward pass alone would be faster with two, 98 us against 122 on 64 rows
+// of 2^18 at NI = 5, L = 7; the step would then take 245 us for 237.)  Arguments
+// already validated.
 static hipError_t ln_run(int mode, const dpd_plan *P, const dpd_plan *A, const dpd_plan *B, hipStream_t hs,
                          const void *coeffs_dev, const void *x, const void *z, const void *grad_y, void *grad_z,
                          int64_t rows, int64_t n, int64_t ld, float scale, float *lpart, float *gpart, int32_t *step,
@@ -61,17 +78,18 @@ static hipError_t ln_run(int mode, const dpd_plan *P, const dpd_plan *A, const d
     p.rows = rows;
     p.n = n;
     p.ld = rows > 1 ? ld : n;
-    p.tpr = (n + kLnChunk - 1) / kLnChunk;
+    const int NI = P->map.NI, L = P->map.L, E = 4 * L * NI + 2;
+    const int walk = ln_walk(mode, rows, n, E), S = ln_s(walk), C = 64 * S;
+    p.tpr = (n + C - 1) / C;
     p.scale = scale;
     p.gscale = (float)(2.0 * scale / (double)N);
     p.fine = fine;
-    p.flush = fine ? (int32_t)std::min<int64_t>(std::max<int64_t>(N >> 18, kLnS + 1), 64) : kLnFlush;
+    p.flush = fine ? (int32_t)std::min<int64_t>(std::max<int64_t>(N >> 18, S + 1), 64) : kLnFlush;
     p.step = step;
-    const int NI = P->map.NI, L = P->map.L;
-    const int64_t cap = (int64_t)num_cus() * ln_blocks(kLnBoth, 4 * L * NI + 2);
+    const int64_t cap = (int64_t)num_cus() * ln_blocks(n % 256 == 0 ? kLnBoth : mode, E);
     const int grid = (int)std::max<int64_t>(
         1, std::min<int64_t>(std::min<int64_t>(kLossBlocks, cap), (rows * p.tpr + kBlock / 64 - 1) / (kBlock / 64)));
-    const hipError_t e = ln_table().fn[NI - 1][L - 1][n % kLnChunk != 0][mode](p, hs, grid);
+    const hipError_t e = ln_table().fn[NI - 1][L - 1][walk][mode](p, hs, grid);
     if (e == hipSuccess) *nblk = grid;
     return e;
 }

@@ -8,24 +8,24 @@
 //   kLnFwd   x -> z, E, dE/dy
 //   kLnBwd   x, z, dE/dy -> coefficient gradient (and dE/dz)
 //   kLnBoth  x -> z, E, dE/dy and the coefficient gradient: nothing but x is read
-// All three walk the data in the same way and use the same arithmetic in the
-// same order, so kLnBoth gives the bits of the other two.
+// On rows of whole 256s all three walk the data in the same way and use the same
+// arithmetic in the same order, so kLnBoth gives the bits of the other two.
 //
-// What bounds it: VALU issue (about 300 instructions per sample against 24
+// What bounds it: VALU issue (about 330 instructions per sample against 24
 // bytes), so every value is computed once and the two passes as one save the
 // second pass's loads, staging and stage A.  Measured on 64 rows of 2^18 samples
-// (a whole step with its finalisation): NI = 4, L = 6 151 us, NI = 2, L = 2 99
-// us; as two kernels, 48 bytes per sample, 196 and 161 us.  Rows that are not
-// whole chunks (16 x 40001, L = 6): 38 us against 186 us in four passes.
+// (a whole step with its finalisation): NI = 4, L = 6 144 us, NI = 4, L = 8 163, NI =
+// 2, L = 2 97; as two calls of 24 bytes per sample each 185, 203 and 154 us.  Rows that
+// are not whole 256s (16 x 40001, L = 6): 39 us.
 //
-// Each wave takes a contiguous run of 512-sample chunks of the flattened rows
-// and walks it forward.  Lane l filters samples 8l .. 8l+7 of a chunk; z and
-// dE/dy at the two samples before them, which stage B's memory needs, come from
+// Each wave takes a contiguous run of chunks of 64 S samples of the flattened rows
+// and walks it forward.  Lane l filters S samples S l .. S l + S - 1 of a chunk; z
+// and dE/dy at the two samples before them, which stage B's memory needs, come from
 // lane l - 1 by a DPP shift, for lane 0 from lane 63 of the chunk before.  The
 // adjoint looks ahead, so it trails: G needs dE/dy two samples on and is formed
-// for samples 8l - 2 .. 8l + 5; the gradient needs G up to L - 1 samples on and
-// takes the basis at 8l - (L + 1) + 0 .. 7, with G through LDS (its first L - 1
-// values are the last of the chunk before).  A row's last chunk is followed by
+// for samples S l - 2 .. S l + S - 3; the gradient needs G up to L - 1 samples on
+// and takes the basis at S l - (L + 1) + 0 .. S - 1, with G through LDS (its first L
+// - 1 values are the last of the chunk before).  A row's last chunk is followed by
 // the L + 1 samples still open, with zeros past the row end.  A run that starts
 // inside a row evaluates the L + 3 samples before it directly, one per lane.
 // Samples past a row's end are zeros in x and contribute nothing (dE/dy = 0).
@@ -47,10 +47,12 @@ namespace dpd {
 constexpr int kLnNIB = 3, kLnLB = 3;     // stage B: orders {1,3,5}, 3 taps
 constexpr int kLnMaxNI = 5;              // predistorter: orders up to 9
 constexpr int kLnMaxL = kSpecL;          // predistorter: up to 8 taps
-constexpr int kLnS = 8;                  // samples per lane
-constexpr int kLnChunk = 64 * kLnS;      // samples per wave chunk
 constexpr int kLnFlush = 128;            // samples per FP32 gradient sum of a lane (at most)
 enum { kLnFwd = 0, kLnBwd = 1, kLnBoth = 2, kLnModes = 3 };
+// Walks: four samples per lane (chunks of 256) or eight, rows of whole chunks or
+// of any length.
+enum { kLn4 = 0, kLn4Any = 1, kLn8 = 2, kLn8Any = 3, kLnWalks = 4 };
+constexpr int ln_s(int walk) { return walk < kLn8 ? 4 : 8; }
 
 struct LnParams {
     const float *M;          // predistorter table (used when raw is null)
@@ -72,9 +74,7 @@ struct LnParams {
 
 typedef hipError_t (*LnLaunch)(const LnParams &, hipStream_t, int grid);
 struct LnTable {
-    // [rows of whole chunks or not][mode]
-    LnLaunch fn[kLnMaxNI][kLnMaxL][2][kLnModes];
-    const void *kern[kLnMaxNI][kLnMaxL][2][kLnModes];
+    LnLaunch fn[kLnMaxNI][kLnMaxL][kLnWalks][kLnModes];   // nullptr: not built
 };
 void register_learn_ni1(LnTable &);
 void register_learn_ni2(LnTable &);
@@ -187,17 +187,20 @@ __device__ __forceinline__ void ln_accumulate(float (&acc)[4 * L * NI + 2], cons
 }
 
 // Blocks per CU the registers are held to: two, one where the gradient's
-// accumulators alone take more than half of 256 (the step at NI = 4, L = 8, 130
-// accumulators: 200 us with two, 222 with one; NI = 5, L = 7, 142: 269 and 240).
+// accumulators alone take more than half of 256 (the step at NI = 5, L = 7, 142
+// accumulators, 64 rows of 2^18: 286 us with two, spilling, and 237 with one).  With
+// four samples per lane nothing spills up to 130, but for one register in the
+// backward pass at NI = 5, L = 6.
 constexpr int ln_blocks(int mode, int E) { return mode == kLnFwd || E <= 130 ? 2 : 1; }
 
-template <int NI, int L, int MODE, bool RAGGED>
+template <int NI, int L, int MODE, int WALK>
 __global__ void __launch_bounds__(kBlock, ln_blocks(MODE, 4 * L * NI + 2)) learn_kernel(LnParams p)
 {
+    constexpr bool RAGGED = WALK == kLn8Any || WALK == kLn4Any;
     constexpr bool FWD = MODE != kLnBwd, GRAD = MODE != kLnFwd, READ = MODE == kLnBwd;
     constexpr int LB = kLnLB, NB = 4 * kLnLB * kLnNIB + 2;
     static_assert(LB == 3, "two samples are handed on between lanes and chunks");
-    constexpr int S = kLnS, C = kLnChunk, NV = S / 2, WAVES = kBlock / 64;
+    constexpr int S = ln_s(WALK), C = 64 * S, NV = S / 2, WAVES = kBlock / 64;
     constexpr int D = L + 1;                         // samples the gradient trails
     constexpr int HX = GRAD ? D : L - 1;             // samples of x before the chunk
     using PL = PadLayout<HX + 1, S>;
@@ -434,8 +437,10 @@ __global__ void __launch_bounds__(kBlock, ln_blocks(MODE, 4 * L * NI + 2)) learn
             asm volatile("" : "+v"(zo));
             fir_outputs_lds<NI, L, S>(a, b, sw, mtab + zo, zr, zi);
         } else {
+            // the two samples that the next lane needs; the others are read when
+            // their turn comes
 #pragma unroll
-            for (int i = 0; i < S; ++i) {
+            for (int i = S - 2; i < S; ++i) {
                 const float2 v = O[lane * (S + 1) + i], g = Y[lane * (S + 1) + i];
                 zr[i] = v.x;
                 zi[i] = v.y;
@@ -453,16 +458,16 @@ __global__ void __launch_bounds__(kBlock, ln_blocks(MODE, 4 * L * NI + 2)) learn
         cz[1] = lane_of(zi[S - 2], 63);
         cz[2] = lane_of(zr[S - 1], 63);
         cz[3] = lane_of(zi[S - 1], 63);
-#pragma unroll
-        for (int w = 0; w < ZW; ++w) {
-            const float2 u = w < LB - 1 ? ln_stage_a(ta, zh[2 * w], zh[2 * w + 1])
-                                        : ln_stage_a(ta, zr[w - (LB - 1)], zi[w - (LB - 1)]);
-            // stage B sees zeros before the row start
-            const bool none = t0 == 0 && lane == 0 && w < LB - 1;
-            uu[w] = none ? make_float2(0.f, 0.f) : u;
-        }
-        __builtin_amdgcn_sched_barrier(0);
         if constexpr (FWD) {
+#pragma unroll
+            for (int w = 0; w < ZW; ++w) {
+                const float2 u = w < LB - 1 ? ln_stage_a(ta, zh[2 * w], zh[2 * w + 1])
+                                            : ln_stage_a(ta, zr[w - (LB - 1)], zi[w - (LB - 1)]);
+                // stage B sees zeros before the row start
+                const bool none = t0 == 0 && lane == 0 && w < LB - 1;
+                uu[w] = none ? make_float2(0.f, 0.f) : u;
+            }
+            __builtin_amdgcn_sched_barrier(0);
             float su[ZW];
 #pragma unroll
             for (int w = 0; w < ZW; ++w) su[w] = __builtin_fmaf(uu[w].x, uu[w].x, uu[w].y * uu[w].y);
@@ -490,17 +495,41 @@ __global__ void __launch_bounds__(kBlock, ln_blocks(MODE, 4 * L * NI + 2)) learn
             cg[1] = lane_of(gi[S - 2], 63);
             cg[2] = lane_of(gr[S - 1], 63);
             cg[3] = lane_of(gi[S - 1], 63);
-        __builtin_amdgcn_sched_barrier(0);
-            float2 g[ZW], G[S];
+            __builtin_amdgcn_sched_barrier(0);
+            // kLnBwd, whose three prefetched streams leave few registers, takes four
+            // samples at a time, z and dE/dy from LDS
+            constexpr int NG = READ ? 4 : S;
+            float2 G[S];
 #pragma unroll
-            for (int w = 0; w < ZW; ++w)
-                g[w] = w < LB - 1 ? make_float2(gh[2 * w], gh[2 * w + 1])
-                                  : make_float2(gr[w - (LB - 1)], gi[w - (LB - 1)]);
+            for (int i0 = 0; i0 < S; i0 += NG) {
+                float2 g[NG + LB - 1];
 #pragma unroll
-            for (int i = 0; i < S; ++i) {
-                const float2 v = ln_adjoint(ta, tb, uu[i], g + i);
-                const bool none = t0 == 0 && lane == 0 && i < LB - 1;   // before the row
-                G[i] = none ? make_float2(0.f, 0.f) : v;
+                for (int w = 0; w < NG + LB - 1; ++w) {
+                    const int m = i0 + w - (LB - 1);
+                    g[w] = m < 0  ? make_float2(gh[2 * (m + LB - 1)], gh[2 * (m + LB - 1) + 1])
+                           : READ ? Y[lane * (S + 1) + m]
+                                  : make_float2(gr[m], gi[m]);
+                }
+#pragma unroll
+                for (int i = 0; i < NG; ++i) {
+                    const int m = i0 + i - (LB - 1);
+                    float2 u;
+                    if constexpr (READ) {
+                        const float2 v = m < 0 ? make_float2(zh[2 * (m + LB - 1)], zh[2 * (m + LB - 1) + 1])
+                                               : O[lane * (S + 1) + m];
+                        u = ln_stage_a(ta, v.x, v.y);
+                    } else {
+                        u = uu[i0 + i];
+                    }
+                    const float2 v = ln_adjoint(ta, tb, u, g + i);
+                    const bool none = t0 == 0 && lane == 0 && m < 0;   // before the row
+                    G[i0 + i] = none ? make_float2(0.f, 0.f) : v;
+                }
+                if constexpr (READ) {
+#pragma unroll
+                    for (int i = 0; i < NG; ++i) asm volatile("" ::"v"(G[i0 + i].x), "v"(G[i0 + i].y));
+                    __builtin_amdgcn_sched_barrier(0);
+                }
             }
             // G into LDS: slot q is sample t0 - D + q
             wave_lds_order();
@@ -509,7 +538,7 @@ __global__ void __launch_bounds__(kBlock, ln_blocks(MODE, 4 * L * NI + 2)) learn
             if (L > 1 && lane < L - 1) O[oslot(lane)] = carry;
             wave_lds_order();
             if constexpr (L > 1) {
-                const float2 v = O[oslot(C) + (lane < L - 1 ? lane : 0)];   // slots C .. C + L - 2: one pad group
+                const float2 v = O[oslot(C + (lane < L - 1 ? lane : 0))];
                 carry = lane < L - 1 ? v : make_float2(0.f, 0.f);
             }
             if (READ && p.gz != nullptr) {
@@ -525,21 +554,26 @@ __global__ void __launch_bounds__(kBlock, ln_blocks(MODE, 4 * L * NI + 2)) learn
                         gzr[m] = u;
                 }
             }
-            {
-                float ga[W], gb[W], va[S], vb[S];
+            // kLnBwd two samples at a time, for its registers (the sums come in the
+            // same order whatever the piece; NI = 4, L = 6, 64 rows of 2^18: 97 us, four
+            // at a time 109)
+            constexpr int NA = READ ? 2 : S;
 #pragma unroll
-                for (int w = 0; w < W; ++w) {
-                    const float2 v = O[oslot(w) + lane * (S + 1)];
+            for (int i0 = 0; i0 < S; i0 += NA) {
+                float ga[NA + L - 1], gb[NA + L - 1], va[NA], vb[NA];
+#pragma unroll
+                for (int w = 0; w < NA + L - 1; ++w) {
+                    const float2 v = O[oslot(i0 + w) + lane * (S + 1)];
                     ga[w] = v.x;
                     gb[w] = v.y;
                 }
 #pragma unroll
-                for (int i = 0; i < S; ++i) {
-                    const float2 v = X[lane * (S + 1) + PL::slot(i - D)];
+                for (int i = 0; i < NA; ++i) {
+                    const float2 v = X[lane * (S + 1) + PL::slot(i0 + i - D)];
                     va[i] = v.x;
                     vb[i] = v.y;
                 }
-                ln_accumulate<NI, L, S>(acc, ga, gb, va, vb);
+                ln_accumulate<NI, L, NA>(acc, ga, gb, va, vb);
             }
             if (last) {
                 // the row's last D samples, one per lane, with the two values of
@@ -629,29 +663,26 @@ __global__ void __launch_bounds__(kBlock, ln_blocks(MODE, 4 * L * NI + 2)) learn
     }
 }
 
-template <int NI, int L, int MODE, bool RAGGED>
+template <int NI, int L, int MODE, int WALK>
 hipError_t launch_learn(const LnParams &p, hipStream_t stream, int grid)
 {
-    hipLaunchKernelGGL((learn_kernel<NI, L, MODE, RAGGED>), dim3((uint32_t)grid), dim3(kBlock), 0, stream, p);
+    hipLaunchKernelGGL((learn_kernel<NI, L, MODE, WALK>), dim3((uint32_t)grid), dim3(kBlock), 0, stream, p);
     return hipGetLastError();
 }
 
-template <int NI, int L, int MODE, bool RAGGED>
-void register_learn_mode(LnTable &t)
+template <int NI, int L, int WALK, int... MODE>
+void register_learn_walk(LnTable &t)
 {
-    t.fn[NI - 1][L - 1][RAGGED][MODE] = &launch_learn<NI, L, MODE, RAGGED>;
-    t.kern[NI - 1][L - 1][RAGGED][MODE] = (const void *)&learn_kernel<NI, L, MODE, RAGGED>;
+    ((t.fn[NI - 1][L - 1][WALK][MODE] = &launch_learn<NI, L, MODE, WALK>), ...);
 }
 
 template <int NI, int L>
 void register_learn_one(LnTable &t)
 {
-    register_learn_mode<NI, L, kLnFwd, false>(t);
-    register_learn_mode<NI, L, kLnBwd, false>(t);
-    register_learn_mode<NI, L, kLnBoth, false>(t);
-    register_learn_mode<NI, L, kLnFwd, true>(t);
-    register_learn_mode<NI, L, kLnBwd, true>(t);
-    register_learn_mode<NI, L, kLnBoth, true>(t);
+    register_learn_walk<NI, L, kLn4, kLnFwd, kLnBwd, kLnBoth>(t);
+    register_learn_walk<NI, L, kLn4Any, kLnBwd>(t);
+    register_learn_walk<NI, L, kLn8Any, kLnFwd>(t);
+    if constexpr (ln_blocks(kLnBoth, 4 * L * NI + 2) == 1) register_learn_walk<NI, L, kLn8, kLnFwd, kLnBwd, kLnBoth>(t);
 }
 
 }  // namespace dpd

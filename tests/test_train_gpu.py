@@ -421,3 +421,37 @@ def test_gradient_sums_of_odd_rows(torch):
     want = rows * row.sum()
     blocks = -(-rows * -(-n // 512) // 4)
     assert abs(complex(gc[L].item()) - want) <= 2 * 2.0 ** -24 * (16 * 1024.0 * (rows + blocks) + abs(want)), (gc[L], want)
+
+
+@pytest.mark.parametrize("orders,taps", [(([1, 3, 5, 7], [1, 3, 5, 7]), 6), (([1, 3, 5, 7, 9], [1]), 8), (([1], [1]), 1)])
+def test_gradient_at_the_ends_of_short_chunks(torch, orc, orders, taps):
+    """As test_gradient_at_row_ends, at row lengths around the samples that a chunk
+    of 256 leaves open, aligned rows and odd starts; dE/dz bit for bit that of
+    dpd_cascade_backward."""
+    from paper_1612_09001_amd import dpd
+    from paper_1612_09001_amd.pa import SyntheticPA
+
+    h0 = signals.aph_coeffs(*orders, taps, config_id=55)
+    P, pa = dpd.Plan(*orders, taps, h0), SyntheticPA()
+    st, rows = dpd.current_stream(), 3
+    ptr = lambda t: t.data_ptr()
+    for n in (4, 246, 247, 250, 253, 254, 255, 256, 257, 258, 265, 767, 1025):
+        host = [np.stack([signals.ofdm_16qam(n, config_id=56 + i, stream_id=r) for r in range(rows)]) for i in range(3)]
+        for off in (0, 1):
+            buf = []
+            for a in host:
+                t = torch.zeros(rows * n + 2, dtype=torch.complex64, device="cuda")
+                t[off:off + rows * n] = torch.from_numpy(a).reshape(-1)
+                buf.append(t[off:])
+            x, z, gy = buf
+            gz, ref = torch.zeros_like(x), torch.zeros_like(x)
+            gc = torch.zeros(P.K, dtype=torch.complex64, device="cuda")
+            wsb = dpd.dpd_backward_ws_size(P.handle, rows, n)
+            ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+            dpd.dpd_transmit_backward(P.handle, pa.iq.handle, pa.pa.handle, st, ptr(x), ptr(z), ptr(gy), ptr(gz), ptr(gc),
+                                      rows, n, n, ptr(ws), wsb)
+            dpd.dpd_cascade_backward(pa.iq.handle, pa.pa.handle, st, ptr(z), ptr(gy), ptr(ref), rows, n, n)
+            assert torch.equal(torch.view_as_real(gz), torch.view_as_real(ref)), (n, off)
+            g = ref.cpu().numpy()[:rows * n].reshape(rows, n).astype(np.complex128)
+            want = sum(orc.backward(host[0][r], *orders, taps, h0, g[r], want_dx=False)[1] for r in range(rows))
+            assert_dcoef(gc.cpu().numpy(), want, "n=%d off=%d" % (n, off))
