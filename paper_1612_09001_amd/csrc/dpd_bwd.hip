@@ -76,6 +76,40 @@ __global__ void __launch_bounds__(kBlock) bwd_finalize(const float *__restrict__
     for (int i = 0; i < c; ++i) gcoef[idx[i]] = g[i];
 }
 
+// dE/dx alone of a memoryless linear plan (NI = L = 1: an I/Q stage), G M^T, on rows
+// shorter than a chunk: one sample per thread and step, so that no lane idles past
+// a row's end (262144 rows of 63 samples 93 us in bwd_kernel, 73 here; 65536 of 255 97
+// and 73).  The bits of bwd_kernel's dE/dx.
+constexpr int kLinearU = 4;   // samples per thread
+__global__ void __launch_bounds__(kBlock) bwd_dx_linear_kernel(BwdParams p)
+{
+    float M[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) M[e] = table_entry(p.M, p.raw, p.map, e);
+    const int64_t total = p.rows * p.n, per = (int64_t)kBlock * kLinearU;
+    for (int64_t at = blockIdx.x * per; at < total; at += gridDim.x * per) {
+        float2 g[kLinearU], v[kLinearU];
+        int64_t to[kLinearU];
+#pragma unroll
+        for (int u = 0; u < kLinearU; ++u) {
+            const int64_t i = at + u * kBlock + threadIdx.x;
+            const int64_t row = total >> 31 ? i / p.n : (int64_t)((uint32_t)i / (uint32_t)p.n);
+            to[u] = i < total ? row * p.ld + (i - row * p.n) : -1;
+            g[u] = v[u] = make_float2(0.f, 0.f);
+            if (to[u] >= 0) {
+                g[u] = p.gz[to[u]];
+                v[u] = p.x[to[u]];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kLinearU; ++u) {
+            const float a = __builtin_fmaf(M[2], g[u].y, M[0] * g[u].x), b = __builtin_fmaf(M[3], g[u].y, M[1] * g[u].x);
+            // + 0 v as in bwd_kernel: not finite where x is not
+            if (to[u] >= 0) p.gx[to[u]] = make_float2(__builtin_fmaf(0.f, v[u].x, a), __builtin_fmaf(0.f, v[u].y, b));
+        }
+    }
+}
+
 static int64_t grid_cap() { return (int64_t)num_cus() * 8; }
 
 size_t bwd_ws_bytes(const CoefMap &map)
@@ -151,7 +185,11 @@ static dpd_status backward_impl(dpd_plan *plan, void *stream, const void *coeffs
     if (!empty) {
         const int64_t C = 64 * kBwdS;
         p.tpr = n / C;
-        const int64_t chunks = rows * ((n + C - 1) / C);
+        // Rows that fit a chunk more than twice are taken several at a time (65536 rows of
+        // 33 samples at NI = L = 4, both gradients: 31 us, a chunk each 76; longer ones
+        // would straddle chunks: 65536 x 254 124 and 100).
+        p.pack = 2 * (n + map.L - 1) <= 240 && ld <= (int64_t)1 << 20;
+        const int64_t chunks = p.pack ? (rows * (n + map.L - 1) + C - 1) / C : rows * ((n + C - 1) / C);
         const BwdTable &t = bwd_table();
         const auto grid_of = [&](int L, int want) {
             const int64_t cap = (int64_t)num_cus() * std::min(8, bwd_occupancy(map.NI, L, want));
@@ -167,7 +205,12 @@ static dpd_status backward_impl(dpd_plan *plan, void *stream, const void *coeffs
         const bool apart = want_dx && want_dc && map.L <= kSpecL &&
                            ((rows * n >= (int64_t)6 << 20 && bwd_occupancy(map.NI, map.L, 2) == 1) ||
                             (p.fine && !bwd_horner(map.NI, true, true)));
-        if (apart) {
+        if (want_dx && !want_dc && map.NI * map.L == 1 && n < 64 * kBwdS) {
+            const int64_t per = (int64_t)kBlock * kLinearU;
+            hipLaunchKernelGGL(bwd_dx_linear_kernel, dim3((uint32_t)std::min<int64_t>((rows * n + per - 1) / per, 1 << 20)),
+                               dim3(kBlock), 0, st, p);
+            e = hipGetLastError();
+        } else if (apart) {
             e = t.fn[map.NI - 1][map.L - 1][0](p, st, grid_of(map.L, 0));
             nblk = grid_of(map.L, 1);
             if (e == hipSuccess) e = t.fn[map.NI - 1][map.L - 1][1](p, st, nblk);

@@ -36,6 +36,7 @@ struct BwdParams {
     int64_t n, ld, rows;
     int64_t tpr;          // full chunks per row (n / (64*S)); the ragged end is extra
     int32_t flush;        // chunks that a lane's FP32 sums cover
+    int32_t pack;         // rows shorter than a chunk: several to a chunk
     int32_t fine;         // the sums over a wave's lanes in FP64 (else FP32)
     const float *M;       // precombined table
     const float2 *raw;    // or the K raw coefficients, precombined by every block
@@ -204,7 +205,7 @@ __global__ void __launch_bounds__(kBlock, bwd_blocks(NI, L, DX && DC)) bwd_kerne
     // the compiler wait for all LDS reads of a window at once (2^24 samples at NI = 4,
     // L = 6, coefficient gradient alone: 69 us and 64).
     const uint32_t nb = gridDim.x;
-    asm volatile("" ::"s"(p.x), "s"(p.gz), "s"(p.n), "s"(p.ld), "s"(p.rows), "s"(p.tpr), "s"(nb));
+    asm volatile("" ::"s"(p.x), "s"(p.gz), "s"(p.n), "s"(p.ld), "s"(p.rows), "s"(p.tpr), "s"(p.pack), "s"(nb));
     if constexpr (DX) asm volatile("" ::"s"(p.gx), "s"(p.M), "s"(p.raw));
     if constexpr (DC) asm volatile("" ::"s"(p.partials), "s"(p.E), "s"(p.flush), "s"(p.fine));
     if constexpr (DX) {
@@ -267,23 +268,60 @@ __global__ void __launch_bounds__(kBlock, bwd_blocks(NI, L, DX && DC)) bwd_kerne
             R.gh = p.gz[row * p.ld + (m < p.n ? m : p.n - 1)];
         }
     };
-    // ragged row end: samples past n read as zero
-    auto load_part = [&](Regs &R, int64_t row, int64_t t0) {
-        const float2 *gr = p.gz + row * p.ld;
-        const float2 *xr = p.x + row * p.ld;
+    // The samples outside full chunks, a chunk at a time: "end" r is what row r has
+    // left.  Packed: the rows one after the other, HS zeros after each, cut into
+    // chunks; end r is chunk r of that.
+    const bool packed = p.pack != 0;
+    const int stride = (int)p.n + HS, lead = (int)p.ld - stride;   // packed: of the rows (both fit)
+    const uint32_t inv = packed ? ((1u << 20) + stride - 1) / stride : 0;
+    struct End {
+        int64_t at;      // first sample of the chunk's first row, or of the rest of the row
+        int skip;        // samples of that row before the chunk
+        int lim, rows;   // samples of a row, rows from this one on
+    };
+    auto end_of = [&](int64_t r) {
+        if (!packed) return End{r * p.ld + p.tpr * C, 0, (int)(p.n - p.tpr * C), 1};
+        const int64_t v = r * C;
+        const int64_t row = v >> 32 ? v / stride : (int64_t)((uint32_t)v / (uint32_t)stride);
+        const int64_t more = p.rows - row;
+        return End{row * p.ld, (int)(v - row * stride), (int)p.n, (int)(more < 1024 ? more : 1024)};
+    };
+    // places of samples j(0), j(1), .. of an end relative to its `at`, -1 where there
+    // is none
+    auto end_at = [&](const End &e, auto j, auto &at) {
+        constexpr int M = sizeof(at) / sizeof(int);
+        if (packed) {
+#pragma unroll
+            for (int i = 0; i < M; ++i) {
+                const int t = e.skip + j(i);
+                const int q = (int)(((uint32_t)t * inv) >> 20);   // t / stride (t below 2^10)
+                at[i] = t - q * stride < e.lim && q < e.rows ? t + q * lead : -1;
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < M; ++i) at[i] = j(i) < e.lim ? j(i) : -1;
+        }
+    };
+    auto load_part = [&](Regs &R, const End &e) {
+        const float2 *gr = p.gz + e.at, *xr = p.x + e.at;
+        int at[S];
+        end_at(e, [&](int i) { return 2 * (lane + 64 * (i / 2)) + i % 2; }, at);
+        const auto get = [&](const float2 *v, int i) { return at[i] >= 0 ? v[(uint32_t)at[i]] : make_float2(0.f, 0.f); };
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
-            const int64_t m = t0 + 2 * (lane + 64 * i);
-            const float2 a = m < p.n ? gr[m] : make_float2(0.f, 0.f);
-            const float2 b = m + 1 < p.n ? gr[m + 1] : make_float2(0.f, 0.f);
+            const float2 a = get(gr, 2 * i), b = get(gr, 2 * i + 1);
             R.g[i] = make_float4(a.x, a.y, b.x, b.y);
-            const float2 c = m < p.n ? xr[m] : make_float2(0.f, 0.f);
-            const float2 d = m + 1 < p.n ? xr[m + 1] : make_float2(0.f, 0.f);
+            const float2 c = get(xr, 2 * i), d = get(xr, 2 * i + 1);
             R.x[i] = make_float4(c.x, c.y, d.x, d.y);
         }
         R.gh = make_float2(0.f, 0.f);
+        if (HS > 0 && packed) {
+            int ah[1];
+            end_at(e, [&](int) { return C + hl; }, ah);
+            if (ah[0] >= 0) R.gh = gr[(uint32_t)ah[0]];
+        }
     };
-    auto stage = [&](const Regs &R, int64_t t0) {
+    auto stage = [&](const Regs &R, bool halo) {
         wave_lds_order();   // the previous chunk's LDS reads are done
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
@@ -293,11 +331,13 @@ __global__ void __launch_bounds__(kBlock, bwd_blocks(NI, L, DX && DC)) bwd_kerne
             X[slot(j)] = make_float2(R.x[i].x, R.x[i].y);
             X[slot(j) + 1] = make_float2(R.x[i].z, R.x[i].w);
         }
-        if (HS > 0 && lane < HS) G[slot(C + lane)] = t0 + C + lane < p.n ? R.gh : make_float2(0.f, 0.f);
+        if (HS > 0 && lane < HS) G[slot(C + lane)] = halo ? R.gh : make_float2(0.f, 0.f);
         wave_lds_order();
     };
-    // gradients of a staged chunk; FULL: every sample of it is inside the row
-    auto compute = [&](int64_t row, int64_t t0, auto full_tag) {
+    // the lane's halo sample of a full chunk at t0 is inside the row
+    auto in_row = [&](int64_t t0) { return t0 + C + lane < p.n; };
+    // gradients of a staged chunk: a full one at e.at, or an end
+    auto compute = [&](const End &e, auto full_tag) {
         constexpr bool FULL = decltype(full_tag)::value;
         // An opaque zero keeps the table reads inside the loop (hoisted, the
         // whole table would occupy registers next to the accumulators).
@@ -424,14 +464,13 @@ __global__ void __launch_bounds__(kBlock, bwd_blocks(NI, L, DX && DC)) bwd_kerne
                 dxa[i] = __builtin_fmaf(q, va[i], Pa[i]);
                 dxb[i] = __builtin_fmaf(q, vb[i], Pb[i]);
             }
-            float2 *gxr = p.gx + row * p.ld;
             if constexpr (FULL) {
                 // back through LDS so every store instruction writes 1 KiB
                 wave_lds_order();
 #pragma unroll
                 for (int i = 0; i < S; ++i) G[slot(lane * S + i)] = make_float2(dxa[i], dxb[i]);
                 wave_lds_order();
-                v4f_s *o4 = reinterpret_cast<v4f_s *>(gxr + t0);
+                v4f_s *o4 = reinterpret_cast<v4f_s *>(p.gx + e.at);
 #pragma unroll
                 for (int i = 0; i < NV; ++i) {
                     const int j = 2 * (lane + 64 * i);
@@ -440,10 +479,12 @@ __global__ void __launch_bounds__(kBlock, bwd_blocks(NI, L, DX && DC)) bwd_kerne
                     __builtin_nontemporal_store(v, o4 + lane + 64 * i);
                 }
             } else {
-                const int64_t m0 = t0 + (int64_t)lane * S;
+                int at[S];
+                end_at(e, [&](int i) { return lane * S + i; }, at);
+                float2 *o = p.gx + e.at;
 #pragma unroll
                 for (int i = 0; i < S; ++i)
-                    if (m0 + i < p.n) gxr[m0 + i] = make_float2(dxa[i], dxb[i]);
+                    if (at[i] >= 0) o[(uint32_t)at[i]] = make_float2(dxa[i], dxb[i]);
             }
         }
     };
@@ -460,9 +501,9 @@ __global__ void __launch_bounds__(kBlock, bwd_blocks(NI, L, DX && DC)) bwd_kerne
         int64_t row = gw / tpr, tix = gw - row * tpr;
         Regs R;
         load_full(R, row, tix * C);
-        stage(R, tix * C);
+        stage(R, in_row(tix * C));
         for (int64_t i = 0; i + 1 < left; ++i) {
-            const int64_t crow = row, ct0 = tix * C;
+            const int64_t cur = row * p.ld + tix * C;
             row += dq;
             tix += dr;
             if (tix >= tpr) {
@@ -470,29 +511,29 @@ __global__ void __launch_bounds__(kBlock, bwd_blocks(NI, L, DX && DC)) bwd_kerne
                 ++row;
             }
             load_full(R, row, tix * C);
-            compute(crow, ct0, BwdTag<true>{});
-            stage(R, tix * C);
+            compute(End{cur, 0, 0, 0}, BwdTag<true>{});
+            stage(R, in_row(tix * C));
             if (++held == p.flush) {
                 flush();
                 held = 0;
             }
         }
-        compute(row, tix * C, BwdTag<true>{});
+        compute(End{row * p.ld + tix * C, 0, 0, 0}, BwdTag<true>{});
         ++held;
     }
-    // ragged row ends continue the round-robin order (chunk c to wave c mod nw)
-    if (p.n > tpr * C) {
-        for (int64_t r = (gw + nw - total % nw) % nw; r < p.rows; r += nw) {
-            Regs R;
-            load_part(R, r, tpr * C);
-            stage(R, tpr * C);
-            if (held == p.flush) {
-                flush();
-                held = 0;
-            }
-            compute(r, tpr * C, BwdTag<false>{});
-            ++held;
+    // the ends continue the round-robin order (chunk c to wave c mod nw)
+    const int64_t ends = packed ? (p.rows * (int64_t)stride - HS + C - 1) / C : p.n > tpr * C ? p.rows : 0;
+    for (int64_t r = (gw + nw - total % nw) % nw; r < ends; r += nw) {
+        Regs R;
+        const End e = end_of(r);
+        load_part(R, e);
+        stage(R, true);
+        if (held == p.flush) {
+            flush();
+            held = 0;
         }
+        compute(e, BwdTag<false>{});
+        ++held;
     }
 
     if constexpr (DC) {

@@ -282,10 +282,10 @@ def test_both_gradients_of_a_long_heavy_input(torch, dpd, over):
         assert_dcoef(gc.cpu().numpy(), gc1.cpu().numpy().astype(np.complex128), "dcoef")
 
 
-@pytest.mark.parametrize("n", [62, 63])
+@pytest.mark.parametrize("n", [62, 63, 300, 301])
 def test_gradient_sums_over_many_short_rows(torch, dpd, n):
-    """Rows shorter than a chunk, some 70 per wave: the FP32 sums of a lane cover at
-    most 128 samples.  x = 1 and G = 1 + 2^-17: FP32 sums of up to 128 of them are
+    """Many rows per wave, shorter than a chunk or ending in a part of one: the FP32
+    sums of a lane cover at most 128 samples.  x = 1 and G = 1 + 2^-17: FP32 sums of up to 128 of them are
     exact (longer ones lose 2^-17 of every sample), after which six FP32 additions
     over the wave (even n; none at odd row starts) and the roundings of a block's
     partial and of the result bound the relative error by 8 u, u = 2^-24."""
@@ -319,3 +319,37 @@ def test_gradient_sums_of_odd_rows_and_long_filters(torch, dpd, L, n, off):
     blocks = -(-rows * -(-n // 256) // 4)
     assert abs(complex(gc[L].item()) - want) <= 2 * 2.0 ** -24 * (1024.0 * rows + blocks), (gc[L], want)
     assert torch.count_nonzero(gc[:L]) == 0
+
+
+@pytest.mark.parametrize("mo,co,L", [([1], [], 1), ([1, 3], [1], 4), ([1, 3, 5, 7], [1, 3, 5, 7], 8), ([1, 3], [1], 16)])
+def test_rows_shorter_than_a_chunk(torch, dpd, orc, mo, co, L):
+    """Rows shorter than 256 samples are taken several to a chunk: lengths around the
+    filter's, fractions of a chunk and one less than it, padded and odd strides;
+    both gradients, dE/dx alone bit for bit, and nothing written between the rows."""
+    h = signals.aph_coeffs(mo, co, L, config_id=96)
+    plan = dpd.Plan(mo, co, L, h)
+    for n, rows, ld in ((1, 1, 1), (1, 700, 1), (2, 300, 3), (L, 130, L), (16, 100, 17), (63, 9, 64), (128, 5, 128), (255, 3, 257)):
+        x = np.stack([signals.ofdm_16qam(n, config_id=96, stream_id=r) for r in range(rows)])
+        G = signals.cgauss((rows, n), config_id=96, stream_id=n)
+        want, rc = np.zeros((rows, n), np.complex128), 0
+        for r in range(rows):
+            want[r], c = orc.backward(x[r], mo, co, L, h, G[r])
+            rc = rc + c
+        def padded(v):
+            t = torch.full((rows, ld), complex(float("nan"), 0.0), dtype=torch.complex64, device="cuda")
+            t[:, :n] = _dev(torch, v)
+            return t
+        xd, gd = padded(x), padded(G)
+        gx = torch.full((rows, ld), complex(7.0, -7.0), dtype=torch.complex64, device="cuda")
+        gc = torch.empty(plan.K, dtype=torch.complex64, device="cuda")
+        ws = torch.empty(dpd.dpd_backward_ws_size(plan.handle, rows, n), dtype=torch.uint8, device="cuda")
+        dpd.dpd_backward(plan.handle, dpd.current_stream(), 0, xd.data_ptr(), gd.data_ptr(), gx.data_ptr(), gc.data_ptr(), rows, n,
+                         ld, ws.data_ptr(), ws.numel())
+        out = gx.cpu().numpy()
+        assert_parity(out[:, :n].reshape(-1), want.reshape(-1), "dx n=%d" % n)
+        assert np.all(out[:, n:] == np.complex64(complex(7.0, -7.0))), n
+        assert_dcoef(gc.cpu().numpy(), rc, "dcoef n=%d" % n)
+        # dE/dx alone (a kernel of its own for a memoryless linear plan)
+        alone = torch.full((rows, ld), complex(7.0, -7.0), dtype=torch.complex64, device="cuda")
+        dpd.dpd_backward(plan.handle, dpd.current_stream(), 0, xd.data_ptr(), gd.data_ptr(), alone.data_ptr(), 0, rows, n, ld, 0, 0)
+        assert np.array_equal(alone.cpu().numpy(), out), n
