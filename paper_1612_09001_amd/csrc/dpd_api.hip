@@ -278,6 +278,18 @@ static dpd_tune fwd_auto(const CoefMap &map, int64_t N)
     return t;
 }
 
+// Rows up to this long (and several of them) go to the one-shot kernel that packs
+// the windows of the rows one after the other: no thread past a row's end, no row
+// left to a wave or a tile of its own.  NI = L = 4: 400000 rows of 9 samples 15 us
+// against 670 (a wave or tile per row), 8192 x 512 13.0 and 13.7, 65536 x 701 155 and
+// 187, 4096 x 5001 51 and 57.  Not long inputs of whole chunks, which the streaming
+// form sweeps in order (65536 x 512 at NI = 4, L = 8: 123 us, packed 131).
+constexpr int64_t kPackRows = 8192;
+static bool fwd_pack(int64_t rows, int64_t n)
+{
+    return rows > 1 && n <= kPackRows && (n % 512 != 0 || rows * n <= (int64_t)10 << 20);
+}
+
 // Forward launch for an already-prepared device table M, with the caller's
 // launch shape or (tune null) fwd_auto's; a history is replaced by the last
 // L - 1 inputs.
@@ -293,7 +305,15 @@ dpd_status run_forward(const CoefMap &map, const dpd_tune *tune_in, const float 
     p.ld = ld;
     p.M = M;
     p.hist = (float2 *)hist;
+    p.rows = rows;
     const FwdTable &t = fwd_table();
+    if (fwd_pack(rows, n) && (tune_in == nullptr || (n < 512 && rows >= 1024))) {
+        const int S = rows * n < (int64_t)1 << 20 || map.NI * map.L <= 9 ? 2 : 4;   // as fwd_auto
+        p.tiles_per_row = (n + S - 1) / S;
+        p.total_tiles = (rows * p.tiles_per_row + kBlock - 1) / kBlock;
+        const hipError_t e = t.rows[map.NI - 1][map.L - 1][S == 4](p, stream, 1);
+        return e == hipSuccess ? DPD_OK : hip_fail(e);
+    }
     const int v = fwd_variant(tune);
     const int64_t T = fwd_tile(map.L, v);
     p.tiles_per_row = (n + T - 1) / T;

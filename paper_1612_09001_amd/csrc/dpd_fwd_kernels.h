@@ -341,7 +341,10 @@ __device__ __forceinline__ void store_outputs(float2 *__restrict__ z, int64_t m0
 // no barrier (3.06 us for 2^16 samples at NI = L = 4 against 3.13).  Larger S:
 // through LDS, whose barrier starts the block's loads together (2^23 samples:
 // 23.6 us against 25.4).
-template <int NI, int L, int S>
+// PACK, for short rows: a tile is kBlock windows of S outputs, the windows of one
+// row after those of the row before, so that no thread is left past a row's end
+// and only a row's first and last windows are loaded sample by sample.
+template <int NI, int L, int S, bool PACK>
 __global__ void __launch_bounds__(kBlock) fwd_tile_kernel(FwdParams p)
 {
     static_assert(S % 2 == 0, "S must be even (16-byte stores)");
@@ -367,14 +370,25 @@ __global__ void __launch_bounds__(kBlock) fwd_tile_kernel(FwdParams p)
 
     for (int64_t step = xcd_remap(blockIdx.x, gridDim.x); step < p.total_tiles; step += gridDim.x) {
         // a 64-bit division is a hundred instructions before the first load
-        const int64_t row = p.total_tiles >> 31 ? step / p.tiles_per_row
-                                                : (int64_t)((uint32_t)step / (uint32_t)p.tiles_per_row);
-        const int64_t t0 = (step - row * p.tiles_per_row) * (int64_t)T;
+        const int64_t at = PACK ? step * kBlock : step;   // window, tile
+        int64_t row = (PACK ? at >> 32 : at >> 31) ? at / p.tiles_per_row
+                                                   : (int64_t)((uint32_t)at / (uint32_t)p.tiles_per_row);
+        int64_t m0;   // first output of this thread
+        bool full;
+        if constexpr (PACK) {
+            const uint32_t w = (uint32_t)(at - row * p.tiles_per_row) + tid, q = w / (uint32_t)p.tiles_per_row;
+            row += q;
+            m0 = (int64_t)(w - q * (uint32_t)p.tiles_per_row) * S;
+            if (row >= p.rows) return;   // the last tile: no barrier follows (no history)
+            full = m0 + S <= p.n;
+        } else {
+            const int64_t t0 = (at - row * p.tiles_per_row) * (int64_t)T;
+            full = t0 + T <= p.n;
+            m0 = t0 + (int64_t)tid * S;
+        }
         const float2 *__restrict__ x = p.in + row * p.ld;
         float2 *__restrict__ z = p.out + row * p.ld;
-        const float2 *hist = row == 0 ? p.hist : nullptr;
-        const bool full = t0 + T <= p.n;
-        const int64_t m0 = t0 + (int64_t)tid * S;   // first output of this thread
+        const float2 *hist = !PACK && row == 0 ? p.hist : nullptr;
 
         float2 raw[WL];
         const int64_t lo = m0 - HP;
@@ -409,7 +423,7 @@ __global__ void __launch_bounds__(kBlock) fwd_tile_kernel(FwdParams p)
         else
             fir_outputs<NI, L, S>(a, b, s, top, M, zr, zi);
         if (m0 < p.n) store_outputs<S>(z, m0, p.n, full, zr, zi);
-        if (L > 1 && p.hist != nullptr && step == 0) {
+        if (!PACK && L > 1 && p.hist != nullptr && step == 0) {
             // a carried history is read by this block alone; replace it once
             // every thread has
             __syncthreads();
@@ -739,7 +753,7 @@ __global__ void __launch_bounds__(kBlock, (fwd_stream_blocks<NI, L>())) fwd_stre
 
 int num_cus();
 
-template <int NI, int L, int S, bool STREAM>
+template <int NI, int L, int S, bool STREAM, bool PACK = false>
 hipError_t launch_fwd(const FwdParams &p, hipStream_t stream, int grid_mult)
 {
     int64_t grid;
@@ -763,7 +777,7 @@ hipError_t launch_fwd(const FwdParams &p, hipStream_t stream, int grid_mult)
     } else {
         const int64_t cap = 1 << 20;
         grid = p.total_tiles < cap ? p.total_tiles : cap;
-        hipLaunchKernelGGL((fwd_tile_kernel<NI, L, S>), dim3((uint32_t)grid), dim3(kBlock), 0,
+        hipLaunchKernelGGL((fwd_tile_kernel<NI, L, S, PACK>), dim3((uint32_t)grid), dim3(kBlock), 0,
                            stream, p);
     }
     return hipGetLastError();
@@ -774,6 +788,8 @@ hipError_t launch_fwd(const FwdParams &p, hipStream_t stream, int grid_mult)
 template <int NI, int L>
 void register_fwd_one(FwdTable &t)
 {
+    t.rows[NI - 1][L - 1][0] = &launch_fwd<NI, L, 2, false, true>;
+    t.rows[NI - 1][L - 1][1] = &launch_fwd<NI, L, 4, false, true>;
     if constexpr (L > kSpecL) {
         for (int v = 0; v < kNumFwdVariants; ++v)
             t.fn[NI - 1][L - 1][v] = (v & 1)  ? &launch_fwd<NI, L, 8, true>

@@ -52,12 +52,14 @@ struct FwdParams {
     const float *M;        // precombined table
     float2 *hist;          // L-1 samples preceding row 0, or nullptr; the kernel leaves the
                            // last L-1 samples of hist ++ in there
+    int64_t rows;          // packed rows, whose tiles_per_row counts windows, total_tiles kBlock of them
 };
 
 typedef hipError_t (*FwdLaunch)(const FwdParams &, hipStream_t, int grid_mult);
 
 struct FwdTable {
     FwdLaunch fn[kSpecNI][kMaxL][kNumFwdVariants];
+    FwdLaunch rows[kSpecNI][kMaxL][2];   // short rows: one-shot at S = 2, 4
 };
 
 // Registration hooks, one per power-level translation unit.

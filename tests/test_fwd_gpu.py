@@ -398,3 +398,29 @@ def test_history_over_odd_chunks(torch, dpd, L, tune):
         want = torch.cat([torch.zeros(L - 1, dtype=torch.complex64, device="cuda"), x[:t]])[-(L - 1):]
         assert torch.equal(torch.view_as_real(hist), torch.view_as_real(want)), t
     assert torch.equal(torch.view_as_real(z), torch.view_as_real(whole))
+
+
+@pytest.mark.parametrize("mo,co,L", [([1, 3, 5, 7], [1, 3, 5, 7], 4), ([1, 3, 5, 7, 9], [1, 3], 12), ([1, 3], [1], 16), ([1], [1], 1)])
+def test_rows_packed_one_after_the_other(torch, dpd, orc, mo, co, L):
+    """Short rows, whose windows are packed: lengths around a window's samples, the
+    filter's and a tile's, few rows and many (both window sizes), padded odd
+    strides at an odd start: the oracle's outputs on the first and last rows, the
+    bits of the shape that a plan is tuned to, nothing written between the rows."""
+    h = signals.aph_coeffs(mo, co, L, config_id=97)
+    plan, tuned = dpd.Plan(mo, co, L, h), dpd.Plan(mo, co, L, h)
+    tuned.set_tune(samples_per_thread=8, stage_lds=1, grid_mult=2)
+    x = _dev(torch, signals.ofdm_16qam((1 << 20) + 40000, config_id=97))
+    for n, rows in ((1, 2), (2, 3), (3, 700), (5, 1023), (15, 300), (16, 9), (17, 500), (255, 7), (512, 3), (513, 5), (1025, 2),
+                    (8191, 2), (1029, 1020), (2047, 513), (8190, 129)):
+        ld = n + 1 + (n & 1)
+        src = x.as_strided((rows, n), (n, 1), 1) if rows * n > 1 << 19 else x.as_strided((rows, n), (ld, 1), 1)
+        ls = n if rows * n > 1 << 19 else ld
+        a, b = (torch.full((rows * ls + 2,), complex(7.0, -7.0), dtype=torch.complex64, device="cuda") for _ in range(2))
+        for p, o in ((plan, a), (tuned, b)):
+            dpd.dpd_apply_rows(p.handle, dpd.current_stream(), src.data_ptr(), o.data_ptr() + 8, rows, n, ls)
+        assert torch.equal(torch.view_as_real(a), torch.view_as_real(b)), (n, rows)
+        body = _host(a)[1:1 + rows * ls].reshape(rows, ls)
+        xs = _host(src)
+        for r in {0, 1, rows - 1}:
+            assert_parity(body[r, :n], orc.forward(xs[r], mo, co, L, h), "n %d row %d" % (n, r))
+        assert np.all(body[:, n:] == np.complex64(complex(7.0, -7.0))) and _host(a)[0] == _host(a)[-1] == np.complex64(complex(7.0, -7.0))
