@@ -278,6 +278,20 @@ static dpd_tune fwd_auto(const CoefMap &map, int64_t N)
     return t;
 }
 
+// Samples in host memory cross the host link, and nothing on the GPU keeps the
+// half of a 64-byte line that a lane's 32 bytes leave: one-shot windows of two
+// samples, whose 16 bytes a lane adjoin its neighbour's (ZeroCopy of 2^22 samples at
+// NI = L = 4: 0.84 ms, four samples 1.32, streaming 0.97).
+static bool in_host_memory(const void *p)
+{
+    hipPointerAttribute_t a;
+    if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+        (void)hipGetLastError();   // memory the runtime does not know
+        return false;
+    }
+    return a.type == hipMemoryTypeHost;
+}
+
 // Rows up to this long (and several of them) go to the one-shot kernel that packs
 // the windows of the rows one after the other: no thread past a row's end, no row
 // left to a wave or a tile of its own.  NI = L = 4: 400000 rows of 9 samples 15 us
@@ -297,7 +311,12 @@ dpd_status run_forward(const CoefMap &map, const dpd_tune *tune_in, const float 
                        const void *in, void *out, int64_t rows, int64_t n, int64_t ld,
                        void *hist)
 {
-    const dpd_tune tune = tune_in != nullptr ? *tune_in : fwd_auto(map, rows * n);
+    dpd_tune tune = tune_in != nullptr ? *tune_in : fwd_auto(map, rows * n);
+    const bool host = tune_in == nullptr && rows * n >= (int64_t)1 << 20 && (in_host_memory(in) || in_host_memory(out));
+    if (host) {
+        tune.stage_lds = 0;
+        tune.samples_per_thread = 2;
+    }
     FwdParams p;
     p.in = (const float2 *)in;
     p.out = (float2 *)out;
@@ -307,7 +326,7 @@ dpd_status run_forward(const CoefMap &map, const dpd_tune *tune_in, const float 
     p.hist = (float2 *)hist;
     p.rows = rows;
     const FwdTable &t = fwd_table();
-    if (fwd_pack(rows, n) && (tune_in == nullptr || (n < 512 && rows >= 1024))) {
+    if (fwd_pack(rows, n) && (tune_in == nullptr ? !host : n < 512 && rows >= 1024)) {
         const int S = rows * n < (int64_t)1 << 20 || map.NI * map.L <= 9 ? 2 : 4;   // as fwd_auto
         p.tiles_per_row = (n + S - 1) / S;
         p.total_tiles = (rows * p.tiles_per_row + kBlock - 1) / kBlock;

@@ -78,3 +78,34 @@ def test_zero_copy_rejects_pageable(torch):
     plan = dpd.Plan([1], [], 2, np.array([1, 0, 0], np.complex64))
     with pytest.raises(ValueError):
         ingest.ZeroCopy(plan).run(torch.zeros(10, dtype=torch.complex64), torch.zeros(10, dtype=torch.complex64))
+
+
+@pytest.mark.parametrize("n", [(1 << 20) - 1, 1 << 20, (11 << 20) + 5])
+@pytest.mark.parametrize("L", [4, 12])
+def test_zero_copy_around_the_size_that_asks_for_the_memory(torch, n, L):
+    """From 2^20 samples on a call looks whether its samples are in host memory and
+    then takes another launch shape: the bits are the device call's with either
+    buffer, or both, in host memory; a call under capture takes the same route."""
+    from paper_1612_09001_amd import dpd, ingest
+
+    mo = [1, 3, 5, 7]
+    plan = dpd.Plan(mo, mo, L, signals.aph_coeffs(mo, mo, L, config_id=83))
+    xd = torch.from_numpy(signals.ofdm_16qam(n, config_id=83)).cuda()
+    xh = xd.cpu().pin_memory()
+    want = torch.view_as_real(plan.apply(xd)).cpu()
+    zh, zd = torch.zeros(n, dtype=torch.complex64).pin_memory(), torch.zeros_like(xd)
+    dx, dz = ingest.device_pointer(xh), ingest.device_pointer(zh)
+    for i, o in ((dx, dz), (dx, zd.data_ptr()), (xd.data_ptr(), dz)):
+        zh.zero_()
+        zd.zero_()
+        dpd.dpd_apply(plan.handle, dpd.current_stream(), i, o, n)
+        torch.cuda.synchronize()
+        got = zd.cpu() if o == zd.data_ptr() else zh
+        assert torch.equal(torch.view_as_real(got), want)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        plan.apply(xd, out=zd)
+    for _ in range(3):
+        zd.zero_()
+        g.replay()
+        assert torch.equal(torch.view_as_real(zd).cpu(), want)
