@@ -808,8 +808,9 @@ __device__ __forceinline__ void ls_panel_load(const double2 *F, int K, int j0, i
     }
 }
 
-// Factors the loaded columns and stores the rows that this wave answers for.
-// Returns 0 or the 1-based column of a pivot that is not positive.
+// Factors the first PC of the loaded columns and stores the rows that this wave
+// answers for.  Returns 0 or the 1-based column of a pivot that is not positive.
+template <int PC>
 __device__ __forceinline__ int ls_panel_factor(double2 *F, double *invd, int K, int j0, int w, int lane,
                                                double2 (&a)[kLsPanel])
 {
@@ -820,7 +821,7 @@ __device__ __forceinline__ int ls_panel_factor(double2 *F, double *invd, int K, 
     // nowhere, and a failed pivot only notes its column.
     int fail = 0;
 #pragma unroll
-    for (int q = 0; q < kLsPanel; ++q) {
+    for (int q = 0; q < PC; ++q) {
         const double piv = ls_bcast(a[q].x, q);
         fail = fail == 0 && j0 + q < K && !(piv > 0.0) ? j0 + q + 1 : fail;
         const double inv = ls_rsqrt(piv);
@@ -828,7 +829,7 @@ __device__ __forceinline__ int ls_panel_factor(double2 *F, double *invd, int K, 
         a[q].x *= inv;
         a[q].y *= inv;
 #pragma unroll
-        for (int c = q + 1; c < kLsPanel; ++c) {
+        for (int c = q + 1; c < PC; ++c) {
             const double cx = ls_bcast(a[q].x, c), cy = ls_bcast(a[q].y, c);   // L[j0 + c][j0 + q]
             a[c].x = fma(-a[q].x, cx, a[c].x);
             a[c].x = fma(-a[q].y, cy, a[c].x);
@@ -838,7 +839,7 @@ __device__ __forceinline__ int ls_panel_factor(double2 *F, double *invd, int K, 
     }
     if (w == 0 && lane < kLsPanel && j0 + lane < K) invd[j0 + lane] = id;
 #pragma unroll
-    for (int q = 0; q < kLsPanel; ++q) {
+    for (int q = 0; q < PC; ++q) {
         const int j = j0 + q, base = j * R - j * (j + 1) / 2;
         if (own && j < K && r >= j) F[base + r] = a[q];
     }
@@ -854,7 +855,9 @@ __device__ __forceinline__ void ls_sub(double2 &acc, double2 a, double2 c)
     acc.y = fma(a.x, c.y, acc.y);
 }
 
-template <int S>
+// PC: columns that a panel is factored in, kLsPanel or, where there is one panel of
+// less, two, four or six (K = 2: 3.6 us against 5.0, K = 4: 4.2 and 5.3).
+template <int S, int PC = kLsPanel>
 __global__ void __launch_bounds__(64 * kLsPanelWaves) ls_solve_panel_kernel(const double2 *__restrict__ A,
                                                                             const double2 *__restrict__ b, int K,
                                                                             double ridge, float2 *__restrict__ h,
@@ -910,7 +913,7 @@ __global__ void __launch_bounds__(64 * kLsPanelWaves) ls_solve_panel_kernel(cons
         if (pw > 1) __syncthreads();   // every wave has the pivot rows before wave 0 stores them
         if (w < pw) {
             __builtin_amdgcn_s_setprio(3);   // the chain before the other wave of its SIMD
-            const int fail = ls_panel_factor(F, invd, K, j0, w, lane, a);
+            const int fail = ls_panel_factor<PC>(F, invd, K, j0, w, lane, a);
             if (w == 0 && lane == 0 && fail != 0) bad = fail;
             __builtin_amdgcn_s_setprio(0);
         } else if (j0 > 0) {
@@ -1442,7 +1445,13 @@ DPD_EXPORT dpd_status dpd_ls_solve(void *stream, int32_t K, const void *A, const
         // the triangle fits one CU's LDS; 64-row slots of a panel: K + 1 rows
         const dim3 blk(64 * kLsPanelWaves);
         const size_t lds = ls_panel_lds(K);
-        if (K < 64)
+        if (K <= 2)
+            hipLaunchKernelGGL((ls_solve_panel_kernel<1, 2>), dim3(1), blk, lds, st, Ad, bd, K, ridge, hd, id);
+        else if (K <= 4)
+            hipLaunchKernelGGL((ls_solve_panel_kernel<1, 4>), dim3(1), blk, lds, st, Ad, bd, K, ridge, hd, id);
+        else if (K <= 6)
+            hipLaunchKernelGGL((ls_solve_panel_kernel<1, 6>), dim3(1), blk, lds, st, Ad, bd, K, ridge, hd, id);
+        else if (K < 64)
             hipLaunchKernelGGL((ls_solve_panel_kernel<1>), dim3(1), blk, lds, st, Ad, bd, K, ridge, hd, id);
         else if (K < 128)
             hipLaunchKernelGGL((ls_solve_panel_kernel<2>), dim3(1), blk, lds, st, Ad, bd, K, ridge, hd, id);

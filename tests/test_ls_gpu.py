@@ -460,3 +460,22 @@ def test_few_slabs_with_an_input_scale(torch, dpd, orders, L, scale):
     K = plan.K
     assert torch.equal(torch.view_as_real(A[:K - 1]), torch.view_as_real(B[:K - 1]))
     assert torch.equal(torch.view_as_real(b), torch.view_as_real(d))
+
+
+@pytest.mark.parametrize("K", [1, 2, 3, 4, 5, 6, 7])
+def test_solve_smallest_systems(torch, dpd, K):
+    """Systems of one panel, factored in as many columns as they take: the residual
+    against numpy's, and the column of a pivot that is not positive."""
+    rng = np.random.default_rng(K)
+    M = rng.standard_normal((2 * K, K)) + 1j * rng.standard_normal((2 * K, K))
+    A, b = M.conj().T @ M, rng.standard_normal(K) + 1j * rng.standard_normal(K)
+    Ad, bd = torch.from_numpy(A).cuda(), torch.from_numpy(b).cuda()
+    h, info = dpd.ls_solve(Ad, bd, 0.0)
+    want = np.linalg.solve(A, b)
+    assert int(info.item()) == 0
+    assert np.linalg.norm(h.cpu().numpy() - want) <= 4 * 2.0 ** -24 * np.linalg.norm(want)   # rounded to complex64
+    for j in range(K):
+        B = Ad.clone()
+        B[j, j] = -1.0
+        h, info = dpd.ls_solve(B, bd, 0.0)
+        assert int(info.item()) == j + 1 and bool(torch.isnan(torch.view_as_real(h)).all()), j
