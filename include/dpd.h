@@ -396,6 +396,8 @@ dpd_status dpd_learn_step_dev(dpd_plan *P, const dpd_plan *A, const dpd_plan *B,
  * copied into the predistorter.
  *
  * dpd_ls_ws_size -- workspace bytes for dpd_ls_normal on rows x n samples.
+ *   Never less for a longer input, up to 6144 samples (rows x n) per compute
+ *   unit: one workspace of the longest serves the shorter ones.
  *   DPD_EUNSUPPORTED if 2K+2 > 192 (K > 95): the Gram kernel holds at most
  *   12 x 12 tiles of 16 x 16.
  *

@@ -1223,17 +1223,24 @@ static int64_t ls_slab(int64_t rows, int64_t n)
     return slab;
 }
 
+// Sizes that never fall as the slabs grow in number, so that a workspace made for
+// a larger input serves a smaller one: the partials of the most blocks that any
+// smaller number of slabs is spread over, and the sums of 256 slabs' 16 groups
+// also where longer groups need fewer.
 static LsWs ls_ws(const LsShape &s, int64_t rows, int64_t n)
 {
     const int64_t slab = ls_slab(rows, n);
     const int64_t spr = (n + slab - 1) / slab;
     const int64_t nslabs = std::max<int64_t>(rows * spr, 1);
     const int64_t group = ls_group(nslabs), groups = (nslabs + group - 1) / group;
+    const int64_t gk = kLsWaves / ls_pair_groups(s.nt);
+    const int64_t parts = std::max(nslabs, std::min<int64_t>(nslabs * gk, 2 * num_cus()));
+    const int64_t sums = nslabs > 256 ? std::max<int64_t>(groups, 16) : groups;
     const int64_t E = (int64_t)s.npairs * 256;
     auto up = [](size_t v) { return (v + 255) & ~(size_t)255; };
     LsWs w;
-    w.partials = up((size_t)(nslabs * ls_sub(s.nt, nslabs) * E) * sizeof(float));
-    w.r1 = up((size_t)(groups * E) * sizeof(double));
+    w.partials = up((size_t)(parts * E) * sizeof(float));
+    w.r1 = up((size_t)(sums * E) * sizeof(double));
     w.total = w.partials + w.r1;
     return w;
 }

@@ -479,3 +479,27 @@ def test_solve_smallest_systems(torch, dpd, K):
         B[j, j] = -1.0
         h, info = dpd.ls_solve(B, bd, 0.0)
         assert int(info.item()) == j + 1 and bool(torch.isnan(torch.view_as_real(h)).all()), j
+
+
+@pytest.mark.parametrize("order,L", [(7, 4), (9, 8)])
+def test_workspace_of_a_longer_input(torch, dpd, order, L):
+    """A workspace sized for a longer input serves a shorter one, with the same
+    bits as its own: sizes never fall with n over the small inputs."""
+    orders = list(range(1, order + 1, 2))
+    plan = dpd.Plan(orders, orders, L, signals.aph_coeffs(orders, orders, L))
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    ns = [1, 1024] + [1024 * s + d for s in (16, 17, cus // 2, cus, 2 * cus, 5 * cus) for d in (0, 1)] + [6144 * cus]
+    sizes = [dpd.dpd_ls_ws_size(plan.handle, 1, n) for n in ns]
+    assert sizes == sorted(sizes)
+    gen = torch.Generator(device="cuda").manual_seed(99)
+    K, st = plan.K, torch.cuda.current_stream().cuda_stream
+    for n, longer in ((512 * cus, 1024 * cus), (1024 * cus, 1024 * cus + 1024)):
+        y, t = (torch.randn(n, dtype=torch.complex64, device="cuda", generator=gen) for _ in range(2))
+        wsb = dpd.dpd_ls_ws_size(plan.handle, 1, longer)
+        ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+        A = torch.empty(K, K, dtype=torch.complex128, device="cuda")
+        b = torch.empty(K, dtype=torch.complex128, device="cuda")
+        dpd.dpd_ls_normal(plan.handle, st, y.data_ptr(), t.data_ptr(), 1, n, n, 1.0, ws.data_ptr(), wsb, A.data_ptr(),
+                          b.data_ptr())
+        B, d = plan.ls_normal(y, t)
+        assert torch.equal(A, B) and torch.equal(b, d), n
