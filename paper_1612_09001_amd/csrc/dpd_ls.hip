@@ -442,19 +442,23 @@ __device__ __forceinline__ void ls_sub_wave(const LsParams &p, uint32_t *X, int 
     const float2 *ys = yr + s0, *ts = tr + s0;
     const int nl = (int)(send - s0);
     const int lo = s0 >= kMaxL ? -kMaxL : (int)-s0;
-    // sample of each row this lane builds, relative to the tile's first
-    int so[RI];
+    // sample of each row this lane builds, relative to the tile's first, and the
+    // first of its step's 64 samples: ls_gram_kernel does not take those that begin
+    // past the slab's end, so their rows are zeros whatever the L - 1 samples before
+    // them hold (an infinity there, times the zeroed row side, would be a NaN)
+    int so[RI], sf[RI];
 #pragma unroll
     for (int e = 0; e < RI; ++e) {
-        const int row = lane + 64 * e, i = row / (8 + H);
-        so[e] = 8 * (GK * i + kw) + (row - i * (8 + H)) - H;
+        const int row = lane + 64 * e, i = row / (8 + H), base = 8 * (GK * i + kw);
+        so[e] = base + (row - i * (8 + H)) - H;
+        sf[e] = base & ~(kLsTile - 1);
     }
     float2 y[RI], t[RI];
     const auto fetch = [&](int m0) {
 #pragma unroll
         for (int e = 0; e < RI; ++e) {
             const int q = m0 + so[e];
-            const bool ok = lane + 64 * e < rows && q >= lo && q < nl;
+            const bool ok = lane + 64 * e < rows && q >= lo && q < nl && m0 + sf[e] < nl;
             y[e] = ok ? ys[q] : make_float2(0.f, 0.f);
             if (last) t[e] = ok && q >= 0 ? ts[q] : make_float2(0.f, 0.f);
         }

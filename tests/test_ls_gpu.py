@@ -503,3 +503,29 @@ def test_workspace_of_a_longer_input(torch, dpd, order, L):
                           b.data_ptr())
         B, d = plan.ls_normal(y, t)
         assert torch.equal(A, B) and torch.equal(b, d), n
+
+
+@pytest.mark.parametrize("order,L", [(3, 3), (7, 4), (9, 8)])
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_last_sample_not_finite(torch, dpd, order, L, value):
+    """An infinity or NaN in the last sample reaches the columns of its own tap and
+    no others, as it does where the same samples are one row of many (the other
+    form of the sums)."""
+    orders = list(range(1, order + 1, 2))
+    plan = dpd.Plan(orders, orders, L, signals.aph_coeffs(orders, orders, L))
+    K = plan.K
+    tap0 = torch.tensor([f < K - 1 and f % L == 0 for f in range(K)], device="cuda")
+    for n in (64, 128, 192, 256, 1024 + 64, 2048 - 64):
+        y, t = signals.ofdm_16qam(n, config_id=96), signals.ofdm_16qam(n, config_id=97)
+        y[-1] = value
+        A, b = plan.ls_normal(_dev(torch, y), _dev(torch, t))
+        assert not bool(torch.isnan(torch.view_as_real(A[~tap0][:, ~tap0])).any()), n
+        assert not bool(torch.isnan(torch.view_as_real(b[~tap0])).any()), n
+        rows = 1 + 2 * torch.cuda.get_device_properties(0).multi_processor_count
+        Y = torch.zeros(rows, n, dtype=torch.complex64, device="cuda")
+        T = torch.zeros_like(Y)
+        Y[1], T[1] = _dev(torch, y), _dev(torch, t)
+        B, d = plan.ls_normal(Y, T)
+        for u, v in ((A[:K - 1], B[:K - 1]), (b, d)):
+            u, v = torch.view_as_real(u), torch.view_as_real(v)
+            assert torch.equal(u.isnan(), v.isnan()) and torch.equal(u.nan_to_num(), v.nan_to_num()), n
