@@ -438,9 +438,9 @@ __global__ void __launch_bounds__(kBlock) fwd_tile_kernel(FwdParams p)
     }
 }
 
-// Compiler-only ordering point for LDS traffic between the lanes of one wave.
-// A wave's LDS instructions execute in program order, so no wait is needed;
-// this only stops the compiler from moving LDS accesses across it.
+// Compiler-only ordering point for LDS and global traffic between the lanes of one
+// wave.  A wave's memory instructions of a kind execute in program order, so no
+// wait is needed; this only stops the compiler from moving accesses across it.
 __device__ __forceinline__ void wave_lds_order()
 {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -560,12 +560,13 @@ __global__ void __launch_bounds__(kBlock, (fwd_stream_blocks<NI, L>())) fwd_stre
     const int hl = HS > 0 ? (lane < HS ? lane : HS - 1) : 0;
     float2 hist_v = make_float2(0.f, 0.f);
     if (HS > 0 && p.hist != nullptr && gw == 0) {
+        // every lane reads before any lane replaces: for n < L - 1 the sample that
+        // a lane keeps is another lane's to overwrite
         hist_v = p.hist[hl];
-        if (lane < HS) {
-            const int64_t m = p.n - HS + lane;
-            const float2 v = m >= 0 ? p.in[m] : p.hist[HS + m];
-            p.hist[lane] = v;
-        }
+        const int64_t m = p.n - HS + hl;
+        const float2 v = *(m >= 0 ? p.in + m : p.hist + (HS + m));
+        wave_lds_order();
+        if (lane < HS) p.hist[lane] = v;
     }
 
     // raw sample for halo sample hl - HS of the chunk starting at t0 (lane hl

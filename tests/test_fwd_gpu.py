@@ -424,3 +424,24 @@ def test_rows_packed_one_after_the_other(torch, dpd, orc, mo, co, L):
         for r in {0, 1, rows - 1}:
             assert_parity(body[r, :n], orc.forward(xs[r], mo, co, L, h), "n %d row %d" % (n, r))
         assert np.all(body[:, n:] == np.complex64(complex(7.0, -7.0))) and _host(a)[0] == _host(a)[-1] == np.complex64(complex(7.0, -7.0))
+
+
+@pytest.mark.parametrize("tune", ALL_TUNES)
+@pytest.mark.parametrize("L", [3, 16])
+def test_history_of_every_short_chunk(torch, dpd, L, tune):
+    """Chunks of 1 to L samples, one after the other: a launch that replaces the
+    history reads all of it before it overwrites any."""
+    mo, co = [1, 3, 5], [1, 3]
+    x = _dev(torch, signals.ofdm_16qam(5 * L * (L + 1), config_id=96))
+    plan = dpd.Plan(mo, co, L, signals.aph_coeffs(mo, co, L, config_id=96))
+    whole = plan.apply(x)
+    plan.set_tune(samples_per_thread=tune[0], stage_lds=tune[1], grid_mult=2)
+    hist = torch.zeros(L - 1, dtype=torch.complex64, device="cuda")
+    z = torch.empty_like(x)
+    t = 0
+    for m in 10 * list(range(1, L + 1)):
+        plan.apply_hist(x[t:t + m], hist, out=z[t:t + m])
+        t += m
+        want = torch.cat([torch.zeros(L - 1, dtype=torch.complex64, device="cuda"), x[:t]])[-(L - 1):]
+        assert torch.equal(torch.view_as_real(hist), torch.view_as_real(want)), (t, m)
+    assert torch.equal(torch.view_as_real(z), torch.view_as_real(whole))
