@@ -143,8 +143,11 @@ DPD_EXPORT dpd_status dpd_batch_create(const dpd_stream_desc *desc, int32_t n_st
         if (!valid_tune(*tune) || tune->stage_lds != 1) return DPD_EINVAL;
         t = *tune;
     } else {
+        // (up to 2^40: a descriptor's length is not checked yet)
+        const int64_t most = (int64_t)1 << 40;
         int64_t samples = 0;
-        for (int32_t s = 0; s < n_streams; ++s) samples += std::max<int64_t>(desc[s].n, 0);
+        for (int32_t s = 0; s < n_streams; ++s)
+            samples = std::min(samples + std::clamp<int64_t>(desc[s].n, 0, most), most);
         t.samples_per_thread = samples < (int64_t)1 << 19 ? 2 : samples < (int64_t)3 << 19 ? 4 : 8;
         t.grid_mult = 3;
     }

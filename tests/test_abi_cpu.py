@@ -139,3 +139,12 @@ def test_learning_entry_points_reject_on_the_host(lib):
                                       fake, 1, 256, 256, ctypes.c_float(0.1), None, None, fake,
                                       1 << 20) == dpd.DPD_EINVAL
     assert lib.dpd_set_coeffs_async(None, None, None) == dpd.DPD_EINVAL
+
+
+def test_batch_refuses_lengths_past_64_bits(lib):
+    """Descriptors are refused one by one also where their lengths add up past 64
+    bits (fake, never dereferenced addresses)."""
+    big = (1 << 63) - 1
+    ds = [dpd.dpd_stream_desc(i, 1 << 21, big, 1, 0, 2, 0, 1 << 20) for i in (None, 1 << 20, 1 << 20)]
+    h = ctypes.c_void_p()
+    assert lib.dpd_batch_create((dpd.dpd_stream_desc * 3)(*ds), 3, None, ctypes.byref(h)) == dpd.DPD_EINVAL
