@@ -129,10 +129,11 @@ dpd_status dpd_set_coeffs_device_if(dpd_plan *plan, const void *coeffs_dev, cons
 
 /* dpd_set_tune / dpd_get_tune -- launch shape of this plan's forward kernels,
  * used from then on at every size but on a thousand and more rows shorter than
- * 512 samples (until then each call takes the shape measured best for its size;
- * dpd_get_tune then reports the shape of long streams).  Filters of more than eight taps have one-shot kernels of 2 and 4
- * samples per thread and a streaming kernel of 8: other values take the
- * nearest.  Fields outside the supported set are DPD_EINVAL. */
+ * 512 samples.  Until then each call takes the shape measured best for its size,
+ * and dpd_get_tune reports the one of streams past 10 * 2^20 samples.  Filters
+ * of more than eight taps have one-shot kernels of 2 and 4 samples per thread and
+ * a streaming kernel of 8: other values take the nearest.  Fields outside the
+ * supported set are DPD_EINVAL. */
 dpd_status dpd_set_tune(dpd_plan *plan, const dpd_tune *tune);
 dpd_status dpd_get_tune(const dpd_plan *plan, dpd_tune *tune);
 

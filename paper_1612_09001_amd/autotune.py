@@ -3,10 +3,13 @@
 Each candidate shape (samples per lane S, one-shot vs streaming kernel,
 persistent blocks per CU) is timed with HIP events on the current stream over
 a few launches after a warm-up; the fastest is applied and cached as JSON,
-keyed by GPU architecture and workload class:
+keyed by GPU architecture, version of the kernels and workload class:
 
   plan   (NI, L, ceil(log2 n))         forward kernels of one plan
   batch  (sorted class histogram, ceil(log2 total samples))
+
+A shape found for other kernels is timed again.  The candidates hold every shape
+that the library itself chooses by size.
 
 The cache file is $DPD_TUNE_CACHE, else ~/.cache/paper_1612_09001_amd/tune.json.
 Tuning changes launch shapes only; every candidate computes the same outputs
@@ -22,9 +25,11 @@ import torch
 
 from . import dpd as _dpd
 
+KERNELS = 2   # raised when the forward or batch kernels or their chosen shapes change
+
 PLAN_CANDIDATES = [dict(samples_per_thread=s, stage_lds=l, grid_mult=g)
-                   for s in (2, 4, 8) for l, gs in ((0, (8,)), (1, (4, 8, 16))) for g in gs]
-BATCH_CANDIDATES = [dict(samples_per_thread=s, grid_mult=g) for s in (2, 4, 8) for g in (2, 4, 8, 16)]
+                   for s in (2, 4, 8) for l, gs in ((0, (8,)), (1, (2, 4, 8, 16))) for g in gs]
+BATCH_CANDIDATES = [dict(samples_per_thread=s, grid_mult=g) for s in (2, 4, 8) for g in (2, 3, 4, 8, 16)]
 
 
 def cache_path() -> str:
@@ -80,7 +85,7 @@ def _levels(orders) -> int:
 
 def plan_key(plan, n) -> str:
     ni = _levels(plan.main_orders + plan.conj_orders)
-    return "plan|%s|NI%d|L%d|n2^%d" % (arch(), ni, plan.L, max(0, math.ceil(math.log2(max(n, 1)))))
+    return "plan|%s|k%d|NI%d|L%d|n2^%d" % (arch(), KERNELS, ni, plan.L, max(0, math.ceil(math.log2(max(n, 1)))))
 
 
 def tune_plan(plan, x, out=None, candidates=None, use_cache=True, iters=10) -> dict:
@@ -117,7 +122,7 @@ def batch_key(specs) -> str:
         hist[k] = hist.get(k, 0) + n
         total += n
     sig = ",".join("%s=%d" % (k, max(0, math.ceil(math.log2(max(v, 1))))) for k, v in sorted(hist.items()))
-    return "batch|%s|%s|n2^%d" % (arch(), sig, max(0, math.ceil(math.log2(max(total, 1)))))
+    return "batch|%s|k%d|%s|n2^%d" % (arch(), KERNELS, sig, max(0, math.ceil(math.log2(max(total, 1)))))
 
 
 def tune_batch(workload, candidates=None, use_cache=True, iters=5):

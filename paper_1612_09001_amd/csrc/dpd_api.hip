@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <limits>
 #include <atomic>
 #include <cstring>
 #include <mutex>
@@ -369,7 +370,7 @@ DPD_EXPORT dpd_status dpd_create(const int32_t *main_orders, int32_t n_main, con
     if (p == nullptr) return DPD_ENOMEM;
     p->map = map;
     p->K = (n_main + n_conj) * L + 1;
-    p->tune = default_tune();
+    p->tune = fwd_auto(map, std::numeric_limits<int64_t>::max());   // what dpd_get_tune reports until dpd_set_tune
     p->raw.assign(coeffs_host, coeffs_host + 2 * p->K);
     hipError_t e = hipGetDevice(&p->device);
     if (e != hipSuccess) {

@@ -445,3 +445,29 @@ def test_history_of_every_short_chunk(torch, dpd, L, tune):
         want = torch.cat([torch.zeros(L - 1, dtype=torch.complex64, device="cuda"), x[:t]])[-(L - 1):]
         assert torch.equal(torch.view_as_real(hist), torch.view_as_real(want)), (t, m)
     assert torch.equal(torch.view_as_real(z), torch.view_as_real(whole))
+
+
+@pytest.mark.parametrize("order,L,grid", [(3, 2, 2), (7, 4, 2), (9, 8, 4)])
+def test_untuned_plan_reports_its_long_stream_shape(torch, dpd, order, L, grid):
+    orders = list(range(1, order + 1, 2))
+    plan = dpd.Plan(orders, orders, L, signals.aph_coeffs(orders, orders, L))
+    assert plan.get_tune() == dict(samples_per_thread=8, stage_lds=1, block=256, grid_mult=grid)
+
+
+def test_autotuner_times_the_librarys_own_shapes(torch, dpd, tmp_path, monkeypatch):
+    """The shapes the library chooses are candidates, and a shape cached for other
+    kernels is not taken."""
+    from paper_1612_09001_amd import autotune
+
+    orders, L, n = [1, 3, 5, 7], 4, 4096
+    plan = dpd.Plan(orders, orders, L, signals.aph_coeffs(orders, orders, L))
+    own = {k: v for k, v in plan.get_tune().items() if k != "block"}
+    assert own in autotune.PLAN_CANDIDATES
+    assert dict(samples_per_thread=8, grid_mult=3) in autotune.BATCH_CANDIDATES
+    monkeypatch.setenv("DPD_TUNE_CACHE", str(tmp_path / "tune.json"))
+    stale = dict(samples_per_thread=8, stage_lds=1, grid_mult=16)
+    autotune._store({"plan|%s|NI4|L4|n2^12" % autotune.arch(): {"tune": stale, "us": 1.0}})
+    timed = []
+    monkeypatch.setattr(autotune, "time_us", lambda fn, **kw: timed.append(fn()) or float(len(timed)))
+    best = autotune.tune_plan(plan, _dev(torch, signals.ofdm_16qam(n, config_id=96)))
+    assert len(timed) == len(autotune.PLAN_CANDIDATES) and best == autotune.PLAN_CANDIDATES[0]
