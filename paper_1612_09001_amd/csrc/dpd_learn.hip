@@ -48,20 +48,19 @@ static int ln_walk(int mode, int64_t rows, int64_t n, int E)
     return ln_blocks(kLnBoth, E) == 1 && n % 512 == 0 && rows * n > (int64_t)1 << 19 ? kLn8 : kLn4;
 }
 
-// One pass over the data; *nblk receives the number of blocks (and partials).
-// One round of resident blocks, on rows of whole 256s the same in every mode --
-// the blocks per CU that the kernels with a gradient are built for -- so that the
-// partial sums, and with them loss and gradient, come out the same whether the step
-// runs as one pass or two.  (With more than 130 accumulators that is one block per
-// CU: the forward pass alone would be faster with two, 98 us against 122 on 64 rows
-// of 2^18 at NI = 5, L = 7; the step would then take 245 us for 237.)  Arguments
-// already validated.
+// One pass over the data; *nblk receives the number of blocks (and gradient
+// partials), *nloss that of loss partials.  One round of resident blocks, on rows of
+// whole 256s the same in every mode -- the blocks per CU that the kernels with a
+// gradient are built for -- so that the partial sums, and with them loss and
+// gradient, come out the same whether the step runs as one pass or two; the forward
+// pass has twice as many where a run has two parts (ln_parts).  Arguments already
+// validated.
 static hipError_t ln_run(int mode, const dpd_plan *P, const dpd_plan *A, const dpd_plan *B, hipStream_t hs,
                          const void *coeffs_dev, const void *x, const void *z, const void *grad_y, void *grad_z,
                          int64_t rows, int64_t n, int64_t ld, float scale, float *lpart, float *gpart, int32_t *step,
-                         bool fine, int *nblk)
+                         bool fine, int *nblk, int *nloss)
 {
-    *nblk = 0;
+    *nblk = *nloss = 0;
     const int64_t N = rows * n;
     LnParams p;
     p.M = P->d_table;
@@ -86,11 +85,15 @@ static hipError_t ln_run(int mode, const dpd_plan *P, const dpd_plan *A, const d
     p.fine = fine;
     p.flush = fine ? (int32_t)std::min<int64_t>(std::max<int64_t>(N >> 18, S + 1), 64) : kLnFlush;
     p.step = step;
-    const int64_t cap = (int64_t)num_cus() * ln_blocks(n % 256 == 0 ? kLnBoth : mode, E);
-    const int grid = (int)std::max<int64_t>(
-        1, std::min<int64_t>(std::min<int64_t>(kLossBlocks, cap), (rows * p.tpr + kBlock / 64 - 1) / (kBlock / 64)));
+    const bool parts = ln_parts(E, walk);
+    const int64_t cap = std::min<int64_t>(kLossBlocks / (parts ? 2 : 1), (int64_t)num_cus() * ln_blocks(n % 256 == 0 ? kLnBoth : mode, E));
+    const int blocks = (int)std::max<int64_t>(1, std::min<int64_t>(cap, (rows * p.tpr + kBlock / 64 - 1) / (kBlock / 64)));
+    const int grid = mode == kLnFwd && parts ? 2 * blocks : blocks;
     const hipError_t e = ln_table().fn[NI - 1][L - 1][walk][mode](p, hs, grid);
-    if (e == hipSuccess) *nblk = grid;
+    if (e == hipSuccess) {
+        *nblk = grid;
+        *nloss = parts ? 2 * blocks : blocks;
+    }
     return e;
 }
 
@@ -195,14 +198,14 @@ DPD_EXPORT dpd_status dpd_transmit_loss_grad(dpd_plan *P, const dpd_plan *A, con
     if (coeffs_dev != nullptr && (uintptr_t)coeffs_dev % 8 != 0) return DPD_EINVAL;
     const int64_t N = rows * n;
     const hipStream_t hs = (hipStream_t)stream;
-    int nblk = 0;
+    int nblk = 0, nloss = 0;
     hipError_t e = hipSuccess;
     if (N > 0)
         e = ln_run(kLnFwd, P, A, B, hs, coeffs_dev, x, z, grad_y, nullptr, rows, n, ld, scale, (float *)ws, nullptr,
-                   nullptr, false, &nblk);
+                   nullptr, false, &nblk, &nloss);
     if (e != hipSuccess) return hip_fail(e);
     if (loss_dev != nullptr) {
-        e = launch_loss_finalize((const float *)ws, nblk, N > 0 ? 1.0 / (double)N : 0.0, loss_dev, hs);
+        e = launch_loss_finalize((const float *)ws, nloss, N > 0 ? 1.0 / (double)N : 0.0, loss_dev, hs);
         if (e != hipSuccess) return hip_fail(e);
     }
     return DPD_OK;
@@ -245,11 +248,11 @@ DPD_EXPORT dpd_status dpd_transmit_backward(const dpd_plan *P, const dpd_plan *A
                             ld, ws, ws_bytes);
     }
     const bool fine = (uintptr_t)x % 16 != 0 || (uintptr_t)grad_z % 16 != 0 || (rows > 1 && ld % 2 != 0);
-    int nblk = 0;
+    int nblk = 0, nloss = 0;
     hipError_t e = hipSuccess;
     if (N > 0)
         e = ln_run(kLnBwd, P, A, B, hs, nullptr, x, z, grad_y, grad_z, rows, n, ld, 0.f, nullptr, (float *)ws, nullptr,
-                   fine, &nblk);
+                   fine, &nblk, &nloss);
     if (e != hipSuccess) return hip_fail(e);
     e = launch_bwd_finalize((const float *)ws, nblk, P->map, (float2 *)grad_coeffs, hs);
     return e == hipSuccess ? DPD_OK : hip_fail(e);
@@ -304,11 +307,11 @@ static dpd_status learn_step(dpd_plan *P, const dpd_plan *A, const dpd_plan *B, 
     const int64_t N = rows * n;
     float *lp = (float *)ws;
     float *dc = (float *)((char *)ws + learn_loss_bytes());
-    int nblk = 0;
+    int nblk = 0, nloss = 0;
     hipError_t e;
     if (N > 0) {
         e = ln_run(kLnBoth, P, A, B, hs, coeffs_dev, x, z, grad_y, nullptr, rows, n, ld, scale, lp, dc, step_dev,
-                   false, &nblk);
+                   false, &nblk, &nloss);
     } else {
         if (step_dev != nullptr) hipLaunchKernelGGL(step_advance, dim3(1), dim3(1), 0, hs, step_dev);
         e = hipGetLastError();
@@ -317,7 +320,7 @@ static dpd_status learn_step(dpd_plan *P, const dpd_plan *A, const dpd_plan *B, 
     const float bc1 = step_dev ? 0.f : (float)(1.0 - std::pow((double)beta1, step));
     const float bc2 = step_dev ? 0.f : (float)(1.0 - std::pow((double)beta2, step));
     hipLaunchKernelGGL(learn_finalize, dim3((uint32_t)(P->map.L * P->map.NI + 2)), dim3(kBlock), 0, hs, dc, nblk,
-                       P->map, lp, nblk, N > 0 ? 1.0 / (double)N : 0.0, loss_dev, (float2 *)grad_coeffs,
+                       P->map, lp, nloss, N > 0 ? 1.0 / (double)N : 0.0, loss_dev, (float2 *)grad_coeffs,
                        (float *)coeffs_dev, adam_m, adam_v, lr, beta1, beta2, eps, bc1, bc2,
                        (const int32_t *)step_dev);
     e = hipGetLastError();

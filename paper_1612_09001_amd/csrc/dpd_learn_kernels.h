@@ -34,7 +34,7 @@
 // over the wave in FP32 and go to its FP64 totals; for rows at odd 8-byte starts or
 // strides ("fine", as in dpd_backward) they cover at most 64 samples, one per 2^18
 // of the input but at least a chunk's, and are added up in FP64.  Loss and gradient
-// leave as one FP32 partial per block.
+// leave as FP32 partials, one per block.
 #pragma once
 
 #include "dpd_bwd_kernels.h"
@@ -62,7 +62,7 @@ struct LnParams {
     const float2 *x;         // rows x n at stride ld
     float2 *z, *gy;          // same layout: written, or read by kLnBwd
     float2 *gz;              // kLnBwd: dE/dz out (nullptr: not written)
-    float *lpart;            // loss partials, one per block
+    float *lpart;            // loss partials, one per block (two where a run has two parts)
     float *gpart;            // gradient partials, [block][4 L NI + 2]
     int64_t rows, n, ld;
     int64_t tpr;             // chunks per row
@@ -193,6 +193,12 @@ __device__ __forceinline__ void ln_accumulate(float (&acc)[4 * L * NI + 2], cons
 // backward pass at NI = 5, L = 6.
 constexpr int ln_blocks(int mode, int E) { return mode == kLnFwd || E <= 130 ? 2 : 1; }
 
+// Where the gradient leaves one block per CU, a run of the one pass on rows of whole
+// chunks has two parts for the loss, each with sums of its own, and the forward pass
+// gives the second part to another wave: two blocks per CU, and the same bits (64
+// rows of 2^18 at NI = 5, L = 7: 123 us with one block).
+constexpr bool ln_parts(int E, int walk) { return ln_blocks(kLnBoth, E) == 1 && (walk == kLn4 || walk == kLn8); }
+
 template <int NI, int L, int MODE, int WALK>
 __global__ void __launch_bounds__(kBlock, ln_blocks(MODE, 4 * L * NI + 2)) learn_kernel(LnParams p)
 {
@@ -250,11 +256,22 @@ __global__ void __launch_bounds__(kBlock, ln_blocks(MODE, 4 * L * NI + 2)) learn
     LossSum ls;
 
     const int64_t total = p.rows * p.tpr;
-    const int64_t nw = (int64_t)gridDim.x * WAVES;
-    const int64_t gw = (int64_t)xcd_remap(blockIdx.x, gridDim.x) * WAVES + wv;
-    const int64_t per = (total + nw - 1) / nw;
-    const int64_t c_begin = gw * per < total ? gw * per : total;
-    const int64_t c_end = c_begin + per < total ? c_begin + per : total;
+    constexpr bool PARTS = FWD && ln_parts(E, WALK);
+    constexpr bool APART = PARTS && !GRAD;   // a wave takes one part of a run
+    const int64_t block = xcd_remap(blockIdx.x, gridDim.x);
+    const int64_t nw = (int64_t)gridDim.x * WAVES / (APART ? 2 : 1);
+    const int64_t gw = (block * WAVES + wv) / (APART ? 2 : 1);
+    const int64_t per = (total + nw - 1) / nw, part = (per + 1) / 2;
+    int64_t c_begin = gw * per < total ? gw * per : total;
+    int64_t c_end = c_begin + per < total ? c_begin + per : total;
+    if constexpr (APART) {
+        const int64_t mid = c_begin + part < c_end ? c_begin + part : c_end;
+        if (wv & 1)
+            c_begin = mid;
+        else
+            c_end = mid;
+    }
+    double first = 0.0;   // the loss of the run's first part
     // the learning step's counter (read by the finalisation launch after this one)
     if (p.step != nullptr && blockIdx.x == 0 && tid == 0) *p.step += 1;
 
@@ -627,6 +644,12 @@ __global__ void __launch_bounds__(kBlock, ln_blocks(MODE, 4 * L * NI + 2)) learn
                 ++row;
             }
             if (left > 1) load(R, row, k * C);
+            if constexpr (PARTS && !APART) {
+                if (c_end - left == c_begin + part) {
+                    first = ls.total();
+                    ls = LossSum();
+                }
+            }
             compute(crow, ck * C, ck == p.tpr - 1);
             if (left > 1) stage(R, k * C);
         }
@@ -635,16 +658,29 @@ __global__ void __launch_bounds__(kBlock, ln_blocks(MODE, 4 * L * NI + 2)) learn
     // wave -> block: one FP32 partial of the loss and of each gradient entry, in
     // fixed order, FP64
     if constexpr (FWD) {
-        double t = ls.total();
+        const auto all = [](double t) {
 #pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) t += __shfl_xor(t, off, 64);
-        if (lane == 0) red[wv] = t;
+            for (int off = 32; off >= 1; off >>= 1) t += __shfl_xor(t, off, 64);
+            return t;
+        };
+        constexpr int NP = PARTS && !APART ? 2 : 1;   // partials of this block
+        if constexpr (NP == 2) {
+            const bool whole = c_begin + part >= c_end;   // no second part
+            const double t0 = all(whole ? ls.total() : first), t1 = all(whole ? 0.0 : ls.total());
+            if (lane == 0) {
+                red[2 * wv] = t0;
+                red[2 * wv + 1] = t1;
+            }
+        } else {
+            const double t = all(ls.total());
+            if (lane == 0) red[wv] = t;
+        }
         __syncthreads();
-        if (tid == 0) {
-            double u = red[0];
+        if (tid < NP) {
+            double u = red[WAVES * tid];
 #pragma unroll
-            for (int w = 1; w < WAVES; ++w) u += red[w];
-            p.lpart[blockIdx.x] = (float)u;
+            for (int w = 1; w < WAVES; ++w) u += red[WAVES * tid + w];
+            p.lpart[(PARTS ? block : blockIdx.x) * NP + tid] = (float)u;
         }
         __syncthreads();
     }

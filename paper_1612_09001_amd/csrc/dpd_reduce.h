@@ -82,20 +82,24 @@ __device__ __forceinline__ double swap_add(double a, double b)
 }
 
 // The same over 16 lanes and less: each lane keeps the value that its bit O
-// selects and adds the copy of the lane that CTRL pairs it with.
-template <int O, int CTRL, class T>
+// selects and adds the copy of lane l ^ O (l ^ 4 by two exchanges, l ^ 7 ^ 3).
+template <int O, class T>
 __device__ __forceinline__ T keep_add(T a, T b, int lane)
 {
     const bool up = (lane & O) != 0;
-    return (up ? b : a) + dpp_from<CTRL, 0xf>(up ? a : b);
+    T v = up ? a : b;
+    if constexpr (O == 8) v = dpp_from<0x128, 0xf>(v);                           // row_ror:8
+    if constexpr (O == 4) v = dpp_from<0x1B, 0xf>(dpp_from<0x141, 0xf>(v));      // row_half_mirror, quad_perm 3,2,1,0
+    if constexpr (O == 2) v = dpp_from<0x4E, 0xf>(v);                            // quad_perm 2,3,0,1
+    if constexpr (O == 1) v = dpp_from<0xB1, 0xf>(v);                            // quad_perm 1,0,3,2
+    return (up ? b : a) + v;
 }
 
 // N <= 64 per-lane FP32 values summed over the wave in T (float or double),
 // transposed: lane l returns the sum of v[l] over all 64 lanes (zero for l >= N).
 // Six butterfly stages, each halving the values still held: a lane keeps the one
-// that its lane bit selects and adds its partner's copy (at bit 2 lanes l and l ^
-// 7 are partners; the last two stages sum over the bits in which those differ).
-// No LDS.  Fixed order: the same inputs give the same bits.
+// that its lane bit selects and adds its partner's copy.  No LDS.  Fixed order:
+// the same inputs give the same bits.
 template <class T, int N>
 __device__ __forceinline__ T wave_transpose_sum(const float *v, int lane)
 {
@@ -109,12 +113,12 @@ __device__ __forceinline__ T wave_transpose_sum(const float *v, int lane)
         a[i] = i < N ? swap_add<16>(x, y) : (T)0;
     }
 #pragma unroll
-    for (int i = 0; i < 8; ++i) a[i] = keep_add<8, 0x128>(a[i], a[i + 8], lane);    // row_ror:8
+    for (int i = 0; i < 8; ++i) a[i] = keep_add<8>(a[i], a[i + 8], lane);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) a[i] = keep_add<4, 0x141>(a[i], a[i + 4], lane);    // row_half_mirror
+    for (int i = 0; i < 4; ++i) a[i] = keep_add<4>(a[i], a[i + 4], lane);
 #pragma unroll
-    for (int i = 0; i < 2; ++i) a[i] = keep_add<2, 0x4E>(a[i], a[i + 2], lane);     // quad_perm 2,3,0,1
-    return keep_add<1, 0xB1>(a[0], a[1], lane);                                     // quad_perm 1,0,3,2
+    for (int i = 0; i < 2; ++i) a[i] = keep_add<2>(a[i], a[i + 2], lane);
+    return keep_add<1>(a[0], a[1], lane);
 }
 
 // Calls f(std::integral_constant<int, G>) for G = 0 .. NG-1.

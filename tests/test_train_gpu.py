@@ -455,3 +455,38 @@ def test_gradient_at_the_ends_of_short_chunks(torch, orc, orders, taps):
             g = ref.cpu().numpy()[:rows * n].reshape(rows, n).astype(np.complex128)
             want = sum(orc.backward(host[0][r], *orders, taps, h0, g[r], want_dx=False)[1] for r in range(rows))
             assert_dcoef(gc.cpu().numpy(), want, "n=%d off=%d" % (n, off))
+
+
+@pytest.mark.parametrize("rows,n", [(1, 256), (1, 1024), (7, 768), (4, 1 << 18), (37, 512 * 101), (13, 256 * 301)])
+@pytest.mark.parametrize("taps", [7, 8])
+def test_loss_of_runs_in_two_parts(torch, rows, n, taps):
+    """Orders to 9 with seven and eight taps, where the forward pass runs two waves
+    per run of the one-pass kernel: the loss of both is the same float and that of
+    the residual that dE/dy holds, over runs of one chunk, odd and even runs and
+    runs that end early."""
+    from paper_1612_09001_amd import dpd
+    from paper_1612_09001_amd.pa import SyntheticPA
+
+    orders = [1, 3, 5, 7, 9]
+    gen = torch.Generator(device="cuda").manual_seed(rows * 1000 + taps)
+    x = torch.view_as_complex(torch.randn(rows, n, 2, generator=gen, device="cuda") * 0.18)
+    h0 = signals.aph_coeffs(orders, orders, taps, config_id=52)
+    h0[0] += 1.0
+    P, pa = dpd.Plan(orders, orders, taps, h0), SyntheticPA()
+    iq, pb, st, K = pa.iq.handle, pa.pa.handle, dpd.current_stream(), P.K
+    wsb = dpd.dpd_learn_step_ws_size(P.handle)
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+    ptr = lambda t: t.data_ptr()
+    h = torch.from_numpy(h0).cuda()
+    z, gy, gy2 = (torch.zeros_like(x) for _ in range(3))
+    l1, l2 = torch.zeros(1, device="cuda"), torch.zeros(1, device="cuda")
+    dpd.dpd_transmit_loss_grad(P.handle, iq, pb, st, ptr(h), ptr(x), ptr(z), rows, n, n, 0.1, ptr(l1), ptr(gy), ptr(ws),
+                               wsb)
+    m, v = torch.zeros(2 * K, device="cuda"), torch.zeros(2 * K, device="cuda")
+    dpd.dpd_learn_step(P.handle, iq, pb, st, ptr(h), ptr(m), ptr(v), 1, 0.01, 0.9, 0.999, 1e-8, ptr(x), ptr(z), ptr(gy2),
+                       rows, n, n, 0.1, ptr(l2), 0, ptr(ws), wsb)
+    assert torch.equal(l1, l2) and torch.equal(gy, gy2)
+    gscale = float(np.float32(2.0 * np.float64(np.float32(0.1)) / (rows * n)))
+    want = float(torch.view_as_real(gy).double().square().sum()) / gscale ** 2 / (rows * n)
+    # dE/dy rounded twice (2^-24 each, squared), FP32 sums of 8 x 32 squares
+    assert abs(float(l1) - want) <= 1e-5 * want
