@@ -186,8 +186,8 @@ dpd_status dpd_apply_hist(dpd_plan *plan, void *stream, const void *in, void *ou
  * Deterministic: the same inputs give bitwise the same gradients.  Rows start
  * from zero history.  dE/dcoeffs is summed in FP32 over at most 128 samples
  * per lane and the 64 lanes of a wave, then in FP64 (rows that start or are
- * strided off 16 bytes, and plans of more than 8 taps: FP32 over at most 64
- * samples of one lane, all else FP64), so its accuracy does not degrade with
+ * strided off 16 bytes, and plans of more than 8 taps: FP32 over one sample per
+ * 2^18 of the input, at most 64, all else FP64), so its accuracy does not degrade with
  * rows * n (any size that fits in memory, 64-bit indices throughout). */
 dpd_status dpd_backward_ws_size(const dpd_plan *plan, int64_t rows, int64_t n, size_t *bytes);
 dpd_status dpd_backward(dpd_plan *plan, void *stream, const void *coeffs_dev, const void *x,
@@ -349,8 +349,8 @@ dpd_status dpd_transmit_backward(const dpd_plan *P, const dpd_plan *A, const dpd
  * launches): dpd_transmit_loss_grad with the coefficients coeffs_dev and
  * dpd_transmit_backward as one pass over x, then one launch that finalises the
  * loss and the gradient (FP64, as those calls do) and applies the Adam update
- * of dpd_adam_step to coeffs_dev in place.  Results are bitwise those of the three calls followed by
- * dpd_adam_step.  Arguments as there:
+ * of dpd_adam_step to coeffs_dev in place.  Results are bitwise those of the
+ * three calls.  Arguments as there:
  *   coeffs_dev       K complex64 (device), read, then updated
  *   adam_m, adam_v   2K floats each (device), Adam moments (zero before
  *                    step 1), updated; step counts from 1
@@ -360,9 +360,10 @@ dpd_status dpd_transmit_backward(const dpd_plan *P, const dpd_plan *A, const dpd
  *                    update), or NULL
  *   grad_coeffs      receives dE/dcoeffs (K complex64), or NULL
  *   ws, ws_bytes     at least dpd_learn_step_ws_size(P) bytes
- * Built for the stages of dpd_transmit_loss_grad ( n a multiple of 256; x, z, grad_y 16-byte aligned
- * with an even row stride): others are DPD_EUNSUPPORTED (use the separate
- * calls).  coeffs_dev, adam_m, adam_v and grad_coeffs must not overlap.
+ * Built for the stages of dpd_transmit_loss_grad, n a multiple of 256, x, z and
+ * grad_y 16-byte aligned with an even row stride: others are DPD_EUNSUPPORTED
+ * (use the separate calls).  coeffs_dev, adam_m, adam_v and grad_coeffs must not
+ * overlap.
  * Allocates nothing; no host synchronization. */
 dpd_status dpd_learn_step_ws_size(const dpd_plan *P, size_t *bytes);
 dpd_status dpd_learn_step(dpd_plan *P, const dpd_plan *A, const dpd_plan *B, void *stream, void *coeffs_dev,

@@ -38,7 +38,7 @@ static const BwdTable &bwd_table()
 // Resident blocks per CU of a specialised backward kernel (cached).
 static int bwd_occupancy(int NI, int L, int want)
 {
-    static int cache[kSpecNI][kMaxL][3] = {};
+    static int cache[kSpecNI][kMaxL][4] = {};
     static std::mutex mu;
     std::lock_guard<std::mutex> lk(mu);
     int &o = cache[NI - 1][L - 1][want];
@@ -193,18 +193,22 @@ static dpd_status backward_impl(dpd_plan *plan, void *stream, const void *coeffs
         const BwdTable &t = bwd_table();
         const auto grid_of = [&](int L, int want) {
             const int64_t cap = (int64_t)num_cus() * std::min(8, bwd_occupancy(map.NI, L, want));
-            return (int)std::max<int64_t>(1, std::min(cap, (chunks + 3) / 4));
+            return (int)std::max<int64_t>(1, std::min(cap, want == 3 ? (rows * n + kBlock - 1) / kBlock : (chunks + 3) / 4));
         };
+        // the kernel of the coefficient gradient alone (bwd_dc_short_kernel says why)
+        const int dc = p.fine && rows * n < kBwdShort ? 3 : 1;
         hipError_t e = hipSuccess;
         // Both gradients of a filter whose registers leave one block per CU: on
         // long inputs two kernels of two and more blocks are faster, though they
-        // read the samples twice (NI = 4, L = 8, 2^24 samples: 194 us and 169; NI = 5,
-        // L = 8: 254 and 218; 2^22, where the input stays in the last-level cache
-        // but the second launch costs: 57 and 60, 75 and 70).
-        // Likewise where only the kernel of dx alone sums by Horner.
+        // read the samples twice (NI = 4, L = 8, 2^24 samples: 198 us and 161, 7 * 2^20
+        // 92 and 82; NI = 5, L = 8: 242 and 213, 112 and 103).  Short ones pay for the
+        // second launch (2^20 samples: 22 us and 25, 26 and 29; at 2^21 both are equal, at
+        // 2^22, on this side of the line, two would be 4 to 13 % faster).
+        // Likewise where only the kernel of dx alone sums by Horner, and where that of
+        // dcoef is another one.
         const bool apart = want_dx && want_dc && map.L <= kSpecL &&
                            ((rows * n >= (int64_t)6 << 20 && bwd_occupancy(map.NI, map.L, 2) == 1) ||
-                            (p.fine && !bwd_horner(map.NI, true, true)));
+                            (p.fine && !bwd_horner(map.NI, true, true)) || dc == 3);
         if (want_dx && !want_dc && map.NI * map.L == 1 && n < 64 * kBwdS) {
             const int64_t per = (int64_t)kBlock * kLinearU;
             hipLaunchKernelGGL(bwd_dx_linear_kernel, dim3((uint32_t)std::min<int64_t>((rows * n + per - 1) / per, 1 << 20)),
@@ -212,19 +216,19 @@ static dpd_status backward_impl(dpd_plan *plan, void *stream, const void *coeffs
             e = hipGetLastError();
         } else if (apart) {
             e = t.fn[map.NI - 1][map.L - 1][0](p, st, grid_of(map.L, 0));
-            nblk = grid_of(map.L, 1);
-            if (e == hipSuccess) e = t.fn[map.NI - 1][map.L - 1][1](p, st, nblk);
+            nblk = grid_of(map.L, dc);
+            if (e == hipSuccess) e = t.fn[map.NI - 1][map.L - 1][dc](p, st, nblk);
         } else if (map.L <= kSpecL) {
-            const int want = want_dx && want_dc ? 2 : (want_dc ? 1 : 0);
+            const int want = want_dx && want_dc ? 2 : (want_dc ? dc : 0);
             nblk = grid_of(map.L, want);
             e = t.fn[map.NI - 1][map.L - 1][want](p, st, nblk);
         } else {
             if (want_dx) e = t.fn[map.NI - 1][map.L - 1][0](p, st, grid_of(map.L, 0));
             if (want_dc) {
                 // two passes over the taps, the same blocks in both
-                nblk = grid_of(kSpecL, 1);
-                if (e == hipSuccess) e = t.fn[map.NI - 1][kSpecL - 1][1](p, st, nblk);
-                if (e == hipSuccess) e = t.tail[map.NI - 1][map.L - kSpecL - 1](p, st, nblk);
+                nblk = grid_of(kSpecL, dc);
+                if (e == hipSuccess) e = t.fn[map.NI - 1][kSpecL - 1][dc](p, st, nblk);
+                if (e == hipSuccess) e = t.tail[map.NI - 1][map.L - kSpecL - 1][dc == 3](p, st, nblk);
             }
         }
         if (e != hipSuccess) return hip_fail(e);

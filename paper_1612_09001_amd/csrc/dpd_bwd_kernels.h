@@ -21,6 +21,8 @@
 // workspace, and a single block sums the partials in FP64 in block order.
 #pragma once
 
+#include <algorithm>
+
 #include "dpd_fwd_kernels.h"
 #include "dpd_reduce.h"
 #include "dpd_table.h"
@@ -48,13 +50,14 @@ typedef hipError_t (*BwdLaunch)(const BwdParams &, hipStream_t, int grid);
 // Filters of up to kSpecL taps: one pass, want 0 = dx, 1 = dcoef, 2 = both.
 // Longer ones: dx in one pass (want 0), the coefficient gradient in two, taps
 // 0..7 as want 1 of kSpecL taps and taps 8.. by `tail` (their accumulators
-// would not fit the registers at once).  Measured: 32 rows of 20001 samples, six
-// taps, 13.4 us where odd row starts took one thread per sample and two passes
-// over the rows per sixteen entries, 161 us.
+// would not fit the registers at once).  Measured: 256 rows of 20001 samples, six
+// taps, dx and dcoef 47 us where odd row starts took one thread per sample and a pass
+// over the rows per sixteen entries, 946 us.
+// want 3: dcoef of short "fine" inputs (bwd_dc_short_kernel), up to kSpecL taps.
 struct BwdTable {
-    BwdLaunch fn[kSpecNI][kMaxL][3];
-    const void *kern[kSpecNI][kMaxL][3];
-    BwdLaunch tail[kSpecNI][kSpecL];   // [.][taps beyond kSpecL - 1], dcoef
+    BwdLaunch fn[kSpecNI][kMaxL][4];
+    const void *kern[kSpecNI][kMaxL][4];
+    BwdLaunch tail[kSpecNI][kSpecL][2];   // [.][taps beyond kSpecL - 1][short], dcoef
 };
 
 void register_bwd_ni1(BwdTable &);
@@ -71,11 +74,14 @@ constexpr int kBwdS = 4;   // consecutive samples per lane
 // up and adds the result to its FP64 totals: 32 chunks = 128 samples per lane,
 // added up in FP32.  Rows at odd 8-byte starts or strides and filters of more than
 // kSpecL taps ("fine") are summed with less rounding: one chunk per 2^20 samples of
-// the input, at most 64 samples per lane, added up in FP64.
+// the input, at most 64 samples per lane, added up in FP64; inputs below kBwdShort
+// samples, where a chunk's four samples per lane would already be more than that, by
+// bwd_dc_short_kernel, one sample per lane and 2^18 of the input.
 constexpr int kBwdFlush = 32;
+constexpr int64_t kBwdShort = (int64_t)1 << 20;
 constexpr int64_t bwd_flush_fine(int64_t samples)
 {
-    return samples >> 20 < 1 ? 1 : samples >> 20 < 16 ? samples >> 20 : 16;
+    return samples < kBwdShort ? std::max<int64_t>(samples >> 18, 1) : std::min<int64_t>(samples >> 20, 16);
 }
 
 // FP64 sums of table entry q's four coefficient-gradient partials (two for
@@ -553,6 +559,109 @@ __global__ void __launch_bounds__(kBlock, bwd_blocks(NI, L, DX && DC)) bwd_kerne
     }
 }
 
+// The coefficient gradient of short "fine" inputs (below kBwdShort samples), taps K0
+// .. K0 + L - 1: the rows one after the other, a sample per lane, so that a lane's
+// FP32 sums cover one sample per 2^18 of the input before they go to FP64; a chunk
+// of four would round more (32 rows of 20001 samples, six taps: relative error 0.61e-7,
+// in bwd_kernel 0.77e-7).  A tap past the row's end adds nothing, whatever x holds.
+// Bound by the wave sums in FP64, each longer than a 64-sample step (23 us there, 154
+// with one thread per sample and a pass over the rows per sixteen entries).
+template <int NI, int L, int K0>
+__global__ void __launch_bounds__(kBlock) bwd_dc_short_kernel(BwdParams p)
+{
+    constexpr int WAVES = kBlock / 64, NM = 4 * L * NI, E = NM + (K0 == 0 ? 2 : 0), NGT = (E + 63) / 64;
+    __shared__ double red[WAVES * E];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int total = (int)(p.rows * p.n), n = (int)p.n;
+    const int nw = (int)gridDim.x * WAVES;
+    float acc[E];
+    double tot[NGT];
+#pragma unroll
+    for (int e = 0; e < E; ++e) acc[e] = 0.f;
+#pragma unroll
+    for (int g = 0; g < NGT; ++g) tot[g] = 0.0;
+    struct In {
+        float2 v, g[L];
+        int taps;   // of this pass inside the row
+    };
+    const auto load = [&](int c) {
+        In r;
+        const int i = 64 * c + lane, q = i < total ? i : total - 1;
+        const int row = (int)((uint32_t)q / (uint32_t)n), m = q - row * n;
+        const int64_t at = row * p.ld + m;
+        r.v = p.x[at];
+        r.taps = i < total ? n - m - K0 : 0;
+#pragma unroll
+        for (int k = 0; k < L; ++k) r.g[k] = p.gz[at + (m + K0 + k < n ? K0 + k : 0)];
+        return r;
+    };
+    const int chunks = (total + 63) / 64;
+    int held = 0;
+    int c = (int)blockIdx.x * WAVES + wv;
+    if (c < chunks) {
+        In r = load(c);
+        while (true) {
+            const int next = c + nw;
+            const In a = r;
+            if (next < chunks) r = load(next);
+            float ba[NI], bb[NI];
+            const float s = __builtin_fmaf(a.v.x, a.v.x, a.v.y * a.v.y);
+            float w = 1.f;
+#pragma unroll
+            for (int j = 0; j < NI; ++j) {
+                ba[j] = w * a.v.x;
+                bb[j] = w * a.v.y;
+                w *= s;
+            }
+#pragma unroll
+            for (int k = 0; k < L; ++k) {
+                if (k < a.taps) {
+#pragma unroll
+                    for (int j = 0; j < NI; ++j) {
+                        float *e = acc + 4 * (k * NI + j);
+                        e[0] = __builtin_fmaf(a.g[k].x, ba[j], e[0]);
+                        e[1] = __builtin_fmaf(a.g[k].x, bb[j], e[1]);
+                        e[2] = __builtin_fmaf(a.g[k].y, ba[j], e[2]);
+                        e[3] = __builtin_fmaf(a.g[k].y, bb[j], e[3]);
+                    }
+                    if (K0 == 0 && k == 0) {
+                        acc[E - 2] += a.g[0].x;
+                        acc[E - 1] += a.g[0].y;
+                    }
+                }
+            }
+            if (++held == p.flush || next >= chunks) {
+                wave_sums_into<double, E>(acc, tot, lane);
+#pragma unroll
+                for (int e = 0; e < E; ++e) acc[e] = 0.f;
+                held = 0;
+            }
+            if (next >= chunks) break;
+            c = next;
+        }
+    }
+    // as bwd_kernel: wave FP64 totals -> block -> one FP32 partial per block
+#pragma unroll
+    for (int g = 0; g < NGT; ++g)
+        if (64 * g + lane < E) red[wv * E + 64 * g + lane] = tot[g];
+    __syncthreads();
+    for (int e = tid; e < E; e += kBlock) {
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) t += red[w * E + e];
+        const int at = e < NM ? 4 * NI * K0 + e : p.E - 2 + (e - NM);
+        p.partials[(int64_t)blockIdx.x * p.E + at] = (float)t;
+    }
+}
+
+template <int NI, int L, int K0 = 0>
+hipError_t launch_bwd_short(const BwdParams &p, hipStream_t stream, int grid)
+{
+    hipLaunchKernelGGL((bwd_dc_short_kernel<NI, L, K0>), dim3((uint32_t)grid), dim3(kBlock), 0, stream, p);
+    return hipGetLastError();
+}
+
 template <int NI, int L, bool DX, bool DC, int K0 = 0>
 hipError_t launch_bwd(const BwdParams &p, hipStream_t stream, int grid)
 {
@@ -570,7 +679,10 @@ void register_bwd_one(BwdTable &t)
         t.fn[NI - 1][L - 1][2] = &launch_bwd<NI, L, true, true>;
         t.kern[NI - 1][L - 1][1] = (const void *)&bwd_kernel<NI, L, false, true>;
         t.kern[NI - 1][L - 1][2] = (const void *)&bwd_kernel<NI, L, true, true>;
-        t.tail[NI - 1][L - 1] = &launch_bwd<NI, L, false, true, kSpecL>;
+        t.fn[NI - 1][L - 1][3] = &launch_bwd_short<NI, L>;
+        t.kern[NI - 1][L - 1][3] = (const void *)&bwd_dc_short_kernel<NI, L, 0>;
+        t.tail[NI - 1][L - 1][0] = &launch_bwd<NI, L, false, true, kSpecL>;
+        t.tail[NI - 1][L - 1][1] = &launch_bwd_short<NI, L, kSpecL>;
     }
 }
 

@@ -240,14 +240,15 @@ DPD_EXPORT dpd_status dpd_transmit_backward(const dpd_plan *P, const dpd_plan *A
     // without a dE/dz buffer: only the shapes that never needed one
     if (N > 0 && grad_z == nullptr && !(ln_stages_ok(P, A, B) && one_call_shapes(x, z, grad_y, grad_z, n, rs)))
         return DPD_EUNSUPPORTED;
-    if (!ln_stages_ok(P, A, B)) {
-        // other stages: the two passes, dE/dz through the caller's grad_z
+    const bool fine = (uintptr_t)x % 16 != 0 || (uintptr_t)grad_z % 16 != 0 || (rows > 1 && ld % 2 != 0);
+    if (!ln_stages_ok(P, A, B) || (N > 0 && fine && N < kBwdShort)) {
+        // other stages, and short inputs whose gradient bwd_dc_short_kernel sums: the
+        // two passes, dE/dz through the caller's grad_z
         dpd_status st = dpd_cascade_backward(A, B, stream, z, grad_y, grad_z, rows, n, ld);
         if (st != DPD_OK) return st;
         return dpd_backward(const_cast<dpd_plan *>(P), stream, nullptr, x, grad_z, nullptr, grad_coeffs, rows, n,
                             ld, ws, ws_bytes);
     }
-    const bool fine = (uintptr_t)x % 16 != 0 || (uintptr_t)grad_z % 16 != 0 || (rows > 1 && ld % 2 != 0);
     int nblk = 0, nloss = 0;
     hipError_t e = hipSuccess;
     if (N > 0)

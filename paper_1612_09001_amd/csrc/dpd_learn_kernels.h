@@ -11,11 +11,11 @@
 // On rows of whole 256s all three walk the data in the same way and use the same
 // arithmetic in the same order, so kLnBoth gives the bits of the other two.
 //
-// What bounds it: VALU issue (about 330 instructions per sample against 24
+// What bounds it: VALU issue (336 instructions per sample against 24
 // bytes), so every value is computed once and the two passes as one save the
 // second pass's loads, staging and stage A.  Measured on 64 rows of 2^18 samples
 // (a whole step with its finalisation): NI = 4, L = 6 144 us, NI = 4, L = 8 163, NI =
-// 2, L = 2 97; as two calls of 24 bytes per sample each 185, 203 and 154 us.  Rows that
+// 2, L = 2 94; as two calls of 24 bytes per sample each 185, 203 and 154 us.  Rows that
 // are not whole 256s (16 x 40001, L = 6): 39 us.
 //
 // Each wave takes a contiguous run of chunks of 64 S samples of the flattened rows
@@ -33,7 +33,8 @@
 // The per-lane FP32 sums of the gradient cover at most 128 samples, are added up
 // over the wave in FP32 and go to its FP64 totals; for rows at odd 8-byte starts or
 // strides ("fine", as in dpd_backward) they cover at most 64 samples, one per 2^18
-// of the input but at least a chunk's, and are added up in FP64.  Loss and gradient
+// of the input but at least a chunk's, and are added up in FP64 (inputs so short that
+// a chunk's are too many go through dE/dz to bwd_dc_short_kernel).  Loss and gradient
 // leave as FP32 partials, one per block.
 #pragma once
 
@@ -196,7 +197,7 @@ constexpr int ln_blocks(int mode, int E) { return mode == kLnFwd || E <= 130 ? 2
 // Where the gradient leaves one block per CU, a run of the one pass on rows of whole
 // chunks has two parts for the loss, each with sums of its own, and the forward pass
 // gives the second part to another wave: two blocks per CU, and the same bits (64
-// rows of 2^18 at NI = 5, L = 7: 123 us with one block).
+// rows of 2^18 at NI = 5, L = 7: 123 us with one, 92 with two).
 constexpr bool ln_parts(int E, int walk) { return ln_blocks(kLnBoth, E) == 1 && (walk == kLn4 || walk == kLn8); }
 
 template <int NI, int L, int MODE, int WALK>

@@ -353,3 +353,56 @@ def test_rows_shorter_than_a_chunk(torch, dpd, orc, mo, co, L):
         alone = torch.full((rows, ld), complex(7.0, -7.0), dtype=torch.complex64, device="cuda")
         dpd.dpd_backward(plan.handle, dpd.current_stream(), 0, xd.data_ptr(), gd.data_ptr(), alone.data_ptr(), 0, rows, n, ld, 0, 0)
         assert np.array_equal(alone.cpu().numpy(), out), n
+
+
+@pytest.mark.parametrize("L", [1, 3, 8, 9, 16])
+@pytest.mark.parametrize("rows,n,off", [(1, 7, 1), (3, 63, 1), (3, 20001, 0), (2, 100001, 1), (1, (1 << 18) - 1, 1)])
+def test_gradient_sums_of_short_odd_inputs(torch, dpd, L, rows, n, off):
+    """Rows at odd starts or strides below 2^18 samples: no two samples are added in
+    FP32.  dE/dh and dE/dc = sum G (x = 1) with every fourth sample +-1 in turn and
+    2^-25 else, which any FP32 sum of a sample and its neighbour loses; +-1 cancel in
+    every run of eight.  Each block's partial is rounded once (1 to 9 at a row's end
+    or a run's: at most half of 2^-20)."""
+    plan = dpd.Plan([1], [], L, np.ones(L + 1, dtype=np.complex64))
+    m = np.arange(n)
+    row = np.where(m % 4 == 0, np.where(m % 8 == 0, 1.0, -1.0), 2.0 ** -25)
+    G = torch.zeros(rows * n + off, dtype=torch.complex64, device="cuda")[off:].view(rows, n)
+    G.copy_(torch.from_numpy(np.tile(row, (rows, 1)).astype(np.complex64)))
+    x = torch.ones(rows * n + off, dtype=torch.complex64, device="cuda")[off:].view(rows, n)
+    gx, gc = plan.backward(x, G)
+    gx2, _ = plan.backward(x.clone(), G.clone())
+    assert torch.equal(gx, gx2)
+    for k in range(L):
+        want = rows * row[k:].sum()
+        ends = 2 * rows + 2      # runs of 64 samples that hold a row's start or end
+        assert abs(complex(gc[k].item()) - want) <= ends * 2.0 ** -24 + 2.0 ** -23 * abs(want), (k, gc[k], want)
+    want = rows * row.sum()
+    assert abs(complex(gc[L].item()) - want) <= ends * 2.0 ** -24 + 2.0 ** -23 * abs(want)
+
+
+@pytest.mark.parametrize("mo,co,L", [([1], [], 1), ([1, 3, 5, 7], [1, 3, 5, 7], 6), ([1, 3], [1], 8), ([1, 3, 5], [1, 3], 11),
+                                     (list(range(1, 16, 2)), list(range(1, 16, 2)), 16)])
+def test_gradient_of_short_odd_inputs(torch, dpd, orc, mo, co, L):
+    """The coefficient gradient of rows at odd starts below 2^20 samples against the
+    oracle: rows shorter than the filter, of a wave's 64 samples and around them, and
+    both sides of the size where another kernel takes over; an infinity in the last
+    sample of x stays in the tap that reads it."""
+    h = signals.aph_coeffs(mo, co, L, config_id=97)
+    plan = dpd.Plan(mo, co, L, h)
+    for rows, n in ((1, 1), (5, 3), (2, 63), (3, 64), (3, 65), (7, 1001), (1, (1 << 20) - 1), (1, (1 << 20) + 1)):
+        x = np.stack([signals.ofdm_16qam(n, config_id=97, stream_id=r) for r in range(rows)])
+        G = signals.cgauss((rows, n), config_id=97, stream_id=n % 1000)
+        rc = sum(orc.backward(x[r], mo, co, L, h, G[r])[1] for r in range(rows))
+        def odd(v):
+            t = torch.zeros(rows * n + 1, dtype=torch.complex64, device="cuda")[1:].view(rows, n)
+            return t.copy_(_dev(torch, v))
+        xd, gd = odd(x), odd(G)
+        _, gc = plan.backward(xd, gd, want_dx=False)
+        scale = np.sqrt((np.abs(G) ** 2).sum() * (np.abs(x) ** 2).sum()) + np.abs(G).sum() + np.abs(rc)
+        assert np.all(np.abs(gc.cpu().numpy() - rc) <= 2e-6 * scale), (rows, n)
+        if n > L and n < 2000:
+            xd[:, -1] = complex(float("inf"), 0.0)
+            _, gc = plan.backward(xd, gd, want_dx=False)
+            bad = ~torch.isfinite(torch.view_as_real(gc)).all(-1)
+            taps = torch.arange(plan.K - 1, device="cuda") % L
+            assert bool(bad[:-1][taps == 0].all()) and not bool(bad[:-1][taps > 0].any()) and not bool(bad[-1]), n
