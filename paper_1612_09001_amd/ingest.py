@@ -18,8 +18,8 @@ libdpd's.
 ``ZeroCopy`` is the paper's zero-copy form on this machine: the kernel reads
 and writes the pinned host buffers in place through their device mapping, so
 every sample crosses the host link inside the kernel and nothing is staged in
-HBM.  On MI355X it measured about 1.5 times the rate of the copy pipeline
-(41.7 against 28.5 GB/s each way with two buffers, 2^25 samples).
+HBM.  On MI355X it measured 1.3 times the rate of the copy pipeline (42.3
+against 32.0 GB/s each way, 2^25 samples).
 """
 from __future__ import annotations
 
